@@ -184,8 +184,10 @@ moeq_status moeq_forward(moeq_layer* layer, const void* x, const float* logits,
  *             DEVICE (current device) per location (MOEQ_WEIGHTS_*); NULL
  *             removes the weight and frees its memory
  * Copied; the caller may free w on return.  Allocates, on the first set,
- * n_experts * hidden * 4 bytes for the weight and max_tokens * n_experts * 4
- * for the logits a forward computes.  Synchronizes the device (do not call
+ * n_experts * hidden * 4 bytes for the weight, max_tokens * n_experts * 4
+ * for the logits a forward computes and, if max_tokens > 8, up to
+ * 8 * min(max_tokens, 4096) * (n_experts rounded up to 32) * 4 for the gate's
+ * partial sums.  Synchronizes the device (do not call
  * while a forward of this layer is being captured).
  * Errors: INVALID_ARG (location, a non-finite HOST element), OUT_OF_MEMORY,
  * DEVICE. */
@@ -194,8 +196,9 @@ moeq_status moeq_set_router_weight(moeq_layer* layer, const float* w, int32_t lo
 /* The gate alone: logits = x W_r^T with the set weight, float32 products and
  * sums.  Each logit is accumulated in a fixed order that depends only on
  * whether n_tokens <= 8 (one streaming pass per expert, per-thread partial
- * sums over strided columns combined by a fixed tree) or not (one fused
- * multiply-add chain over the hidden index), so results are deterministic.
+ * sums over strided columns combined by a fixed tree) or not (32 runs of the
+ * hidden index on the matrix cores, combined by a fixed tree), so results are
+ * deterministic.
  *   x        DEVICE bfloat16 [n_tokens x hidden], 16-byte aligned
  *   n_tokens 0..max_tokens
  *   logits   DEVICE float32 [n_tokens x n_experts] (written)

@@ -104,7 +104,8 @@ struct moeq_layer {
   int down_bits = 0;                   // width of every kept and shared down tensor when they agree
   int32_t* kept_ids = nullptr;  // kept experts ascending, when the router regroups them
   float* router_w = nullptr;    // float32 [n_experts x hidden] gate weight, when set
-  float* gate_logits = nullptr; // float32 [max_tokens x n_experts], logits the forward computes
+  float* gate_logits = nullptr; // float32 [max_tokens x n_experts], logits the forward computes, and
+  float* gate_part = nullptr;   // (in the same allocation) the gate's partial sums
   void* ws_mem = nullptr;
   Workspace ws{};
   hipEvent_t stage_events[MOEQ_STAGE_EVENTS] = {};
@@ -578,7 +579,7 @@ moeq_status moeq_forward(moeq_layer* L, const void* x, const float* logits, int3
   mark(0);
   if (!logits) {
     if (e == hipSuccess)
-      e = launch_router_gate(a.x, L->router_w, n, a.H, a.E, L->gate_logits, s);
+      e = launch_router_gate(a.x, L->router_w, n, a.H, a.E, L->gate_part, L->gate_logits, s);
     logits = L->gate_logits;
   }
   // one token: the gate/up workgroups route the token themselves
@@ -634,17 +635,20 @@ moeq_status moeq_set_router_weight(moeq_layer* L, const float* w, int32_t locati
     hipFree(L->gate_logits);
     L->router_w = nullptr;
     L->gate_logits = nullptr;
+    L->gate_part = nullptr;
     return ok();
   }
   if (!L->router_w) {
     float *rw = nullptr, *lg = nullptr;
     if ((e = hipMalloc((void**)&rw, wb)) != hipSuccess) return hip_fail(e, "hipMalloc(router weight)");
-    if ((e = hipMalloc((void**)&lg, (size_t)L->cfg.max_tokens * E * 4)) != hipSuccess) {
+    const size_t nl = align_up((size_t)L->cfg.max_tokens * E, 64);
+    if ((e = hipMalloc((void**)&lg, (nl + gate_part_floats(L->cfg.max_tokens, E)) * 4)) != hipSuccess) {
       hipFree(rw);
       return hip_fail(e, "hipMalloc(router logits)");
     }
     L->router_w = rw;
     L->gate_logits = lg;
+    L->gate_part = lg + nl;
   }
   e = hipMemcpy(L->router_w, w, wb, location == MOEQ_WEIGHTS_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice);
   if (e != hipSuccess || (e = hipDeviceSynchronize()) != hipSuccess) return hip_fail(e, "hipMemcpy(router weight)");
@@ -662,7 +666,7 @@ moeq_status moeq_router_logits(moeq_layer* L, const void* x, int32_t n, float* l
   moeq_status st = check_device(L);
   if (st != MOEQ_OK) return st;
   const hipError_t e = launch_router_gate((const uint16_t*)x, L->router_w, n, L->cfg.hidden, L->cfg.n_experts,
-                                          logits, (hipStream_t)stream);
+                                          L->gate_part, logits, (hipStream_t)stream);
   return e == hipSuccess ? ok() : hip_fail(e, "router gate launch");
 }
 

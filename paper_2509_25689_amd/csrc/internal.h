@@ -165,9 +165,18 @@ hipError_t launch_down_decode(const DecodeArgs& a, hipStream_t s);
 bool down_combines(const DecodeArgs& a);
 hipError_t launch_combine(const DecodeArgs& a, hipStream_t s);
 // gate.hip: logits = x W_r^T (bf16 x [n x H], float32 W_r [E x H]); up to
-// kGateFewTokens tokens take the streaming kernel, more the tiled one
+// kGateFewTokens tokens take the streaming kernel, more the matrix cores, at
+// most kGateChunk at a time with partial sums in `part` (gate_part_floats)
 constexpr int kGateFewTokens = 8;
-hipError_t launch_router_gate(const uint16_t* x, const float* w, int n, int H, int E, float* logits,
+constexpr int kGateSplit = 8;     // runs of the hidden index over the grid
+constexpr int kGateChunk = 4096;  // tokens whose partial sums are held at a time
+__host__ __device__ constexpr int gate_pitch(int E) { return (E + 31) / 32 * 32; }
+constexpr size_t gate_part_floats(int max_tokens, int E) {
+  return max_tokens <= kGateFewTokens
+             ? 0
+             : (size_t)kGateSplit * (max_tokens < kGateChunk ? max_tokens : kGateChunk) * gate_pitch(E);
+}
+hipError_t launch_router_gate(const uint16_t* x, const float* w, int n, int H, int E, float* part, float* logits,
                               hipStream_t s);
 // prune.hip
 hipError_t launch_fill_u8(uint8_t* p, int n, uint8_t v, hipStream_t s);

@@ -84,6 +84,34 @@ def test_gate_within_float32_bound(v3_gate, n):
     assert np.max(np.abs(got - ref)) < 1e-4
 
 
+@pytest.mark.parametrize("E,H", [(40, 128), (24, 1152)])
+def test_gate_matrix_core_edges(gpu_lib, E, H):
+    """The many-token gate at the edges of its tiles (32 and 128 tokens, 32
+    experts) and with fewer hidden groups than runs (H = 128) or runs of
+    unequal length (H = 1152): exact on the grid, the same for a token
+    whatever n is, and an infinite x gives what the multiply-add chain gives."""
+    shape = synth.LayerShape(hidden=H, inter=128, n_experts=E, n_kept=E, n_shared=0, n_group=1, topk_group=1, top_k=2)
+    data = layers.quantized_layer(shape, "all2", f"gate-edge-{E}")
+    L = gpu_lib.Layer(shape, data.mask, data.routed(), [], max_tokens=161)
+    w = synth.grid_router_weight(E, H, "gate-edge", E)
+    L.set_router_weight(w)
+    x_bits = synth.grid_activations(161, H, "gate-edge", E)
+    ref = router.gate_logits(x_bits, w)
+    for n in (9, 31, 32, 33, 64, 65, 128, 129, 161):
+        got = L.router_logits(_xdev(x_bits[:n])).cpu().numpy().astype(np.float64)
+        assert np.array_equal(got, ref[:n]), n
+    x_bits = synth.activations(70, H, "gate-edge-normal", E)
+    many = L.router_logits(_xdev(x_bits))
+    assert torch.equal(many[:9], L.router_logits(_xdev(x_bits[:9])))
+    x_bits[3, 5] = 0x7F80   # +infinity
+    got = L.router_logits(_xdev(x_bits)).cpu().numpy()
+    assert np.array_equal(np.delete(got, 3, 0), np.delete(many.cpu().numpy(), 3, 0))
+    with np.errstate(invalid="ignore"):
+        chain = np.float32(np.inf) * w[:, 5]   # (0 * inf: NaN)
+    assert np.array_equal(got[3], chain, equal_nan=True)
+    L.close()
+
+
 def test_gate_deterministic(v3_gate):
     data, L = v3_gate
     E, H = data.shape.n_experts, data.shape.hidden
