@@ -150,49 +150,104 @@ __global__ __launch_bounds__(256) void dequant_sub_kernel(TensorDev t, float* ou
   }
 }
 
-// float64 -> binary16 bit pattern, round to nearest even; v >= 0
-__device__ uint16_t half_rne_from_double(double v) {
-  if (!(v > 0.0)) return 0;
-  if (v >= 65520.0) return 0x7C00;  // at or above the midpoint to 2^16: infinity
-  int ex;
-  frexp(v, &ex);
-  int e2 = ex - 1;  // v in [2^e2, 2^(e2+1))
-  if (e2 < -14) return (uint16_t)rint(ldexp(v, 24));  // subnormal, units of 2^-24 (1024 = min normal)
-  double m = rint(ldexp(v, 10 - e2));               // in [1024, 2048]
-  if (m == 2048.0) {
-    m = 1024.0;
-    ++e2;
+// binary16 of amax / qm, rounded once to nearest even from the exact quotient:
+// the float32 quotient is made odd when it is inexact (truncated, last bit
+// set), so that the second rounding sees which side of a tie the exact value
+// lies on.
+__device__ __forceinline__ uint16_t half_rne_quotient(float amax, float qm) {
+  const float q = amax / qm;  // correctly rounded
+  const float r = fmaf(-q, qm, amax);
+  uint32_t u = __float_as_uint(q);
+  if (r != 0.0f && q < 65536.0f) {
+    if (r < 0.0f) --u;
+    u |= 1u;
   }
-  return (uint16_t)(((e2 + 15) << 10) | ((int)m - 1024));
+  return __builtin_bit_cast(uint16_t, (_Float16)__uint_as_float(u));
 }
 
-// one thread per block of 32
-__global__ __launch_bounds__(256) void quantize_kernel(const float* w, int rows, int K, int bits,
-                                                       uint8_t* codes, uint16_t* scales) {
-  const int nb = K / kBlock;
-  const long long gid = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (gid >= (long long)rows * nb) return;
-  const float* src = w + gid * kBlock;  // row-major, blocks contiguous
-  float amax = 0.0f;
-  for (int i = 0; i < kBlock; ++i) amax = fmaxf(amax, fabsf(src[i]));
-  const int qm = (1 << (bits - 1)) - 1, z = 1 << (bits - 1);
-  const uint16_t hb = half_rne_from_double((double)amax / (double)qm);
-  scales[gid] = hb;
-  const double d = (double)half_to_float(hb);
-  uint32_t acc[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};  // 32 * bits <= 256 bits
-  for (int i = 0; i < kBlock; ++i) {
-    int q = 0;
-    if (d > 0.0) {
-      const double qq = rint((double)src[i] / d);
-      q = (int)fmin(fmax(qq, (double)-qm), (double)qm);
+// clamp(rint(w / d), -qm, qm), ties to even from the exact quotient; d > 0 or
+// infinite (then 0), inv = 1 / d.  w * inv is within 2^-22 of the quotient
+// relatively, so the rounded product k is off by at most one and only next to
+// a tie; the remainder w - k d is exact (one fused multiply-add) and decides.
+__device__ __forceinline__ int quantize_code(float w, float d, float inv, float qm) {
+  float k = rintf(fminf(fmaxf(w * inv, -256.0f), 256.0f));
+  const float r2 = 2.0f * fmaf(-k, d, w), a = fabsf(r2);
+  const bool odd = (int)k & 1;
+  if (a > d || (a == d && odd)) k += r2 > 0.0f ? 1.0f : -1.0f;
+  return (int)fminf(fmaxf(k, -qm), qm);
+}
+
+// Eight values per lane, four lanes per block of 32, kQuantSteps wave-wide
+// pieces of 512 values per wave with all their loads in flight; the lanes'
+// packed bits meet in LDS and leave as dwords.  Memory-bound: 4 bytes read
+// and bits / 8 written per value (16 us for 2048 x 7168 at 3 bits, 4 TB/s).  One thread per block (128-byte strides
+// between lanes, a byte store per code byte, double-precision quotients) took
+// 233 us.
+// ALIGNED: w on 16 bytes and codes on 4 (else element loads, byte stores).
+constexpr int kQuantSteps = 2;
+template <int B, bool ALIGNED>
+__global__ __launch_bounds__(256) void quantize_kernel(const float* w, long long n, uint8_t* codes,
+                                                       uint16_t* scales) {
+  __shared__ uint32_t bits_l[4][kQuantSteps][16 * B];  // 64 * B bytes per wave piece
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const long long base = ((long long)blockIdx.x * 4 + wave) * (512 * kQuantSteps);  // the wave's first value
+  constexpr int z = 1 << (B - 1);
+  constexpr float qm = (float)(z - 1);
+  float f[kQuantSteps][8];
+#pragma unroll
+  for (int s = 0; s < kQuantSteps; ++s) {
+    const long long i = base + 512 * s + 8 * lane;
+    // (n is a multiple of 32: a block's four lanes are all in or all out)
+    if (i < n) {
+      if constexpr (ALIGNED) {
+        const MOEQ_GLOBAL f32x4* src = gptr(reinterpret_cast<const f32x4*>(w + i));
+        const f32x4 v0 = src[0], v1 = src[1];
+        f[s][0] = v0.x; f[s][1] = v0.y; f[s][2] = v0.z; f[s][3] = v0.w;
+        f[s][4] = v1.x; f[s][5] = v1.y; f[s][6] = v1.z; f[s][7] = v1.w;
+      } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) f[s][j] = w[i + j];
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) f[s][j] = 0.0f;
     }
-    const uint32_t c = (uint32_t)(q + z);
-    const int bit = i * bits;
-    acc[bit >> 5] |= c << (bit & 31);
-    if ((bit & 31) + bits > 32) acc[(bit >> 5) + 1] |= c >> (32 - (bit & 31));
   }
-  uint8_t* dst = codes + gid * 4 * bits;
-  for (int i = 0; i < 4 * bits; ++i) dst[i] = (uint8_t)(acc[i >> 2] >> (8 * (i & 3)));
+#pragma unroll
+  for (int s = 0; s < kQuantSteps; ++s) {
+    float am = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) am = fmaxf(am, fabsf(f[s][j]));
+    am = fmaxf(am, __shfl_xor(am, 1, 64));
+    am = fmaxf(am, __shfl_xor(am, 2, 64));
+    const uint16_t hb = half_rne_quotient(am, qm);
+    const float d = half_to_float(hb);
+    const float inv = 1.0f / d;
+    uint64_t acc = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int q = d > 0.0f ? quantize_code(f[s][j], d, inv, qm) : 0;
+      acc |= (uint64_t)(uint32_t)(q + z) << (B * j);
+    }
+    const long long i = base + 512 * s + 8 * lane;
+    if (i < n && (lane & 3) == 0) scales[i / kBlock] = hb;
+    uint8_t* dst = reinterpret_cast<uint8_t*>(bits_l[wave][s]) + lane * B;
+#pragma unroll
+    for (int j = 0; j < B; ++j) dst[j] = (uint8_t)(acc >> (8 * j));
+  }
+  __syncthreads();
+#pragma unroll
+  for (int s = 0; s < kQuantSteps; ++s) {
+    const long long i = base + 512 * s;
+    const int nb = (int)(min(512ll, max(0ll, n - i)) * B / 8);  // bytes of this piece, a multiple of 4 B
+    uint8_t* dst = codes + i * B / 8;
+    if constexpr (ALIGNED) {
+      for (int j = lane; j < nb / 4; j += 64) reinterpret_cast<uint32_t*>(dst)[j] = bits_l[wave][s][j];
+    } else {
+      const uint8_t* src = reinterpret_cast<const uint8_t*>(bits_l[wave][s]);
+      for (int j = lane; j < nb; j += 64) dst[j] = src[j];
+    }
+  }
 }
 
 }  // namespace
@@ -280,10 +335,29 @@ hipError_t launch_dequant(const TensorDev& t, float* out, hipStream_t s) {
   return hipGetLastError();
 }
 
+namespace {
+template <int B>
+void quantize_launch(const float* w, long long n, uint8_t* codes, uint16_t* scales, hipStream_t s) {
+  const int grid = (int)((n + 2048 * kQuantSteps - 1) / (2048 * kQuantSteps));
+  if (((uintptr_t)w & 15) == 0 && ((uintptr_t)codes & 3) == 0)
+    quantize_kernel<B, true><<<grid, 256, 0, s>>>(w, n, codes, scales);
+  else
+    quantize_kernel<B, false><<<grid, 256, 0, s>>>(w, n, codes, scales);
+}
+}  // namespace
+
 hipError_t launch_quantize(const float* w, int rows, int K, int bits, uint8_t* codes,
                            uint16_t* scales, hipStream_t s) {
-  const long long n = (long long)rows * (K / kBlock);
-  quantize_kernel<<<(int)((n + 255) / 256), 256, 0, s>>>(w, rows, K, bits, codes, scales);
+  const long long n = (long long)rows * K;
+  switch (bits) {
+    case 2: quantize_launch<2>(w, n, codes, scales, s); break;
+    case 3: quantize_launch<3>(w, n, codes, scales, s); break;
+    case 4: quantize_launch<4>(w, n, codes, scales, s); break;
+    case 5: quantize_launch<5>(w, n, codes, scales, s); break;
+    case 6: quantize_launch<6>(w, n, codes, scales, s); break;
+    case 8: quantize_launch<8>(w, n, codes, scales, s); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 

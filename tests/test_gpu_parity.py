@@ -89,6 +89,47 @@ def test_quantize_bit_exact(gpu_lib, bits):
     assert np.array_equal(codes.cpu().numpy(), quant.pack(ref_c, bits))
 
 
+@pytest.mark.parametrize("bits", [2, 3, 4, 5, 6, 8])
+def test_quantize_edges(gpu_lib, bits):
+    """Every width at ragged sizes, with misaligned buffers (byte stores), and
+    with blocks at the limits: exact ties, one-sided near ties, quotients that
+    round to a subnormal, zero or infinite scale, float32 subnormals."""
+    qm = 2 ** (bits - 1) - 1
+    w = synth.normal_weights(67, 992, "quantize-edge", bits)
+    d = np.float32(2.0 ** -7)
+    ties = ((np.arange(32) % (2 * qm)) - qm + 0.5).astype(np.float32) * d
+    ties[0] = qm * d                                   # the block's scale is d exactly
+    for r, blk in enumerate([ties, np.nextafter(ties, np.float32(np.inf)), np.nextafter(ties, np.float32(-np.inf)),
+                             ties * np.float32(2.0 ** -15), ties * np.float32(2.0 ** -17), ties * np.float32(2.0 ** -130),
+                             ties * np.float32(2.0 ** 23), ties * np.float32(2.0 ** 110)]):
+        w[r, 32:64] = blk
+    # scales next to binary16 ties: the quotient a little off a midpoint
+    w[8:40, :32] = np.float32(0.0)
+    w[8:40, 0] = np.nextafter(np.float32((1 + 2.0 ** -11) * qm * 0.01) * np.ones(32, np.float32),
+                              np.where(np.arange(32) % 2, np.float32(9), np.float32(0)))
+    for i in range(32):
+        for _ in range(i // 2):
+            w[8 + i, 0] = np.nextafter(w[8 + i, 0], np.float32(9 if i % 2 else 0))
+    with np.errstate(over="ignore", invalid="ignore", divide="ignore"):
+        ref_c, ref_s = quant.quantize(w, bits)
+    ref_c = quant.pack(ref_c, bits)
+    n = w.size
+    for rows in (67, 1):
+        c, s = gpu_lib.quantize(_dev(w[:rows]), bits)
+        assert np.array_equal(s.cpu().numpy().view(np.uint16), ref_s[:rows])
+        assert np.array_equal(c.cpu().numpy(), ref_c[:rows])
+    # the same with w on 4 bytes and codes on 1
+    wb = torch.zeros(n + 1, device="cuda")
+    wb[1:] = _dev(w).view(-1)
+    cb = torch.zeros(n * bits // 8 + 1, dtype=torch.uint8, device="cuda")
+    sb = torch.zeros(n // 32, dtype=torch.int16, device="cuda")
+    gpu_lib.moeq_quantize(wb.data_ptr() + 4, 67, 992, bits, cb.data_ptr() + 1, sb.data_ptr(),
+                          torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert np.array_equal(sb.cpu().numpy().view(np.uint16), ref_s.ravel())
+    assert np.array_equal(cb.cpu().numpy()[1:], ref_c.ravel()) and int(cb[0]) == 0
+
+
 @pytest.mark.parametrize("which", ["tiny", "tiny_mixed"])
 def test_dequant_bit_exact_every_tensor(request, which):
     data, L = request.getfixturevalue(which)
