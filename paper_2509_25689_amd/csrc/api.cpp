@@ -297,7 +297,7 @@ moeq_status moeq_layer_create(const moeq_config* cfg, const uint8_t* expert_mask
 
   // ---- plan the weight store: one allocation, 256-byte aligned tensors ----
   std::vector<TensorPlan> plan((size_t)(E + S) * 3);
-  size_t off = 0, max_codes = 0;
+  size_t off = 0, max_codes = 0, max_scales = 0;
   uint64_t wbytes = 0;
   auto plan_tensor = [&](int slot, int p, const moeq_qtensor& t) {
     TensorPlan& tp = plan[(size_t)slot * 3 + p];
@@ -307,9 +307,10 @@ moeq_status moeq_layer_create(const moeq_config* cfg, const uint8_t* expert_mask
     const size_t cb = (size_t)tp.rows * tp.K * t.bits / 8, sb = (size_t)tp.rows * (tp.K / kBlock) * 2;
     tp.codes_off = off;
     off = align_up(off + cb, 256);
-    tp.scales_off = off;
-    off = align_up(off + sb, 256);
+    tp.scales_off = off;  // by pairs of units
+    off = align_up(off + (size_t)tp.rows * ((tp.K / kUnit + 1) / 2) * 16, 256);
     max_codes = cb > max_codes ? cb : max_codes;
+    max_scales = sb > max_scales ? sb : max_scales;
     wbytes += cb + sb;
   };
   for (int e = 0; e < E; ++e)
@@ -365,7 +366,7 @@ moeq_status moeq_layer_create(const moeq_config* cfg, const uint8_t* expert_mask
     return hip_fail(he, "hipGetDevice");
   }
   uint8_t* staging = nullptr;
-  uint32_t* scale_keys = nullptr;  // per descriptor: the largest scale key (launch_scale_key_max)
+  uint32_t* scale_keys = nullptr;  // per descriptor: the largest scale key (launch_repack_scales)
   auto bail = [&](hipError_t e, const char* what) {
     hipStreamSynchronize(nullptr);
     hipFree(staging);
@@ -388,7 +389,7 @@ moeq_status moeq_layer_create(const moeq_config* cfg, const uint8_t* expert_mask
   }
   if ((he = hipMalloc((void**)&L->bias, sizeof(float) * E)) != hipSuccess) return bail(he, "hipMalloc(bias)");
   if (weights_location == MOEQ_WEIGHTS_HOST && max_codes &&
-      (he = hipMalloc((void**)&staging, max_codes)) != hipSuccess)
+      (he = hipMalloc((void**)&staging, align_up(max_codes, 256) + max_scales)) != hipSuccess)
     return bail(he, "hipMalloc(staging)");
   if ((he = hipMalloc((void**)&scale_keys, sizeof(uint32_t) * plan.size())) != hipSuccess ||
       (he = hipMemset(scale_keys, 0, sizeof(uint32_t) * plan.size())) != hipSuccess)
@@ -400,19 +401,18 @@ moeq_status moeq_layer_create(const moeq_config* cfg, const uint8_t* expert_mask
     const TensorPlan& tp = plan[(size_t)slot * 3 + p];
     const size_t cb = (size_t)tp.rows * tp.K * tp.bits / 8, sb = (size_t)tp.rows * (tp.K / kBlock) * 2;
     const uint8_t* src = (const uint8_t*)t.codes;
+    const uint16_t* ssrc = (const uint16_t*)t.scales;
     hipError_t e;
     if (weights_location == MOEQ_WEIGHTS_HOST) {
-      // staging is reused: the null-stream copy waits for the previous repack
-      if ((e = hipMemcpy(staging, src, cb, hipMemcpyHostToDevice)) != hipSuccess) return e;
+      // staging is reused: the null-stream copies wait for the previous repack
+      if ((e = hipMemcpy(staging, src, cb, hipMemcpyHostToDevice)) != hipSuccess ||
+          (e = hipMemcpy(staging + align_up(max_codes, 256), ssrc, sb, hipMemcpyHostToDevice)) != hipSuccess)
+        return e;
       src = staging;
+      ssrc = (const uint16_t*)(staging + align_up(max_codes, 256));
     }
-    if ((e = launch_repack(src, tp.rows, tp.K, tp.bits, (uint32_t*)(base + tp.codes_off), 0)) != hipSuccess)
-      return e;
-    if ((e = hipMemcpy(base + tp.scales_off, t.scales, sb,
-                       weights_location == MOEQ_WEIGHTS_HOST ? hipMemcpyHostToDevice
-                                                             : hipMemcpyDeviceToDevice)) != hipSuccess)
-      return e;
-    if ((e = launch_scale_key_max((const uint16_t*)(base + tp.scales_off), sb / 2,
+    if ((e = launch_repack(src, tp.rows, tp.K, tp.bits, (uint32_t*)(base + tp.codes_off), 0)) != hipSuccess ||
+        (e = launch_repack_scales(ssrc, tp.rows, tp.K, (uint16_t*)(base + tp.scales_off),
                                   scale_keys + (size_t)slot * 3 + p, 0)) != hipSuccess)
       return e;
     TensorDev& d = L->desc_host[(size_t)slot * 3 + p];
@@ -432,8 +432,7 @@ moeq_status moeq_layer_create(const moeq_config* cfg, const uint8_t* expert_mask
       if ((he = upload(E + s, p, shared[s * 3 + p])) != hipSuccess) return bail(he, "weight upload");
 
   // tensors the grouped GEMMs' register decoder cannot take (wider than 4
-  // bits, a scale outside (0, rd_scale_limit(bits)], or rows of an odd number
-  // of 128-weight units)
+  // bits, or a scale outside (0, rd_scale_limit(bits)])
   {
     std::vector<uint32_t> keys(plan.size());
     if ((he = hipMemcpy(keys.data(), scale_keys, sizeof(uint32_t) * plan.size(), hipMemcpyDeviceToHost)) !=
@@ -442,7 +441,7 @@ moeq_status moeq_layer_create(const moeq_config* cfg, const uint8_t* expert_mask
     for (size_t i = 0; i < plan.size(); ++i) {
       TensorDev& d = L->desc_host[i];
       if (!d.codes) continue;
-      if (d.bits <= 4 && (keys[i] > rd_scale_limit(d.bits) || (d.K / kUnit) % 2 != 0))
+      if (d.bits <= 4 && keys[i] > rd_scale_limit(d.bits))
         d.flags |= kTensorOffRegisterDecoder;
       if (d.bits > 4 || (d.flags & kTensorOffRegisterDecoder)) {
         if (i % 3 == 2)

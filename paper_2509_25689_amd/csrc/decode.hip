@@ -10,14 +10,12 @@
 // Work decomposition.  A workgroup handles one (expert slot, row tile) pair:
 // the slot is a shared expert or one entry of the device-built list of active
 // experts (no host synchronization: slots beyond the active count exit at
-// once).  Inside, lanes are split into groups of LPR lanes; a group owns one
-// row, each lane one 128-weight unit of it (coalesced 16-byte loads of the
-// packed codes, see layout.h).  The weights of the wave's rows are loaded to
-// registers once and reused for every token of the expert's bucket, whose
-// activations are staged in LDS in chunks of TM tokens together with their
-// per-block sums.  The dot products accumulate in float32; the per-block
-// scale and zero point are applied once per block; the group reduces its partial sums with cross-lane shuffles in a
-// fixed order, so results are deterministic.
+// once).  Lanes hold neighbouring rows (R of them) at 64 / R neighbouring
+// 128-weight units, so a load of 16-byte chunks takes runs of 16 R bytes
+// (layout.h) and reads the staged activations of only 64 / R units; a lane's
+// waves and lanes of one row meet at the end in a fixed order, so results are
+// deterministic.  The dot products accumulate in float32; the per-block scale
+// and zero point are applied once per block.
 //
 // gate/up kernel: writes h (float32) for every assignment in bucket order.
 // Arithmetic of the 2-4-bit kernels.  The one-token gate/up kernel and the
@@ -44,31 +42,6 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kXStride = 68;  // dwords per staged unit: 64 + 4 padding against LDS bank conflicts
-
-// Pipeline shape of the down GEMV: each wave walks kDownSteps row steps with
-// kDownBuf register buffers, i.e. NBUF - 1 steps of codes in flight while
-// one is reduced; MinBlocks bounds registers for occupancy.
-#ifndef MOEQ_DOWN_STEPS
-#define MOEQ_DOWN_STEPS 4
-#endif
-#ifndef MOEQ_DOWN_BUF
-#define MOEQ_DOWN_BUF 1
-#endif
-#ifndef MOEQ_DOWN_MINBLOCKS
-#define MOEQ_DOWN_MINBLOCKS 4
-#endif
-// the down kernel for 2-64 tokens (the values above serve one token)
-#ifndef MOEQ_DOWNM_STEPS
-#define MOEQ_DOWNM_STEPS 4
-#endif
-#ifndef MOEQ_DOWNM_BUF
-#define MOEQ_DOWNM_BUF 1
-#endif
-static_assert(MOEQ_DOWN_STEPS % MOEQ_DOWN_BUF == 0, "steps per wave must be a multiple of the pipeline depth");
-constexpr int kDownSteps = MOEQ_DOWN_STEPS, kDownBuf = MOEQ_DOWN_BUF;
-constexpr int kDownStepsM = MOEQ_DOWNM_STEPS, kDownBufM = MOEQ_DOWNM_BUF;
-static_assert(MOEQ_DOWNM_STEPS % MOEQ_DOWNM_BUF == 0, "steps per wave must be a multiple of the pipeline depth");
-constexpr int kDownMinBlocks = MOEQ_DOWN_MINBLOCKS;
 
 __device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float c) {
   return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a),
@@ -214,97 +187,105 @@ __device__ __forceinline__ float dpp_f(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROW_MASK, 0xF, false));
 }
 
-// Sum over a group of LPR lanes (16, 32 or 64) with DPP adds in a fixed order:
-// quad butterflies, row rotations, then row broadcasts.  The group's last
-// lane holds the total.
-template <int LPR>
-__device__ __forceinline__ float group_sum(float v) {
-  v += dpp_f<0xB1>(v);   // quad_perm [1,0,3,2]
-  v += dpp_f<0x4E>(v);   // quad_perm [2,3,0,1]
-  v += dpp_f<0x124>(v);  // row_ror:4
-  v += dpp_f<0x128>(v);  // row_ror:8
-  if constexpr (LPR >= 32) v += dpp_f<0x142, 0xA>(v);  // row_bcast:15 into rows 1, 3
-  if constexpr (LPR >= 64) v += dpp_f<0x143, 0xC>(v);  // row_bcast:31 into rows 2, 3
+// Sum over the lanes l % R of a wave (R = 8, 16, 32 or 64), in a fixed order;
+// every lane holds its row's total.
+template <int R>
+__device__ __forceinline__ float row_sum(float v) {
+  if constexpr (R <= 8) v += dpp_f<0x128>(v);  // row_ror:8
+  if constexpr (R <= 16) v += __shfl_xor(v, 16, 64);
+  if constexpr (R <= 32) v += __shfl_xor(v, 32, 64);
   return v;
 }
 
 __device__ __forceinline__ float silu(float g) { return g / (1.0f + expf(-g)); }
 
-// ---------------------------------------------------------------------------
-// down x routing weight for one (slot, row tile), down width BD; the same
-// two-buffer walk over each wave's row steps.
-template <int BD>
-struct DownRows {
-  uint32_t w[4 * BD];
+// One unit of a row: its chunks and scales.
+template <int B>
+struct UnitBuf {
+  uint32_t w[4 * B];
   u32x2 s;
 };
 
-template <int BD>
-__device__ __forceinline__ void load_down(DownRows<BD>& b, const TensorDev& td, int row, int U, int u, int I) {
-  load_unit<BD>(td.codes + (size_t)row * BD * U * 4, U, u, b.w);
-  b.s = *gptr(reinterpret_cast<const u32x2*>(td.scales + (size_t)row * (I / kBlock) + 4 * u));
+// A row's chunks and scales (lanes of a wave hold different rows).
+struct RowPtr {
+  const MOEQ_GLOBAL u32x4* c;
+  const MOEQ_GLOBAL u32x2* s;
+};
+__device__ __forceinline__ RowPtr row_ptr(const TensorDev& t, int bits, int U, int row) {
+  return RowPtr{row_chunks(t.codes, bits, U, row), row_scales(t.scales, U, row)};
 }
 
-template <int BD, int LPR, int TM>
-__device__ __forceinline__ void compute_down(const DownRows<BD>& b, bool active, const uint32_t* xu,
-                                             const float2* su4, int xts, int sts, int mc, int u,
-                                             const Slot sl, int m0, int row, const DecodeArgs& a) {
-  float o[TM];
+template <int B>
+__device__ __forceinline__ void load_unit_buf(UnitBuf<B>& b, const RowPtr& r, int u) {
+  load_unit<B>(r.c, u, b.w);
+  b.s = r.s[scale_step(u)];
+}
+
+// acc[m] += d * sum (c - z) x_m over one 128-weight unit, for the mc <= TM
+// tokens staged at xu / su4 (strides xts, sts)
+template <int B, int TM>
+__device__ __forceinline__ void unit_dots(const uint32_t* w, u32x2 sc, const uint32_t* xu, const float2* su4, int xts,
+                                          int sts, int mc, float (&acc)[TM]) {
 #pragma unroll
-  for (int m = 0; m < TM; ++m) o[m] = 0.0f;
-  if (active) {
+  for (int q = 0; q < 4; ++q) {
+    uint32_t p[16];
+    block_pairs_sub<B>(w + q * B, p);
+    const float ds = block_scale_sub(sc, q);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      uint32_t p[16];
-      block_pairs_sub<BD>(b.w + q * BD, p);
-      const float dd = block_scale_sub(b.s, q);
-#pragma unroll
-      for (int m = 0; m < TM; ++m)
-        if (m < mc) o[m] = block_dot_sub<BD>(p, xu + m * xts + 16 * q, dd, su4[m * sts + q], o[m]);
-    }
+    for (int m = 0; m < TM; ++m)
+      if (TM == 1 || m < mc) acc[m] = block_dot_sub<B>(p, xu + m * xts + 16 * q, ds, su4[m * sts + q], acc[m]);
   }
+}
+
+// This lane's share of a row against the staged tokens: units u0, u0 + step,
+// ... < U, the next one in flight while one is reduced; `first` holds unit
+// min(u0, U - 1).
+template <int B, int TM>
+__device__ __forceinline__ void row_dots(const RowPtr& r, int U, int u0, int step, const uint32_t* xl,
+                                         const float2* xs, int xts, int sts, int mc, const UnitBuf<B>& first,
+                                         float (&acc)[TM]) {
+  UnitBuf<B> buf[2];
+  buf[0] = first;
 #pragma unroll
-  for (int m = 0; m < TM; ++m) {
-    if (m < mc) {
-      const float os = group_sum<LPR>(o[m]);
-      if (u == LPR - 1) {
-        int prow;
-        float wv;
-        if (sl.shared >= 0) {
-          prow = a.n * a.k + sl.shared * a.n + m0 + m;
-          wv = 1.0f;
-        } else {
-          prow = a.perm[sl.base + m0 + m];
-          wv = a.w[prow];
-        }
-        a.partial[(size_t)prow * a.H + row] = wv * os;
+  for (int m = 0; m < TM; ++m) acc[m] = 0.0f;
+  const int n = (U + step - 1) / step;  // the same for every lane
+#pragma unroll 1
+  for (int i0 = 0; i0 < n; i0 += 2) {
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const int i = i0 + b;
+      if (i < n) {
+        // the next unit (clamped to the row's last) goes out before this one is reduced
+        load_unit_buf<B>(buf[1 - b], r, min(u0 + step * min(i + 1, n - 1), U - 1));
+        const int u = u0 + step * i;
+        if (u < U) unit_dots<B, TM>(buf[b].w, buf[b].s, xl + u * kXStride, xs + u * 4, xts, sts, mc, acc);
       }
     }
   }
 }
 
-template <int BD, int LPR, int TM, int RW, int NBUF>
-__device__ __forceinline__ void down_body(const DecodeArgs& a, const Slot sl, const TensorDev& td,
-                                          uint32_t* smem) {
+// ---------------------------------------------------------------------------
+// Down x routing weight, one partial row per (token, slot).  A workgroup owns
+// 128 rows of one slot, a wave 32 of them with two units per step.
+constexpr int kDownTokens = 4;  // staged per pass
+
+template <int B>
+__device__ __forceinline__ void down_body(const DecodeArgs& a, const Slot sl, const TensorDev& td, uint32_t* smem) {
+  constexpr int TM = kDownTokens, R = 32;
   const int H = a.H, I = a.I, U = I / kUnit;
-  const int xts = U * kXStride, sts = U * 4;  // per-token LDS strides (dwords, float pairs)
+  const int xts = U * kXStride, sts = U * 4;  // per-token LDS strides (dwords, float2)
   uint32_t* xl = smem;
   float2* xs = reinterpret_cast<float2*>(smem + TM * xts);
-
-  constexpr int GPW = 64 / LPR;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int grp = lane / LPR, u = lane % LPR;
-  const bool uok = u < U;
-  const int row0 = blockIdx.x * (4 * GPW * RW) + wave * (GPW * RW) + grp;  // + step * GPW
-
-  DownRows<BD> buf[NBUF];
+  const int row = blockIdx.x * (4 * R) + wave * R + lane % R;  // (H is a multiple of 128)
+  const RowPtr rp = row_ptr(td, B, U, row);
   for (int m0 = 0; m0 < sl.M; m0 += TM) {
     const int mc = min(TM, sl.M - m0);
-    asm volatile("" ::: "memory");  // weight loads stay inside the chunk loop
-#pragma unroll
-    for (int st = 0; st < NBUF; ++st)
-      if (st < RW && uok && row0 + st * GPW < H) load_down(buf[st], td, row0 + st * GPW, U, u, I);
-    __syncthreads();
+    // the first unit is requested before h is staged
+    UnitBuf<B> first;
+    load_unit_buf<B>(first, rp, min(lane / R, U - 1));
+    if (m0 > 0) __syncthreads();
     // stage h rows in binary16 with per-block prescales
     for (int m = 0; m < mc; ++m) {
       const MOEQ_GLOBAL f32x4* src = gptr(reinterpret_cast<const f32x4*>(a.h + (size_t)(sl.base + m0 + m) * I));
@@ -316,35 +297,40 @@ __device__ __forceinline__ void down_body(const DecodeArgs& a, const Slot sl, co
       }
     }
     __syncthreads();
-    const uint32_t* xu = xl + u * kXStride;
-    const float2* su4 = xs + u * 4;
-#pragma unroll 1
-    for (int g0 = 0; g0 < RW; g0 += NBUF) {
-      asm volatile("" ::: "memory");
+    float o[TM];
+    row_dots<B, TM>(rp, U, lane / R, 64 / R, xl, xs, xts, sts, mc, first, o);
 #pragma unroll
-      for (int b = 0; b < NBUF; ++b) {
-        const int st = g0 + b;
-        const int r = row0 + st * GPW;
-        if (r < H) compute_down<BD, LPR, TM>(buf[b], uok, xu, su4, xts, sts, mc, u, sl, m0, r, a);
-        const int rn = row0 + (st + NBUF) * GPW;
-        if (st + NBUF < RW && uok && rn < H) load_down(buf[b], td, rn, U, u, I);
+    for (int m = 0; m < TM; ++m) {
+      if (m < mc) {
+        const float os = row_sum<R>(o[m]);
+        if (lane < R) {
+          int prow;
+          float wv;
+          if (sl.shared >= 0) {
+            prow = a.n * a.k + sl.shared * a.n + m0 + m;
+            wv = 1.0f;
+          } else {
+            prow = a.perm[sl.base + m0 + m];
+            wv = a.w[prow];
+          }
+          a.partial[(size_t)prow * H + row] = wv * os;
+        }
       }
     }
   }
 }
 
-// grid = (row tiles of H, S + max_active), 256 threads
-template <int LPR, int TM, int RW, int NBUF>
-__global__ __launch_bounds__(256, TM == 1 ? kDownMinBlocks : 2) void down_kernel(DecodeArgs a) {
+// grid = (H / 128, S + max_active), 256 threads
+__global__ __launch_bounds__(256, 4) void down_kernel(DecodeArgs a) {
   extern __shared__ uint32_t smem[];
   const Slot sl = slot_info(a, blockIdx.y);
   if (sl.M < 0 || sl.M > a.gemm_above) return;  // (large buckets: the grouped GEMMs)
   const TensorDev td = a.desc[sl.desc * 3 + 2];
   if (!td.codes) return;
   switch (td.bits) {
-    case 2: down_body<2, LPR, TM, RW, NBUF>(a, sl, td, smem); break;
-    case 3: down_body<3, LPR, TM, RW, NBUF>(a, sl, td, smem); break;
-    case 4: down_body<4, LPR, TM, RW, NBUF>(a, sl, td, smem); break;
+    case 2: down_body<2>(a, sl, td, smem); break;
+    case 3: down_body<3>(a, sl, td, smem); break;
+    case 4: down_body<4>(a, sl, td, smem); break;
     default: break;
   }
 }
@@ -355,14 +341,14 @@ __global__ __launch_bounds__(256, TM == 1 ? kDownMinBlocks : 2) void down_kernel
 // width BD, or (BD = 0) widths that differ between tensors, where every
 // unit is fetched as four chunk loads, those past the slot's width from 16
 // zero bytes that stay in the vector cache, and the slot's width picks the
-// decoder.  A workgroup of NT threads owns NT / 16 rows of y across every slot (the
-// token's k choices in choice order, then the shared experts): a group of 16
-// lanes owns one row, lane u unit u of that row in every slot, with D slots'
-// codes in flight.  The lane accumulates w_j * (its partial dot of slot j) in
-// slot order and the group sums its lanes with DPP in a fixed order: no
-// partial rows, no combine launch.  All h rows are staged once per workgroup
-// (binary16 with per-block prescales, as in the down kernel), their loads
-// issued in batches so a batch costs one memory round trip.
+// decoder.  A workgroup of NT threads owns R = NT / 16 rows of y across every
+// slot (the token's k choices in choice order, then the shared experts): lane
+// l of wave w holds row l % R and unit w * 64 / R + l / R of it in every slot,
+// with D slots' codes in flight.  The lane accumulates w_j * (its partial dot
+// of slot j) in slot order and the 16 lanes of a row are summed in a fixed
+// order: no partial rows, no combine launch.  All h rows are staged once per
+// workgroup (binary16 with per-block prescales, as in the down kernel), their
+// loads issued in batches so a batch costs one memory round trip.
 struct DownSlot {
   const uint32_t* codes;
   const uint16_t* scales;
@@ -371,18 +357,12 @@ struct DownSlot {
   int bits;
 };
 
-// w_j-free partial dot of one slot's unit: sum over its 4 blocks
+// w_j-free partial dot of one slot's unit
 template <int B>
-__device__ __forceinline__ float down1_unit_dot(const uint32_t* w, u32x2 sc, const uint32_t* xu,
-                                                const float2* su4) {
-  float o = 0.0f;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    uint32_t pr[16];
-    block_pairs_sub<B>(w + q * B, pr);
-    o = block_dot_sub<B>(pr, xu + 16 * q, block_scale_sub(sc, q), su4[q], o);
-  }
-  return o;
+__device__ __forceinline__ float down1_unit_dot(const uint32_t* w, u32x2 sc, const uint32_t* xu, const float2* su4) {
+  float o[1] = {0.0f};
+  unit_dots<B, 1>(w, sc, xu, su4, 0, 0, 1, o);
+  return o[0];
 }
 
 constexpr int kDown1Batch = 6;  // staged 32-byte pieces per thread per round trip
@@ -391,6 +371,8 @@ template <int BD, int NT, int D>
 __global__ __launch_bounds__(NT) void down1_kernel(DecodeArgs a) {
   extern __shared__ uint32_t smem[];
   __shared__ DownSlot slots[kMaxTopK + kMaxShared];
+  constexpr int R = NT / 16, NW = NT / 64;
+  __shared__ float red[NW][R];
   const int H = a.H, I = a.I, U = I / kUnit, k = a.k, NS = a.k + a.S;
   const int xts = U * kXStride, sts = U * 4;
   uint32_t* xl = smem;
@@ -419,31 +401,31 @@ __global__ __launch_bounds__(NT) void down1_kernel(DecodeArgs a) {
   }
   __syncthreads();
 
-  const int u = threadIdx.x & 15;
-  const int row = blockIdx.x * (NT / 16) + (threadIdx.x >> 4);
-  const int rowc = min(row, H - 1), uc = min(u, U - 1);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int u = wave * (64 / R) + lane / R;
+  const int row = blockIdx.x * R + lane % R;  // (H is a multiple of 128)
+  const int uc = min(u, U - 1);
   constexpr int BL = BD == 0 ? 4 : BD;  // chunks loaded per unit
-  auto load_slot = [&](DownRows<BL>& b, int j) {
+  auto load_slot = [&](UnitBuf<BL>& b, int j) {
     const DownSlot& sl = slots[min(j, NS - 1)];
     if constexpr (BD == 0) {
       const int bits = sl.bits;
-      const MOEQ_GLOBAL u32x4* r4 =
-          gptr(reinterpret_cast<const u32x4*>(sl.codes + (size_t)rowc * bits * U * 4)) + uc;
+      const MOEQ_GLOBAL u32x4* r4 = row_chunks(sl.codes, bits, U, row) + uc * bits * kRowTile;
       const MOEQ_GLOBAL u32x4* z4 = gptr(reinterpret_cast<const u32x4*>(a.zeros));
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        const u32x4 v = __builtin_nontemporal_load(c < bits ? r4 + (size_t)c * U : z4);
+        const u32x4 v = __builtin_nontemporal_load(c < bits ? r4 + c * kRowTile : z4);
         b.w[4 * c + 0] = v.x;
         b.w[4 * c + 1] = v.y;
         b.w[4 * c + 2] = v.z;
         b.w[4 * c + 3] = v.w;
       }
     } else {
-      load_unit<BD>(sl.codes + (size_t)rowc * BD * U * 4, U, uc, b.w);
+      load_unit<BD>(row_chunks(sl.codes, BD, U, row), uc, b.w);
     }
-    b.s = *gptr(reinterpret_cast<const u32x2*>(sl.scales + (size_t)rowc * (I / kBlock) + 4 * uc));
+    b.s = row_scales(sl.scales, U, row)[scale_step(uc)];
   };
-  DownRows<BL> buf[D];
+  UnitBuf<BL> buf[D];
 #pragma unroll
   for (int i = 0; i < D - 1; ++i) load_slot(buf[i], i);
 
@@ -505,8 +487,15 @@ __global__ __launch_bounds__(NT) void down1_kernel(DecodeArgs a) {
       }
     }
   }
-  const float ys = group_sum<16>(acc);
-  if (u == 15 && row < H) a.y[row] = ys;
+  acc = row_sum<R>(acc);
+  if (lane < R) red[wave][lane] = acc;
+  __syncthreads();
+  if ((int)threadIdx.x < R) {
+    float ys = red[0][threadIdx.x];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) ys += red[w][threadIdx.x];
+    a.y[row] = ys;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -541,78 +530,78 @@ __global__ __launch_bounds__(256) void combine_kernel(DecodeArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Buckets of one token: gate/up + SwiGLU with 16 lanes per row pair.  Lanes 0-7 of a
-// 16-lane group stream the gate row and lanes 8-15 the up row; lane j of a
-// half walks the units j, j + 8, j + 16, ... of its row, so all lanes are
-// busy for any number of units, and the per-row work (sums, activation,
-// store) is spread over several units per lane.  The codes of unit i + 1 are
-// in flight while unit i is reduced.  A half sums its lanes with DPP (quad
-// butterflies, then the half-row mirror); the up half's last lane receives
-// the gate total across the row (row_ror:8) and writes h.
-template <int B>
-struct UnitBuf {
-  uint32_t w[4 * B];
-  u32x2 s;
+// Gate/up + SwiGLU.  A workgroup of kGuWaves waves owns kGuRows features of one
+// slot: the first half of the waves takes their gate rows, the other half
+// their up rows (a wave decodes one width), each wave kGuRows rows at 64 /
+// kGuRows units per step, the units of a row dealt to the waves of its tensor.
+// The partial sums meet in LDS in wave order.
+#ifndef MOEQ_GU_WAVES
+#define MOEQ_GU_WAVES 4
+#endif
+#ifndef MOEQ_GU_ROWS
+#define MOEQ_GU_ROWS 16
+#endif
+#ifndef MOEQ_GU_OCC
+#define MOEQ_GU_OCC 5
+#endif
+constexpr int kGuWaves = MOEQ_GU_WAVES, kGuRows = MOEQ_GU_ROWS, kGuThreads = 64 * kGuWaves;
+constexpr int kGuHalf = kGuWaves / 2;  // waves per tensor
+static_assert(128 % kGuRows == 0, "a workgroup's features are all in or all out");
+
+struct GateUpShared {
+  float red[kGuWaves][4][kGuRows];
 };
 
-template <int B>
-__device__ __forceinline__ void load_unit_buf(UnitBuf<B>& b, const TensorDev& t, int row, int U, int u, int K) {
-  load_unit<B>(t.codes + (size_t)row * B * U * 4, U, u, b.w);
-  b.s = *gptr(reinterpret_cast<const u32x2*>(t.scales + (size_t)row * (K / kBlock) + 4 * u));
+template <int TM>
+struct Dots {
+  float v[TM];
+};
+
+// this lane's share of its row (of the tensor its wave takes); the first
+// unit is requested before `stage` brings the tokens into LDS
+template <int B, int TM, typename F>
+__device__ __forceinline__ void gateup_dots(const TensorDev& t, int row, int U, int u0, const uint32_t* xl,
+                                            const float2* xs, int xts, int sts, int mc, F stage, float (&acc)[TM]) {
+  const RowPtr rp = row_ptr(t, B, U, row);
+  UnitBuf<B> first;
+  load_unit_buf<B>(first, rp, min(u0, U - 1));
+  stage();
+  row_dots<B, TM>(rp, U, u0, kGuHalf * (64 / kGuRows), xl, xs, xts, sts, mc, first, acc);
 }
 
-// d * sum (c - z) x over one 128-weight unit, for the token staged at xu / su4
-template <int B>
-__device__ __forceinline__ float unit_dot(const UnitBuf<B>& b, const uint32_t* xu, const float2* su4, float acc) {
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    uint32_t p[16];
-    block_pairs_sub<B>(b.w + q * B, p);
-    acc = block_dot_sub<B>(p, xu + 16 * q, block_scale_sub(b.s, q), su4[q], acc);
+// features [f0, f0 + kGuRows) of one slot for mc <= TM tokens, which `stage`
+// brings into LDS (with a barrier at its end); h rows hrow .. hrow + mc - 1
+template <int TM, typename F>
+__device__ __forceinline__ void gateup_rows(const DecodeArgs& a, const TensorDev& tg, const TensorDev& tu, int f0,
+                                            int hrow, int mc, const uint32_t* xl, const float2* xs, int xts, int sts,
+                                            GateUpShared& sh, F stage) {
+  constexpr int R = kGuRows;
+  const int H = a.H, I = a.I, U = H / kUnit;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const TensorDev& t = wave < kGuHalf ? tg : tu;
+  const int row = f0 + lane % R, u0 = (wave % kGuHalf) * (64 / R) + lane / R;
+  float acc[TM];
+  switch (__builtin_amdgcn_readfirstlane(t.bits)) {
+    case 2: gateup_dots<2, TM>(t, row, U, u0, xl, xs, xts, sts, mc, stage, acc); break;
+    case 3: gateup_dots<3, TM>(t, row, U, u0, xl, xs, xts, sts, mc, stage, acc); break;
+    default: gateup_dots<4, TM>(t, row, U, u0, xl, xs, xts, sts, mc, stage, acc); break;
   }
-  return acc;
-}
-
-__device__ __forceinline__ float half_sum8(float v) {
-  v += dpp_f<0xB1>(v);   // quad_perm [1,0,3,2]
-  v += dpp_f<0x4E>(v);   // quad_perm [2,3,0,1]
-  v += dpp_f<0x141>(v);  // row_half_mirror: the other quad of the half row
-  return v;
-}
-
-// the half's partial dot over its units (units j, j + 8, ... of row `row`);
-// GU1_DEPTH units are in flight while one is reduced
-#ifndef MOEQ_GU1_DEPTH
-#define MOEQ_GU1_DEPTH 2
-#endif
-#ifndef MOEQ_GU1_MINBLOCKS
-#define MOEQ_GU1_MINBLOCKS 5
-#endif
-template <int B>
-__device__ __forceinline__ float row_half_dot(const TensorDev& t, int row, int U, int j, int H, const uint32_t* xl,
-                                              const float2* xs, const UnitBuf<B>& first) {
-  constexpr int NB = MOEQ_GU1_DEPTH;
-  const int UPL = (U + 7) / 8;
-  UnitBuf<B> buf[NB];
-  buf[0] = first;
 #pragma unroll
-  for (int i = 1; i < NB - 1; ++i) load_unit_buf<B>(buf[i], t, row, U, min(j + 8 * min(i, UPL - 1), U - 1), H);
-  float acc = 0.0f;
-#pragma unroll 1
-  for (int i0 = 0; i0 < UPL; i0 += NB) {
-    asm volatile("" ::: "memory");
+  for (int m = 0; m < TM; ++m) {
+    const float v = row_sum<R>(acc[m]);
+    if (lane < R) sh.red[wave][m][lane] = v;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < R * mc; i += kGuThreads) {
+    const int m = i / R, r = i % R;
+    float g = sh.red[0][m][r], u = sh.red[kGuHalf][m][r];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const int i = i0 + b;
-      if (i < UPL) {
-        // unit i + NB - 1 (clamped to the last valid one) goes out before unit i is reduced
-        load_unit_buf<B>(buf[(b + NB - 1) % NB], t, row, U, min(j + 8 * min(i + NB - 1, UPL - 1), U - 1), H);
-        const int u = j + 8 * i;
-        if (u < U) acc = unit_dot<B>(buf[b], xl + u * kXStride, xs + u * 4, acc);
-      }
+    for (int w = 1; w < kGuHalf; ++w) {
+      g += sh.red[w][m][r];
+      u += sh.red[kGuHalf + w][m][r];
     }
+    a.h[(size_t)(hrow + m) * I + f0 + r] = silu(g) * u;
   }
-  return acc;
 }
 
 // the token's x into LDS in binary16 with per-block prescales (16-byte
@@ -623,7 +612,7 @@ __device__ __forceinline__ void stage_x1(const DecodeArgs& a, const Slot sl, uin
   // routing workgroup of gateup1_route_kernel may still be writing)
   const int t = sl.shared >= 0 || a.n == 1 ? 0 : a.perm[sl.base] / a.k;
   const MOEQ_GLOBAL u32x4* src = gptr(reinterpret_cast<const u32x4*>(a.x + (size_t)t * H));
-  for (int q = threadIdx.x; q < H / 8; q += 256) {
+  for (int q = threadIdx.x; q < H / 8; q += kGuThreads) {
     float f[8];
     bf16x8_to_f32(src[q], f);
     const int uu = q >> 4, cq = q & 15;
@@ -644,91 +633,50 @@ __device__ __forceinline__ void stage_x1_token0(const DecodeArgs& a, int t0, int
   }
 }
 
-// Each lane requests its first unit before x is staged, so the staging
-// latency overlaps the weight traffic (STAGED: x is in LDS already).
-template <int BG, int BU, bool STAGED = false>
-__device__ __forceinline__ void gateup1_body(const DecodeArgs& a, const Slot sl, const TensorDev& tg,
-                                             const TensorDev& tu, uint32_t* xl, float2* xs) {
-  const int H = a.H, I = a.I, U = H / kUnit;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 16 + wave * 4 + (lane >> 4);
-  const bool up = (lane & 8) != 0;
-  const int j = lane & 7;
-  const int rowc = min(row, I - 1);
-  float v;
-  if constexpr (BG == BU) {
-    const TensorDev& t = up ? tu : tg;
-    UnitBuf<BG> first;
-    load_unit_buf<BG>(first, t, rowc, U, min(j, U - 1), H);
-    if constexpr (!STAGED) {
-      stage_x1(a, sl, xl, xs);
-      __syncthreads();
-    }
-    v = row_half_dot<BG>(t, rowc, U, j, H, xl, xs, first);
-  } else {
-    UnitBuf<BG> fg;
-    UnitBuf<BU> fu;
-    if (up)
-      load_unit_buf<BU>(fu, tu, rowc, U, min(j, U - 1), H);
-    else
-      load_unit_buf<BG>(fg, tg, rowc, U, min(j, U - 1), H);
-    if constexpr (!STAGED) {
-      stage_x1(a, sl, xl, xs);
-      __syncthreads();
-    }
-    if (up)
-      v = row_half_dot<BU>(tu, rowc, U, j, H, xl, xs, fu);
-    else
-      v = row_half_dot<BG>(tg, rowc, U, j, H, xl, xs, fg);
-  }
-  v = half_sum8(v);
-  const float other = dpp_f<0x128>(v);  // row_ror:8: the other half's total
-  if ((lane & 15) == 15 && row < I) a.h[(size_t)sl.base * a.I + row] = silu(other) * v;
+// 2-4-bit gate and up tensors (the others: the wide kernels)
+__device__ __forceinline__ bool narrow_gateup(const TensorDev& tg, const TensorDev& tu) {
+  return tg.codes && tu.codes && tg.bits <= 4 && tu.bits <= 4;
 }
 
-// one workgroup's share of the gate/up of a bucket of one token
+// one workgroup's share of the gate/up of a bucket of one token (STAGED: x is
+// in LDS already)
 template <bool STAGED = false>
-__device__ __forceinline__ void gateup1_slot(const DecodeArgs& a, const Slot& sl, uint32_t* smem) {
+__device__ __forceinline__ void gateup1_slot(const DecodeArgs& a, const Slot& sl, uint32_t* smem, GateUpShared& sh) {
   if (sl.M != 1) return;  // the buckets of one token, of any batch
   const TensorDev tg = a.desc[sl.desc * 3 + 0], tu = a.desc[sl.desc * 3 + 1];
-  if (!tg.codes || !tu.codes) return;
-  const int U = a.H / kUnit;
+  if (!narrow_gateup(tg, tu)) return;
   uint32_t* xl = smem;
-  float2* xs = reinterpret_cast<float2*>(smem + U * kXStride);
-  switch (tg.bits * 8 + tu.bits) {
-    case 2 * 8 + 2: gateup1_body<2, 2, STAGED>(a, sl, tg, tu, xl, xs); break;
-    case 2 * 8 + 3: gateup1_body<2, 3, STAGED>(a, sl, tg, tu, xl, xs); break;
-    case 2 * 8 + 4: gateup1_body<2, 4, STAGED>(a, sl, tg, tu, xl, xs); break;
-    case 3 * 8 + 2: gateup1_body<3, 2, STAGED>(a, sl, tg, tu, xl, xs); break;
-    case 3 * 8 + 3: gateup1_body<3, 3, STAGED>(a, sl, tg, tu, xl, xs); break;
-    case 3 * 8 + 4: gateup1_body<3, 4, STAGED>(a, sl, tg, tu, xl, xs); break;
-    case 4 * 8 + 2: gateup1_body<4, 2, STAGED>(a, sl, tg, tu, xl, xs); break;
-    case 4 * 8 + 3: gateup1_body<4, 3, STAGED>(a, sl, tg, tu, xl, xs); break;
-    case 4 * 8 + 4: gateup1_body<4, 4, STAGED>(a, sl, tg, tu, xl, xs); break;
-    default: break;
-  }
+  float2* xs = reinterpret_cast<float2*>(smem + a.H / kUnit * kXStride);
+  gateup_rows<1>(a, tg, tu, blockIdx.x * kGuRows, sl.base, 1, xl, xs, 0, 0, sh, [&] {
+    if constexpr (!STAGED) {
+      stage_x1(a, sl, xl, xs);
+      __syncthreads();
+    }
+  });
 }
 
-// grid = (I / 16, S + max_active), 256 threads; the buckets of one token
-__global__ __launch_bounds__(256, MOEQ_GU1_MINBLOCKS) void gateup1_kernel(DecodeArgs a) {
+// grid = (I / kGuRows, S + max_active), kGuThreads threads; the buckets of one token
+__global__ __launch_bounds__(kGuThreads, MOEQ_GU_OCC) void gateup1_kernel(DecodeArgs a) {
   extern __shared__ uint32_t smem[];
-  gateup1_slot(a, slot_info(a, blockIdx.y), smem);
+  __shared__ GateUpShared sh;
+  gateup1_slot(a, slot_info(a, blockIdx.y), smem, sh);
 }
 
 // The same for a forward of one token that needs no routing launch: wave 0
 // of every workgroup of a routed slot routes the token itself (the routing
 // kernels' selection, deterministic, so every workgroup finds the same
-// experts; waves 1-3 stage x meanwhile) while the shared experts'
+// experts; the other waves stage x meanwhile) while the shared experts'
 // workgroups start at once.  Routed slot
 // i is the i-th chosen expert in ascending id order, as the bucketing lists
 // them.  Workgroup (0, S) also writes what the routing launch would have:
 // idx and w in choice order, offsets, the active list and the permutation,
 // which the down kernel and any 5/6/8-bit gate/up kernel read after this
-// launch.  grid = (I / 16, S + k), 256 threads.
+// launch.  grid = (I / kGuRows, S + k), kGuThreads threads.
 template <int EPL>
-__global__ __launch_bounds__(256, MOEQ_GU1_MINBLOCKS) void gateup1_route_kernel(DecodeArgs a, RouterParams rp,
+__global__ __launch_bounds__(kGuThreads, MOEQ_GU_OCC) void gateup1_route_kernel(DecodeArgs a, RouterParams rp,
                                                                                 Workspace ws) {
   extern __shared__ uint32_t smem[];
+  __shared__ GateUpShared sh;
   __shared__ float gs_l[64];
   __shared__ int32_t chosen[kMaxTopK];
   Slot sl;
@@ -764,9 +712,9 @@ __global__ __launch_bounds__(256, MOEQ_GU1_MINBLOCKS) void gateup1_route_kernel(
         ws.active[0] = rp.k;
       }
     } else {
-      // waves 1-3 stage the token's x meanwhile
+      // the other waves stage the token's x meanwhile
       const int U = a.H / kUnit;
-      stage_x1_token0(a, 64, 192, smem, reinterpret_cast<float2*>(smem + U * kXStride));
+      stage_x1_token0(a, 64, kGuThreads - 64, smem, reinterpret_cast<float2*>(smem + U * kXStride));
     }
     __syncthreads();
     const int i = blockIdx.y - a.S;
@@ -774,27 +722,22 @@ __global__ __launch_bounds__(256, MOEQ_GU1_MINBLOCKS) void gateup1_route_kernel(
     sl.base = i;
     sl.M = 1;
     sl.shared = -1;
-    gateup1_slot<true>(a, sl, smem);
+    gateup1_slot<true>(a, sl, smem, sh);
     return;
   }
-  gateup1_slot(a, sl, smem);
+  gateup1_slot(a, sl, smem, sh);
 }
 
 // ---------------------------------------------------------------------------
-// Buckets of 2 or more tokens, in the one-token kernel's layout (16 lanes per
-// row pair, lane j of a half walking the units j, j + 8, ... of its row, code
-// pairs as binary16 subnormals), TM tokens staged per pass: each unit's code
-// pairs are unpacked once and multiplied with every staged token.  Measured
-// at 16 tokens: 2 tokens per pass (four workgroups per compute unit) 427 us
-// per step, 3 per pass 427, 4 per pass (two workgroups per CU) 451, against
-// 446 for a kernel that gave a whole wave to each row and staged 4 tokens
-// in bfloat16.
+// Buckets of 2 or more tokens, in the one-token kernel's layout, TM tokens
+// staged per pass: each unit's code pairs are unpacked once and multiplied
+// with every staged token.
 
 // token t's x into LDS at xl / xs (binary16 with per-block prescales)
 __device__ __forceinline__ void stage_x_token(const DecodeArgs& a, int t, uint32_t* xl, float2* xs) {
   const int H = a.H;
   const MOEQ_GLOBAL u32x4* src = gptr(reinterpret_cast<const u32x4*>(a.x + (size_t)t * H));
-  for (int q = threadIdx.x; q < H / 8; q += 256) {
+  for (int q = threadIdx.x; q < H / 8; q += kGuThreads) {
     float f[8];
     bf16x8_to_f32(src[q], f);
     const int uu = q >> 4, cq = q & 15;
@@ -802,144 +745,46 @@ __device__ __forceinline__ void stage_x_token(const DecodeArgs& a, int t, uint32
   }
 }
 
-// the half's partial dots over its units for the mc <= TM staged tokens
-template <int B, int TM>
-__device__ __forceinline__ void row_half_dot_tm(const TensorDev& t, int row, int U, int j, int H, const uint32_t* xl,
-                                                const float2* xs, int xts, int sts, int mc,
-                                                const UnitBuf<B>& first, float (&acc)[TM]) {
-  constexpr int NB = MOEQ_GU1_DEPTH;
-  const int UPL = (U + 7) / 8;
-  UnitBuf<B> buf[NB];
-  buf[0] = first;
-#pragma unroll
-  for (int i = 1; i < NB - 1; ++i) load_unit_buf<B>(buf[i], t, row, U, min(j + 8 * min(i, UPL - 1), U - 1), H);
-#pragma unroll
-  for (int m = 0; m < TM; ++m) acc[m] = 0.0f;
-#pragma unroll 1
-  for (int i0 = 0; i0 < UPL; i0 += NB) {
-    asm volatile("" ::: "memory");
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const int i = i0 + b;
-      if (i < UPL) {
-        load_unit_buf<B>(buf[(b + NB - 1) % NB], t, row, U, min(j + 8 * min(i + NB - 1, UPL - 1), U - 1), H);
-        const int u = j + 8 * i;
-        if (u < U) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            uint32_t p[16];
-            block_pairs_sub<B>(buf[b].w + q * B, p);
-            const float ds = block_scale_sub(buf[b].s, q);
-#pragma unroll
-            for (int m = 0; m < TM; ++m)
-              if (m < mc)
-                acc[m] = block_dot_sub<B>(p, xl + m * xts + u * kXStride + 16 * q, ds, xs[m * sts + u * 4 + q],
-                                          acc[m]);
-          }
-        }
-      }
-    }
-  }
-}
-
-template <int BG, int BU, int TM>
-__device__ __forceinline__ void gateupn_body(const DecodeArgs& a, const Slot sl, const TensorDev& tg,
-                                             const TensorDev& tu, uint32_t* smem) {
-  const int H = a.H, I = a.I, U = H / kUnit;
-  const int xts = U * kXStride, sts = U * 4;  // per-token LDS strides (dwords, float2)
-  uint32_t* xl = smem;
-  float2* xs = reinterpret_cast<float2*>(smem + TM * xts);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 16 + wave * 4 + (lane >> 4);
-  const bool up = (lane & 8) != 0;
-  const int j = lane & 7;
-  const int rowc = min(row, I - 1);
-  for (int m0 = 0; m0 < sl.M; m0 += TM) {
-    const int mc = min(TM, sl.M - m0);
-    // the first unit is requested before x is staged
-    UnitBuf<BG> fg;
-    UnitBuf<BU> fu;
-    if constexpr (BG == BU) {
-      load_unit_buf<BG>(fg, up ? tu : tg, rowc, U, min(j, U - 1), H);
-    } else {
-      if (up)
-        load_unit_buf<BU>(fu, tu, rowc, U, min(j, U - 1), H);
-      else
-        load_unit_buf<BG>(fg, tg, rowc, U, min(j, U - 1), H);
-    }
-    if (m0 > 0) __syncthreads();  // the previous pass has read its x
-    for (int m = 0; m < mc; ++m) {
-      const int t = sl.shared >= 0 ? m0 + m : a.perm[sl.base + m0 + m] / a.k;
-      stage_x_token(a, t, xl + m * xts, xs + m * sts);
-    }
-    __syncthreads();
-    float acc[TM];
-    if constexpr (BG == BU) {
-      row_half_dot_tm<BG, TM>(up ? tu : tg, rowc, U, j, H, xl, xs, xts, sts, mc, fg, acc);
-    } else {
-      if (up)
-        row_half_dot_tm<BU, TM>(tu, rowc, U, j, H, xl, xs, xts, sts, mc, fu, acc);
-      else
-        row_half_dot_tm<BG, TM>(tg, rowc, U, j, H, xl, xs, xts, sts, mc, fg, acc);
-    }
-#pragma unroll
-    for (int m = 0; m < TM; ++m) {
-      if (m < mc) {
-        const float v = half_sum8(acc[m]);
-        const float other = dpp_f<0x128>(v);  // row_ror:8: the gate half's total
-        if ((lane & 15) == 15 && row < I) a.h[(size_t)(sl.base + m0 + m) * I + row] = silu(other) * v;
-      }
-    }
-  }
-}
-
-// grid = (I / 16, S + max_active), 256 threads; buckets of 2 .. gemm_above tokens
+// grid = (I / kGuRows, S + max_active), kGuThreads threads; buckets of 2 .. gemm_above tokens
 template <int TM>
-__global__ __launch_bounds__(256, TM <= 2 ? 4 : 2) void gateupn_kernel(DecodeArgs a) {
+__global__ __launch_bounds__(kGuThreads, TM <= 2 ? 4 : 2) void gateupn_kernel(DecodeArgs a) {
   extern __shared__ uint32_t smem[];
+  __shared__ GateUpShared sh;
   const Slot sl = slot_info(a, blockIdx.y);
   if (sl.M < 2 || sl.M > a.gemm_above) return;
   const TensorDev tg = a.desc[sl.desc * 3 + 0], tu = a.desc[sl.desc * 3 + 1];
-  if (!tg.codes || !tu.codes) return;
-  switch (tg.bits * 8 + tu.bits) {
-    case 2 * 8 + 2: gateupn_body<2, 2, TM>(a, sl, tg, tu, smem); break;
-    case 2 * 8 + 3: gateupn_body<2, 3, TM>(a, sl, tg, tu, smem); break;
-    case 2 * 8 + 4: gateupn_body<2, 4, TM>(a, sl, tg, tu, smem); break;
-    case 3 * 8 + 2: gateupn_body<3, 2, TM>(a, sl, tg, tu, smem); break;
-    case 3 * 8 + 3: gateupn_body<3, 3, TM>(a, sl, tg, tu, smem); break;
-    case 3 * 8 + 4: gateupn_body<3, 4, TM>(a, sl, tg, tu, smem); break;
-    case 4 * 8 + 2: gateupn_body<4, 2, TM>(a, sl, tg, tu, smem); break;
-    case 4 * 8 + 3: gateupn_body<4, 3, TM>(a, sl, tg, tu, smem); break;
-    case 4 * 8 + 4: gateupn_body<4, 4, TM>(a, sl, tg, tu, smem); break;
-    default: break;
+  if (!narrow_gateup(tg, tu)) return;
+  const int U = a.H / kUnit, xts = U * kXStride, sts = U * 4;  // per-token LDS strides (dwords, float2)
+  uint32_t* xl = smem;
+  float2* xs = reinterpret_cast<float2*>(smem + TM * xts);
+  for (int m0 = 0; m0 < sl.M; m0 += TM) {
+    const int mc = min(TM, sl.M - m0);
+    // (the previous pass's last barrier came after its reads of x; its sums
+    // are read before the barrier that ends the staging)
+    gateup_rows<TM>(a, tg, tu, blockIdx.x * kGuRows, sl.base + m0, mc, xl, xs, xts, sts, sh, [&] {
+      for (int m = 0; m < mc; ++m) {
+        const int t = sl.shared >= 0 ? m0 + m : a.perm[sl.base + m0 + m] / a.k;
+        stage_x_token(a, t, xl + m * xts, xs + m * sts);
+      }
+      __syncthreads();
+    });
   }
 }
 
 // ---------------------------------------------------------------------------
 // Wide tensors (5, 6 and 8 bits).  The kernels above skip a slot whose gate or
-// up (down) tensor is wide; these take exactly those slots.  LPR lanes per
-// row (8, 16 or 32): lane j walks the units j, j + LPR, ... of its row with the
-// next unit in flight, for up to TM tokens per pass (1 for a single token,
-// else 4).  Gate, up and down are reduced one tensor at a time, so a wave
-// decodes one width at a time.  Few slots (shared experts only) take more
-// lanes per row, so that the grid still covers the chip.
+// up (down) tensor is wide; these take exactly those slots.  A workgroup of
+// NW waves owns 16 rows of the tensor, a wave 4 units of each per step, the
+// units of a row dealt to the waves, for up to TM tokens per pass (1 for a
+// single token, else 4).  Gate, up and down are reduced one tensor at a time,
+// so a wave decodes one width at a time.  Few slots (shared experts only)
+// take more waves, so that the grid still covers the chip.
+constexpr int kWideRows = 16;
 __device__ __forceinline__ bool wide_bits(int b) { return b > 4; }
-
-template <int B>
-struct WideUnit {
-  uint32_t w[4 * B];
-  u32x2 s;
-};
-
-template <int B>
-__device__ __forceinline__ void wide_load(WideUnit<B>& b, const TensorDev& t, int row, int U, int u, int K) {
-  load_unit<B>(t.codes + (size_t)row * B * U * 4, U, u, b.w);
-  b.s = *gptr(reinterpret_cast<const u32x2*>(t.scales + (size_t)row * (K / kBlock) + 4 * u));
-}
 
 // acc[m] += d * sum (c - z) x_m over one unit, for the mc staged tokens
 template <int B, int NX, int TM>
-__device__ __forceinline__ void wide_unit_dot(const WideUnit<B>& b, const uint32_t* xu, int xts, int lo,
+__device__ __forceinline__ void wide_unit_dot(const UnitBuf<B>& b, const uint32_t* xu, int xts, int lo,
                                               const float* su4, int sts, int mc, float (&acc)[TM]) {
   const PairConsts pk = pair_consts();
 #pragma unroll
@@ -980,20 +825,21 @@ struct WideAcc {
 // through a pointer argument) keeps the accesses LDS instructions.
 extern __shared__ uint32_t wide_lds[];
 
-// This lane's share (units j, j + 8, ...) of row `row` against the staged
+// This lane's share (units j, j + step, ...) of row `row` against the staged
 // tokens.  Not inlined: one function per width keeps each width's registers
 // to itself (inlined together, the allocator merges all six).
-template <int B, int NX, int TM, int LPR>
-__device__ __noinline__ WideAcc<TM> wide_row_dot(const TensorDev t, int row, int U, int K, int j, int xts, int lo,
+template <int B, int NX, int TM>
+__device__ __noinline__ WideAcc<TM> wide_row_dot(const TensorDev t, int row, int U, int j, int step, int xts, int lo,
                                                  int sts, int mc) {
   const uint32_t* xl = wide_lds;
   const float* xs = reinterpret_cast<const float*>(wide_lds + TM * xts);
   WideAcc<TM> r;
 #pragma unroll
   for (int m = 0; m < TM; ++m) r.v[m] = 0.0f;
-  const int UPL = (U + LPR - 1) / LPR;
-  WideUnit<B> buf[2];
-  wide_load<B>(buf[0], t, row, U, min(j, U - 1), K);
+  const int UPL = (U + step - 1) / step;
+  const RowPtr rp = row_ptr(t, B, U, row);
+  UnitBuf<B> buf[2];
+  load_unit_buf<B>(buf[0], rp, min(j, U - 1));
 #pragma unroll 1
   for (int i0 = 0; i0 < UPL; i0 += 2) {
     asm volatile("" ::: "memory");
@@ -1002,8 +848,8 @@ __device__ __noinline__ WideAcc<TM> wide_row_dot(const TensorDev t, int row, int
       const int i = i0 + b;
       if (i < UPL) {
         // the next unit (clamped to the last valid one) goes out before this one is reduced
-        wide_load<B>(buf[1 - b], t, row, U, min(j + LPR * min(i + 1, UPL - 1), U - 1), K);
-        const int u = j + LPR * i;
+        load_unit_buf<B>(buf[1 - b], rp, min(j + step * min(i + 1, UPL - 1), U - 1));
+        const int u = j + step * i;
         if (u < U) wide_unit_dot<B, NX, TM>(buf[b], xl + u * kXStride, xts, lo, xs + u * 4, sts, mc, r.v);
       }
     }
@@ -1011,31 +857,40 @@ __device__ __noinline__ WideAcc<TM> wide_row_dot(const TensorDev t, int row, int
   return r;
 }
 
-template <int NX, int TM, int LPR>
-__device__ __forceinline__ WideAcc<TM> wide_row_dot_any(const TensorDev& t, int row, int U, int K, int j, int xts,
+template <int NX, int TM>
+__device__ __forceinline__ WideAcc<TM> wide_row_dot_any(const TensorDev& t, int row, int U, int j, int step, int xts,
                                                         int lo, int sts, int mc) {
-  switch (t.bits) {
-    case 2: return wide_row_dot<2, NX, TM, LPR>(t, row, U, K, j, xts, lo, sts, mc);
-    case 3: return wide_row_dot<3, NX, TM, LPR>(t, row, U, K, j, xts, lo, sts, mc);
-    case 4: return wide_row_dot<4, NX, TM, LPR>(t, row, U, K, j, xts, lo, sts, mc);
-    case 5: return wide_row_dot<5, NX, TM, LPR>(t, row, U, K, j, xts, lo, sts, mc);
-    case 6: return wide_row_dot<6, NX, TM, LPR>(t, row, U, K, j, xts, lo, sts, mc);
-    default: return wide_row_dot<8, NX, TM, LPR>(t, row, U, K, j, xts, lo, sts, mc);
+  switch (__builtin_amdgcn_readfirstlane(t.bits)) {
+    case 2: return wide_row_dot<2, NX, TM>(t, row, U, j, step, xts, lo, sts, mc);
+    case 3: return wide_row_dot<3, NX, TM>(t, row, U, j, step, xts, lo, sts, mc);
+    case 4: return wide_row_dot<4, NX, TM>(t, row, U, j, step, xts, lo, sts, mc);
+    case 5: return wide_row_dot<5, NX, TM>(t, row, U, j, step, xts, lo, sts, mc);
+    case 6: return wide_row_dot<6, NX, TM>(t, row, U, j, step, xts, lo, sts, mc);
+    default: return wide_row_dot<8, NX, TM>(t, row, U, j, step, xts, lo, sts, mc);
   }
 }
 
-// sum over the LPR lanes of a row group; the group's last lane holds it
-template <int LPR>
-__device__ __forceinline__ float wide_sum(float v) {
-  if constexpr (LPR == 8)
-    return half_sum8(v);
-  else
-    return group_sum<LPR>(v);
+// The row totals of a workgroup's waves: red[tensor][wave][token][row], summed
+// over the waves in order by the threads that store them.
+template <int TM, int NW>
+__device__ __forceinline__ void wide_put(const WideAcc<TM>& v, float (*red)[TM][kWideRows], int wave, int lane) {
+#pragma unroll
+  for (int m = 0; m < TM; ++m) {
+    const float s = row_sum<kWideRows>(v.v[m]);
+    if (lane < kWideRows) red[wave][m][lane] = s;
+  }
+}
+template <int TM, int NW>
+__device__ __forceinline__ float wide_total(float (*red)[TM][kWideRows], int m, int r) {
+  float s = red[0][m][r];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) s += red[w][m][r];
+  return s;
 }
 
-// grid = (ceil(I / (4 * 64 / LPR)), slots), 256 threads
-template <int TM, int LPR>
-__global__ __launch_bounds__(256) void wide_gateup_kernel(DecodeArgs a) {
+// grid = (I / kWideRows, slots), 64 * NW threads
+template <int TM, int NW>
+__global__ __launch_bounds__(64 * NW) void wide_gateup_kernel(DecodeArgs a) {
   const Slot sl = slot_info(a, blockIdx.y);
   if (sl.M < 0 || sl.M > a.gemm_above) return;  // (large buckets: the grouped GEMMs)
   const TensorDev tg = a.desc[sl.desc * 3 + 0], tu = a.desc[sl.desc * 3 + 1];
@@ -1046,16 +901,16 @@ __global__ __launch_bounds__(256) void wide_gateup_kernel(DecodeArgs a) {
   uint32_t* xl = wide_lds;
   float* xs = reinterpret_cast<float*>(wide_lds + TM * xts);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  constexpr int RPW = 64 / LPR;  // rows per wave
-  const int row = blockIdx.x * 4 * RPW + wave * RPW + lane / LPR, j = lane % LPR;
-  const int rowc = min(row, I - 1);
+  constexpr int ULANES = 64 / kWideRows;  // units of a row per wave and step
+  __shared__ float red[2][NW][TM][kWideRows];
+  const int row = blockIdx.x * kWideRows + lane % kWideRows, j = wave * ULANES + lane / kWideRows;
   for (int m0 = 0; m0 < sl.M; m0 += TM) {
     const int mc = min(TM, sl.M - m0);
     __syncthreads();
     for (int m = 0; m < mc; ++m) {
       const int t = sl.shared >= 0 ? m0 + m : a.perm[sl.base + m0 + m] / a.k;
       const MOEQ_GLOBAL u32x4* src = gptr(reinterpret_cast<const u32x4*>(a.x + (size_t)t * H));
-      for (int q = threadIdx.x; q < H / 8; q += 256) {
+      for (int q = threadIdx.x; q < H / 8; q += 64 * NW) {
         const u32x4 v = src[q];
         float s = 0.0f;
         s += bf16_lo(v.x); s += bf16_hi(v.x); s += bf16_lo(v.y); s += bf16_hi(v.y);
@@ -1068,21 +923,20 @@ __global__ __launch_bounds__(256) void wide_gateup_kernel(DecodeArgs a) {
       }
     }
     __syncthreads();
-    const WideAcc<TM> g = wide_row_dot_any<1, TM, LPR>(tg, rowc, U, H, j, xts, 0, sts, mc);
-    const WideAcc<TM> u = wide_row_dot_any<1, TM, LPR>(tu, rowc, U, H, j, xts, 0, sts, mc);
-#pragma unroll
-    for (int m = 0; m < TM; ++m) {
-      if (m < mc) {
-        const float gs = wide_sum<LPR>(g.v[m]), us = wide_sum<LPR>(u.v[m]);
-        if (j == LPR - 1 && row < I) a.h[(size_t)(sl.base + m0 + m) * I + row] = silu(gs) * us;
-      }
+    wide_put<TM, NW>(wide_row_dot_any<1, TM>(tg, row, U, j, NW * ULANES, xts, 0, sts, mc), red[0], wave, lane);
+    wide_put<TM, NW>(wide_row_dot_any<1, TM>(tu, row, U, j, NW * ULANES, xts, 0, sts, mc), red[1], wave, lane);
+    __syncthreads();
+    for (int i = threadIdx.x; i < kWideRows * mc; i += 64 * NW) {
+      const int m = i / kWideRows, r = i % kWideRows;
+      a.h[(size_t)(sl.base + m0 + m) * I + blockIdx.x * kWideRows + r] =
+          silu(wide_total<TM, NW>(red[0], m, r)) * wide_total<TM, NW>(red[1], m, r);
     }
   }
 }
 
-// grid = (ceil(H / (4 * 64 / LPR)), slots), 256 threads
-template <int TM, int LPR>
-__global__ __launch_bounds__(256) void wide_down_kernel(DecodeArgs a) {
+// grid = (H / kWideRows, slots), 64 * NW threads
+template <int TM, int NW>
+__global__ __launch_bounds__(64 * NW) void wide_down_kernel(DecodeArgs a) {
   const Slot sl = slot_info(a, blockIdx.y);
   if (sl.M < 0 || sl.M > a.gemm_above) return;  // (large buckets: the grouped GEMMs)
   const TensorDev td = a.desc[sl.desc * 3 + 2];
@@ -1092,16 +946,16 @@ __global__ __launch_bounds__(256) void wide_down_kernel(DecodeArgs a) {
   uint32_t* xl = wide_lds;
   float* xs = reinterpret_cast<float*>(wide_lds + TM * xts);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  constexpr int RPW = 64 / LPR;  // rows per wave
-  const int row = blockIdx.x * 4 * RPW + wave * RPW + lane / LPR, j = lane % LPR;
-  const int rowc = min(row, H - 1);
+  constexpr int ULANES = 64 / kWideRows;  // units of a row per wave and step
+  __shared__ float red[NW][TM][kWideRows];
+  const int row0 = blockIdx.x * kWideRows, row = row0 + lane % kWideRows, j = wave * ULANES + lane / kWideRows;
   for (int m0 = 0; m0 < sl.M; m0 += TM) {
     const int mc = min(TM, sl.M - m0);
     __syncthreads();
     // h rows as bfloat16 hi + lo pairs; block sums of hi + lo
     for (int m = 0; m < mc; ++m) {
       const MOEQ_GLOBAL f32x4* src = gptr(reinterpret_cast<const f32x4*>(a.h + (size_t)(sl.base + m0 + m) * I));
-      for (int q = threadIdx.x; q < I / 8; q += 256) {
+      for (int q = threadIdx.x; q < I / 8; q += 64 * NW) {
         const f32x4 v0 = src[2 * q], v1 = src[2 * q + 1];
         const float f[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
         uint32_t hi[4], lw[4];
@@ -1126,24 +980,20 @@ __global__ __launch_bounds__(256) void wide_down_kernel(DecodeArgs a) {
       }
     }
     __syncthreads();
-    const WideAcc<TM> o = wide_row_dot_any<2, TM, LPR>(td, rowc, U, I, j, xts, lo, sts, mc);
-#pragma unroll
-    for (int m = 0; m < TM; ++m) {
-      if (m < mc) {
-        const float os = wide_sum<LPR>(o.v[m]);
-        if (j == LPR - 1 && row < H) {
-          int prow;
-          float wv;
-          if (sl.shared >= 0) {
-            prow = a.n * a.k + sl.shared * a.n + m0 + m;
-            wv = 1.0f;
-          } else {
-            prow = a.perm[sl.base + m0 + m];
-            wv = a.w[prow];
-          }
-          a.partial[(size_t)prow * H + row] = wv * os;
-        }
+    wide_put<TM, NW>(wide_row_dot_any<2, TM>(td, row, U, j, NW * ULANES, xts, lo, sts, mc), red, wave, lane);
+    __syncthreads();
+    for (int i = threadIdx.x; i < kWideRows * mc; i += 64 * NW) {
+      const int m = i / kWideRows, r = i % kWideRows;
+      int prow;
+      float wv;
+      if (sl.shared >= 0) {
+        prow = a.n * a.k + sl.shared * a.n + m0 + m;
+        wv = 1.0f;
+      } else {
+        prow = a.perm[sl.base + m0 + m];
+        wv = a.w[prow];
       }
+      a.partial[(size_t)prow * H + row0 + r] = wv * wide_total<TM, NW>(red, m, r);
     }
   }
 }
@@ -1159,60 +1009,34 @@ hipError_t launch_lds(K kernel, dim3 grid, size_t lds, hipStream_t s, const Deco
   return hipGetLastError();
 }
 
-template <int TM, int LPR>
+template <int TM, int NW>
 hipError_t launch_wide_gateup_tm(const DecodeArgs& a, hipStream_t s) {
   const int U = a.H / kUnit;
   const size_t lds = (size_t)TM * (U * kXStride + U * 4) * 4;
-  const int rows_wg = 4 * (64 / LPR);
-  dim3 grid((a.I + rows_wg - 1) / rows_wg, a.wide_gateup == 1 ? a.S : a.S + a.max_active);
-  return launch_lds(wide_gateup_kernel<TM, LPR>, grid, lds, s, a);
+  dim3 grid(a.I / kWideRows, a.wide_gateup == 1 ? a.S : a.S + a.max_active);
+  return launch_lds(wide_gateup_kernel<TM, NW>, grid, lds, s, a, 64 * NW);
 }
 
-template <int TM, int LPR>
+template <int TM, int NW>
 hipError_t launch_wide_down_tm(const DecodeArgs& a, hipStream_t s) {
   const int U = a.I / kUnit;
   const size_t lds = (size_t)TM * (2 * U * kXStride + U * 4) * 4;
-  const int rows_wg = 4 * (64 / LPR);
-  dim3 grid((a.H + rows_wg - 1) / rows_wg, a.wide_down == 1 ? a.S : a.S + a.max_active);
-  return launch_lds(wide_down_kernel<TM, LPR>, grid, lds, s, a);
+  dim3 grid(a.H / kWideRows, a.wide_down == 1 ? a.S : a.S + a.max_active);
+  return launch_lds(wide_down_kernel<TM, NW>, grid, lds, s, a, 64 * NW);
 }
 
-// shared experts only: more lanes per row (as many as the units allow, up
-// to 32 for gate/up and 16 for down) keep enough workgroups for a few slots
+// shared experts only: eight waves share a row's units in gate/up (long rows,
+// few workgroups), else four
 hipError_t launch_wide_gateup(const DecodeArgs& a, hipStream_t s) {
   if (!a.wide_gateup) return hipSuccess;
-  const bool few = a.wide_gateup == 1 && a.H / kUnit >= 32;
-  if (a.n == 1) return few ? launch_wide_gateup_tm<1, 32>(a, s) : launch_wide_gateup_tm<1, 8>(a, s);
-  return few ? launch_wide_gateup_tm<4, 32>(a, s) : launch_wide_gateup_tm<4, 8>(a, s);
+  const bool few = a.wide_gateup == 1;
+  if (a.n == 1) return few ? launch_wide_gateup_tm<1, 8>(a, s) : launch_wide_gateup_tm<1, 4>(a, s);
+  return few ? launch_wide_gateup_tm<4, 8>(a, s) : launch_wide_gateup_tm<4, 4>(a, s);
 }
 
 hipError_t launch_wide_down(const DecodeArgs& a, hipStream_t s) {
   if (!a.wide_down) return hipSuccess;
-  const bool few = a.wide_down == 1 && a.I / kUnit >= 16;
-  if (a.n == 1) return few ? launch_wide_down_tm<1, 16>(a, s) : launch_wide_down_tm<1, 8>(a, s);
-  return few ? launch_wide_down_tm<4, 16>(a, s) : launch_wide_down_tm<4, 8>(a, s);
-}
-
-// Rows per wave step of the down GEMV are 64 / LPR; a workgroup covers
-// 4 * (64 / LPR) * steps rows of one slot.
-
-template <int LPR, int TM>
-hipError_t launch_down_lpr_tm(const DecodeArgs& a, hipStream_t s) {
-  const int slots = a.S + a.max_active;
-  const int U = a.I / kUnit;
-  const size_t lds = (size_t)TM * (U * kXStride + U * 8) * 4;
-  constexpr int RW = TM == 1 ? kDownSteps : kDownStepsM, NB = TM == 1 ? kDownBuf : kDownBufM;
-  const int rows_wg = 4 * (64 / LPR) * RW;
-  dim3 grid((a.H + rows_wg - 1) / rows_wg, slots);
-  return launch_lds(down_kernel<LPR, TM, RW, NB>, grid, lds, s, a);
-}
-
-template <int TM>
-hipError_t launch_down_tm(const DecodeArgs& a, hipStream_t s) {
-  const int U = a.I / kUnit;
-  if (U > 32) return launch_down_lpr_tm<64, TM>(a, s);
-  if (U > 16) return launch_down_lpr_tm<32, TM>(a, s);
-  return launch_down_lpr_tm<16, TM>(a, s);
+  return a.n == 1 ? launch_wide_down_tm<1, 4>(a, s) : launch_wide_down_tm<4, 4>(a, s);
 }
 
 }  // namespace
@@ -1224,8 +1048,8 @@ hipError_t launch_down_tm(const DecodeArgs& a, hipStream_t s) {
 hipError_t launch_gateup_decode_single(const DecodeArgs& a, hipStream_t s) {
   const int U = a.H / kUnit;
   const size_t lds = (size_t)(U * kXStride + U * 8) * 4;
-  dim3 grid((a.I + 15) / 16, a.S + a.max_active);
-  gateup1_kernel<<<grid, 256, lds, s>>>(a);
+  dim3 grid(a.I / kGuRows, a.S + a.max_active);
+  gateup1_kernel<<<grid, kGuThreads, lds, s>>>(a);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? launch_wide_gateup(a, s) : e;
 }
@@ -1238,8 +1062,8 @@ hipError_t launch_gateup_decode_multi(const DecodeArgs& a, hipStream_t s2) {
   constexpr int TM = MOEQ_GATEUPN_TOKENS;
   const int U = a.H / kUnit;
   const size_t lds = (size_t)TM * (U * kXStride + U * 8) * 4;
-  dim3 grid((a.I + 15) / 16, a.S + a.max_active);
-  return launch_lds(gateupn_kernel<TM>, grid, lds, s2, a);
+  dim3 grid(a.I / kGuRows, a.S + a.max_active);
+  return launch_lds(gateupn_kernel<TM>, grid, lds, s2, a, kGuThreads);
 }
 
 bool gateup1_routes(const RouterParams& rp) { return !rp.kept_ids && !rp.x && rp.E_row <= 256 && rp.k <= kMaxTopK; }
@@ -1248,13 +1072,13 @@ hipError_t launch_gateup_decode_routing(const DecodeArgs& a, const RouterParams&
                                         hipStream_t s) {
   const int U = a.H / kUnit;
   const size_t lds = (size_t)(U * kXStride + U * 8) * 4;
-  dim3 grid((a.I + 15) / 16, a.S + rp.k);
+  dim3 grid(a.I / kGuRows, a.S + rp.k);
   if (rp.E_row <= 64)
-    gateup1_route_kernel<1><<<grid, 256, lds, s>>>(a, rp, ws);
+    gateup1_route_kernel<1><<<grid, kGuThreads, lds, s>>>(a, rp, ws);
   else if (rp.E_row <= 128)
-    gateup1_route_kernel<2><<<grid, 256, lds, s>>>(a, rp, ws);
+    gateup1_route_kernel<2><<<grid, kGuThreads, lds, s>>>(a, rp, ws);
   else
-    gateup1_route_kernel<4><<<grid, 256, lds, s>>>(a, rp, ws);
+    gateup1_route_kernel<4><<<grid, kGuThreads, lds, s>>>(a, rp, ws);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? launch_wide_gateup(a, s) : e;
 }
@@ -1301,7 +1125,9 @@ hipError_t launch_down_decode(const DecodeArgs& a, hipStream_t s) {
       default: return launch_down1_b<4>(a, s);
     }
   }
-  const hipError_t e = a.n == 1 ? launch_down_tm<1>(a, s) : launch_down_tm<4>(a, s);
+  const int U = a.I / kUnit;
+  const size_t lds = (size_t)kDownTokens * (U * kXStride + U * 8) * 4;
+  const hipError_t e = launch_lds(down_kernel, dim3(a.H / 128, a.S + a.max_active), lds, s, a);
   return e == hipSuccess ? launch_wide_down(a, s) : e;
 }
 

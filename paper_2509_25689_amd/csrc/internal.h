@@ -25,13 +25,19 @@ constexpr int kDecodeMaxTokens = 64;
 constexpr int kDefaultDecodeMax = 64;
 
 // One stored tensor in the device layout.
-//   codes:  rows * (K/128) units of 16*bits bytes.  Row r's unit u, 16-byte
-//           chunk j lives at byte ((r*bits + j) * U + u) * 16 with U = K/128,
-//           so that chunk j of consecutive units is contiguous (one coalesced
-//           load per wave per chunk).  Inside a unit, block q (q = 0..3) is the
-//           dwords [q*bits, q*bits + bits) of the unit's 4*bits dwords, encoded
-//           as in encode_block() (weights.hip).
-//   scales: row-major [rows x K/32] binary16 (the canonical array, unchanged).
+//   codes:  tiles of 64 rows (rows are a multiple of 128), each U = K/128 units
+//           of `bits` chunks of 64 x 16 bytes: row r's 16-byte chunk j of unit u
+//           is the (((r/64 * U + u) * bits + j) * 64 + r%64)-th.  A wave whose
+//           lanes hold neighbouring rows reads runs of 16 bytes per row, in
+//           full lines.  Inside a unit, block q (q = 0..3) is the dwords
+//           [q*bits, q*bits + bits) of the unit's 4*bits dwords, encoded as in
+//           encode_block() (weights.hip).
+//   scales: the same tiles by pairs of units: the four binary16 scales of row
+//           r's unit u are the ((r/64 * ceil(U/2) + u/2) * 128 + r%64 * 2 +
+//           u%2)-th 8 bytes.  With U odd the last pair's second unit is zero
+//           (a weight decoded with it is zero).
+// With rows kept whole (a chunk plane of consecutive units, row after row) a
+// GEMM wave's load of 32 rows touched 32 separate half lines.
 struct TensorDev {
   const uint32_t* codes;
   const uint16_t* scales;
@@ -43,9 +49,8 @@ struct TensorDev {
 
 // TensorDev.flags: the grouped GEMMs' register-decoded kernels cannot take
 // the tensor, because some block scale is not a positive finite binary16 at
-// most rd_scale_limit(bits) (they form d * (c - z) from d * 2^(14 + b)) or
-// its rows hold an odd number of 128-weight units (they load the scales of
-// two units at once); its tiles go to the LDS-decoded kernels instead.
+// most rd_scale_limit(bits) (they form d * (c - z) from d * 2^(14 + b)); its
+// tiles go to the LDS-decoded kernels instead.
 constexpr int32_t kTensorOffRegisterDecoder = 1;
 // Largest binary16 bit pattern of a scale d with d * 2^(14 + b) finite.
 constexpr uint32_t rd_scale_limit(int b) { return 0x7BFFu - ((uint32_t)(14 + b) << 10); }
@@ -101,13 +106,14 @@ hipError_t launch_bucket_chunked(const int32_t* idx, int n, int k, int E, const 
 // weights.hip
 hipError_t launch_repack(const uint8_t* canon_codes, int rows, int K, int bits,
                          uint32_t* dev_codes, hipStream_t s);
+// canonical scales [rows x K/32] -> device layout; *key = max over them of
+// their key: the magnitude bits of a positive finite scale, 0xFFFF for a
+// zero, negative or non-finite one (atomic maximum: *key must start at 0)
+hipError_t launch_repack_scales(const uint16_t* canon, int rows, int K, uint16_t* dev, uint32_t* key,
+                                hipStream_t s);
 hipError_t launch_dequant(const TensorDev& t, float* out, hipStream_t s);
 // widths 2-4: the binary16-subnormal pair decoder rebuilt to float32
 hipError_t launch_dequant_sub(const TensorDev& t, float* out, hipStream_t s);
-// *out = max over the n binary16 scales of key(s): the magnitude bits of a
-// positive finite scale, 0xFFFF for a zero, negative or non-finite one
-// (atomic maximum: *out must start at 0)
-hipError_t launch_scale_key_max(const uint16_t* scales, size_t n, uint32_t* out, hipStream_t s);
 hipError_t launch_quantize(const float* w, int rows, int K, int bits, uint8_t* codes,
                            uint16_t* scales, hipStream_t s);
 // decode.hip

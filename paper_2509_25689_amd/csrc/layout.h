@@ -245,14 +245,30 @@ __device__ __forceinline__ void block_pairs_sub(const uint32_t* w, uint32_t (&p)
 // nibbles and dwords 4..7 their high nibbles, each plane exactly as a 4-bit
 // block.  The 8-bit value d (c - 128) = 16 d (hi - 8) + d (lo - 8) + 8 d.
 
-// Load unit u of a row (4*B dwords) with B coalesced 16-byte loads.
-//   row: the row's first dword; U: units per row.
+// Where a row's units live (TensorDev in internal.h): tiles of 64 rows, unit by
+// unit, chunk by chunk, the 64 rows' 16-byte chunks side by side; scales by
+// pairs of units.  A lane per row reads whole lines whatever the unit, and
+// a wave of the grouped GEMMs (32 rows) streams one contiguous region.
+constexpr int kRowTile = 64;
+
+// chunk 0 of unit 0 of `row`; chunk j of unit u follows at [(u * bits + j) * 64]
+__device__ __forceinline__ const MOEQ_GLOBAL u32x4* row_chunks(const uint32_t* codes, int bits, int U, int row) {
+  return gptr(reinterpret_cast<const u32x4*>(codes)) + (size_t)(row / kRowTile) * U * bits * kRowTile + row % kRowTile;
+}
+// the four binary16 scales of unit 0 of `row`; unit u's at [scale_step(u)]
+__device__ __forceinline__ const MOEQ_GLOBAL u32x2* row_scales(const uint16_t* scales, int U, int row) {
+  return gptr(reinterpret_cast<const u32x2*>(scales)) + (size_t)(row / kRowTile) * ((U + 1) / 2) * (2 * kRowTile) +
+         row % kRowTile * 2;
+}
+__device__ __forceinline__ int scale_step(int u) { return (u >> 1) * (2 * kRowTile) + (u & 1); }
+
+// The 4 * B dwords of unit u of the row whose chunks start at rc.
 template <int B>
-__device__ __forceinline__ void load_unit(const uint32_t* row, int U, int u, uint32_t (&w)[4 * B]) {
-  const MOEQ_GLOBAL u32x4* r4 = gptr(reinterpret_cast<const u32x4*>(row));
+__device__ __forceinline__ void load_unit(const MOEQ_GLOBAL u32x4* rc, int u, uint32_t (&w)[4 * B]) {
+  const MOEQ_GLOBAL u32x4* c = rc + (size_t)u * (B * kRowTile);
 #pragma unroll
   for (int j = 0; j < B; ++j) {
-    const u32x4 v = __builtin_nontemporal_load(r4 + (size_t)j * U + u);
+    const u32x4 v = __builtin_nontemporal_load(c + j * kRowTile);
     w[4 * j + 0] = v.x;
     w[4 * j + 1] = v.y;
     w[4 * j + 2] = v.z;

@@ -255,12 +255,6 @@ __device__ __forceinline__ bool rd_ok(const TensorDev& t) {
   return t.bits <= 4 && !(t.flags & kTensorOffRegisterDecoder);
 }
 
-// Row-base pointer of a tensor row in the device layout.
-__device__ __forceinline__ const MOEQ_GLOBAL u32x4* row_chunks(const TensorDev& t, int bits, int row) {
-  const int U = t.K / kUnit;
-  return gptr(reinterpret_cast<const u32x4*>(t.codes + (size_t)row * bits * U * 4));
-}
-
 // (c_lo, c_hi) at bit offset s of each half -> binary16 pair d * (c - z), exact
 // code extraction through the 1024 + c binary16 bit trick, then one rounding.
 template <int S>
@@ -363,18 +357,17 @@ struct RawBlk {
 // runs past the end of the first (Q and B are compile-time, so a block that
 // sits in one chunk issues one load).
 template <int B, int Q>
-__device__ __forceinline__ RawBlk load_blk(const MOEQ_GLOBAL u32x4* rc, const MOEQ_GLOBAL uint16_t* rs, int U,
-                                           int u) {
+__device__ __forceinline__ RawBlk load_blk(const MOEQ_GLOBAL u32x4* rc, const MOEQ_GLOBAL u32x2* rs, int u) {
   constexpr int c0 = (Q * B) >> 2;
   constexpr bool two = ((Q * B) & 3) + B > 4;
   RawBlk r;
-  r.a = rc[(size_t)c0 * U + u];
+  r.a = rc[(u * B + c0) * kRowTile];
   if constexpr (two)
-    r.b = rc[(size_t)(c0 + 1) * U + u];
+    r.b = rc[(u * B + c0 + 1) * kRowTile];
   else
     r.b = u32x4{0u, 0u, 0u, 0u};
   // the aligned pair of binary16 scales holding block Q's (Q even: low half)
-  r.sc = *reinterpret_cast<const MOEQ_GLOBAL uint32_t*>(rs + 4 * u + (Q & 2));
+  r.sc = reinterpret_cast<const MOEQ_GLOBAL uint32_t*>(rs + scale_step(u))[Q >> 1];
   return r;
 }
 
@@ -529,7 +522,7 @@ __device__ __forceinline__ void mfmas8(const half8 (&fa)[2][4], const half8 (&fb
 // half unit); NA: u32x4 activation pieces this thread moves per step (0, 2
 // or 4).
 template <int NT, int B, int BLK, bool DW, int NA>
-__device__ __forceinline__ void gemm_loop8(const MOEQ_GLOBAL u32x4* rc, const MOEQ_GLOBAL uint16_t* rs, int U,
+__device__ __forceinline__ void gemm_loop8(const MOEQ_GLOBAL u32x4* rc, const MOEQ_GLOBAL u32x2* rs,
                                            const MOEQ_GLOBAL u32x4* arow, _Float16* wdst, _Float16* adst,
                                            const _Float16* As, const _Float16* Ws, int lane, int wm, int wn, int nk,
                                            f32x4v (&acc)[NT][4][2]) {
@@ -537,7 +530,7 @@ __device__ __forceinline__ void gemm_loop8(const MOEQ_GLOBAL u32x4* rc, const MO
   u32x4 xv[2][NA > 0 ? NA : 1];
 #define L8(slot, st)                                                                        \
   do {                                                                                      \
-    if constexpr (DW) hw[slot] = load_blk<B, 2 * (slot) + BLK>(rc, rs, U, (st) >> 1);        \
+    if constexpr (DW) hw[slot] = load_blk<B, 2 * (slot) + BLK>(rc, rs, (st) >> 1);           \
     _Pragma("unroll") for (int i_ = 0; i_ < NA; ++i_) xv[slot][i_] = arow[(st) * 8 + i_];   \
   } while (0)
 #define D8(slot)                                                                                         \
@@ -591,8 +584,8 @@ __device__ void gateup_gemm_body8(const GemmArgs a, const SlotInfo sl, int m0, i
   const TensorDev t = wt ? tu : tg;
   const int bits = __builtin_amdgcn_readfirstlane(t.bits);
   const int wrow = n0 + (tid & 127);
-  const MOEQ_GLOBAL u32x4* rc = row_chunks(t, bits, wrow);
-  const MOEQ_GLOBAL uint16_t* rs = gptr(t.scales + (size_t)wrow * (H / kBlock));
+  const MOEQ_GLOBAL u32x4* rc = row_chunks(t.codes, bits, U, wrow);
+  const MOEQ_GLOBAL u32x2* rs = row_scales(t.scales, U, wrow);
   _Float16* wdst = Ws + (wt * BN + (tid & 127)) * LDS_STRIDE + 32 * blk;
   const int ar = tid >> 2, aq = tid & 3;
   int tok = 0;
@@ -608,7 +601,7 @@ __device__ void gateup_gemm_body8(const GemmArgs a, const SlotInfo sl, int m0, i
 #pragma unroll
       for (int c = 0; c < 2; ++c) acc[q][i][c] = f32x4v{0.f, 0.f, 0.f, 0.f};
   const int nk = H / BK;
-#define GU8(B, BL) gemm_loop8<2, B, BL, true, 2>(rc, rs, U, arow, wdst, adst, As, Ws, lane, wm, wn, nk, acc)
+#define GU8(B, BL) gemm_loop8<2, B, BL, true, 2>(rc, rs, arow, wdst, adst, As, Ws, lane, wm, wn, nk, acc)
   if (bits == 2) {
     if (blk) GU8(2, 1); else GU8(2, 0);
   } else if (bits == 3) {
@@ -682,8 +675,8 @@ __device__ void down_gemm_body8(const GemmArgs a, const SlotInfo sl, int m0, int
   const int blk = __builtin_amdgcn_readfirstlane((tid >> 7) & 1);
   const int bits = __builtin_amdgcn_readfirstlane(td.bits);
   const int wrow = n0 + (tid & 127);
-  const MOEQ_GLOBAL u32x4* rc = row_chunks(td, bits, wrow);
-  const MOEQ_GLOBAL uint16_t* rs = gptr(td.scales + (size_t)wrow * (I / kBlock));
+  const MOEQ_GLOBAL u32x4* rc = row_chunks(td.codes, bits, U, wrow);
+  const MOEQ_GLOBAL u32x2* rs = row_scales(td.scales, U, wrow);
   _Float16* wdst = Ws + (tid & 127) * LDS_STRIDE + 32 * blk;
   const int at = tid & 255, ar = at >> 1, ah = at & 1;
   const bool aok = m0 + ar < sl.M;
@@ -700,9 +693,9 @@ __device__ void down_gemm_body8(const GemmArgs a, const SlotInfo sl, int m0, int
 #pragma unroll
     for (int c = 0; c < 2; ++c) acc[0][i][c] = f32x4v{0.f, 0.f, 0.f, 0.f};
   const int nk = I / BK;
-#define DN8(B, BL) gemm_loop8<1, B, BL, true, 0>(rc, rs, U, arow, wdst, adst, As, Ws, lane, wm, wn, nk, acc)
+#define DN8(B, BL) gemm_loop8<1, B, BL, true, 0>(rc, rs, arow, wdst, adst, As, Ws, lane, wm, wn, nk, acc)
   if (!wrole) {
-    gemm_loop8<1, 4, 0, false, 4>(rc, rs, U, arow, wdst, adst, As, Ws, lane, wm, wn, nk, acc);
+    gemm_loop8<1, 4, 0, false, 4>(rc, rs, arow, wdst, adst, As, Ws, lane, wm, wn, nk, acc);
   } else {
     if (bits == 2) {
       if (blk) DN8(2, 1); else DN8(2, 0);
@@ -987,7 +980,7 @@ __device__ __forceinline__ void rd_kloop(const MOEQ_GLOBAL u32x4* const (&rc)[RD
       for (int v = 0; v < 2; ++v) {
         const int uc = min(4 * V + 2 * g + v, Uk - 1);
 #pragma unroll
-        for (int r = 0; r < RD_RT; ++r) dst[r][v].c[j] = rc[r][(size_t)j * Uk + uc];
+        for (int r = 0; r < RD_RT; ++r) dst[r][v].c[j] = rc[r][(uc * B + j) * kRowTile];
       }
     }
   };
@@ -1016,7 +1009,7 @@ __device__ __forceinline__ void rd_kloop(const MOEQ_GLOBAL u32x4* const (&rc)[RD
       const int unit = 4 * V + 2 * g;
 #pragma unroll
       for (int r = 0; r < RD_RT; ++r) {
-        const MOEQ_GLOBAL u32x4* src = unit < Uk ? reinterpret_cast<const MOEQ_GLOBAL u32x4*>(rs[r] + unit)
+        const MOEQ_GLOBAL u32x4* src = unit < Uk ? reinterpret_cast<const MOEQ_GLOBAL u32x4*>(rs[r] + scale_step(unit))
                                                  : reinterpret_cast<const MOEQ_GLOBAL u32x4*>(zero);
         sn[r] = *src;
       }
@@ -1195,8 +1188,8 @@ __device__ void rd_gateup_tile(const GemmArgs& a, const SlotInfo& sl, int m0, in
 #pragma unroll
   for (int r = 0; r < RD_RT; ++r) {
     const int row = act ? row0 + 32 * r + (lane & 31) : 0;
-    rc[r] = gptr(reinterpret_cast<const u32x4*>(t.codes + (size_t)row * bits * Uk * 4));
-    rs[r] = gptr(reinterpret_cast<const u32x2*>(t.scales + (size_t)row * (H / kBlock)));
+    rc[r] = row_chunks(t.codes, bits, Uk, row);
+    rs[r] = row_scales(t.scales, Uk, row);
   }
   // staging slots of this thread: rows j * RD_RPJ + tid / 16 (the NT token
   // tiles multiplied), piece (tid % 16) ^ (row % 16)
@@ -1279,8 +1272,8 @@ __device__ void rd_down_tile(const GemmArgs& a, const SlotInfo& sl, int m0, int 
 #pragma unroll
   for (int r = 0; r < RD_RT; ++r) {
     const int row = act ? row0 + 32 * r + (lane & 31) : 0;
-    rc[r] = gptr(reinterpret_cast<const u32x4*>(td.codes + (size_t)row * bits * Uk * 4));
-    rs[r] = gptr(reinterpret_cast<const u32x2*>(td.scales + (size_t)row * (I / kBlock)));
+    rc[r] = row_chunks(td.codes, bits, Uk, row);
+    rs[r] = row_scales(td.scales, Uk, row);
   }
   const MOEQ_GLOBAL u32x4* arow[RD_APT] = {};
 #pragma unroll
@@ -1390,15 +1383,15 @@ __global__ __launch_bounds__(256) void dequant_gemm_kernel(TensorDev t, uint16_t
   const long long gid = (long long)blockIdx.x * 256 + threadIdx.x;
   if (gid >= (long long)t.rows * U) return;
   const int r = (int)(gid / U), u = (int)(gid % U);
-  const MOEQ_GLOBAL u32x4* rc = row_chunks(t, B, r);
-  const MOEQ_GLOBAL uint16_t* rs = gptr(t.scales + (size_t)r * (t.K / kBlock));
+  const MOEQ_GLOBAL u32x4* rc = row_chunks(t.codes, B, U, r);
+  const MOEQ_GLOBAL u32x2* rs = row_scales(t.scales, U, r);
   u32x4* o = reinterpret_cast<u32x4*>(out + (size_t)r * t.K + kUnit * u);
   if (rd_ok(t)) {
     if constexpr (B <= 4) {
     RdUnit<B> un;
 #pragma unroll
-    for (int j = 0; j < B; ++j) un.c[j] = rc[(size_t)j * U + u];
-    un.s = *reinterpret_cast<const MOEQ_GLOBAL u32x2*>(rs + 4 * u);
+    for (int j = 0; j < B; ++j) un.c[j] = rc[(u * B + j) * kRowTile];
+    un.s = rs[scale_step(u)];
     const RdConsts kc = rd_consts<B>();
 #define DQG(Q, M) o[4 * (Q) + (M)] = __builtin_bit_cast(u32x4, rd_piece<B, Q, M>(un, kc))
     DQG(0, 0); DQG(0, 1); DQG(0, 2); DQG(0, 3);
@@ -1411,7 +1404,7 @@ __global__ __launch_bounds__(256) void dequant_gemm_kernel(TensorDev t, uint16_t
     __attribute__((aligned(16))) _Float16 blk[32];
 #define DQW(Q)                                                                    \
   do {                                                                            \
-    const RawBlk rb = load_blk<B, Q>(rc, rs, U, u);                               \
+    const RawBlk rb = load_blk<B, Q>(rc, rs, u);                                  \
     decode_blk<B>(rb, ((Q) * B) & 3, ((Q) & 1) != 0, blk);                        \
     _Pragma("unroll") for (int i = 0; i < 4; ++i) o[4 * (Q) + i] = reinterpret_cast<const u32x4*>(blk)[i]; \
   } while (0)

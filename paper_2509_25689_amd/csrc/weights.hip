@@ -15,10 +15,12 @@ namespace {
 
 // codes of one block (32 values < 2^b) -> its b device dwords
 template <int B>
-__device__ void encode_block(const uint8_t* c, uint32_t* w) {
+__device__ __forceinline__ void encode_block(const uint8_t* c, uint32_t* w) {
+#pragma unroll
   for (int d = 0; d < B; ++d) w[d] = 0u;
   if constexpr (B == 8) {
     uint8_t lo[32], hi[32];
+#pragma unroll
     for (int i = 0; i < 32; ++i) {
       lo[i] = c[i] & 15;
       hi[i] = c[i] >> 4;
@@ -26,9 +28,12 @@ __device__ void encode_block(const uint8_t* c, uint32_t* w) {
     encode_block<4>(lo, w);
     encode_block<4>(hi, w + 4);
   } else if constexpr (B == 6) {
+#pragma unroll
     for (int d = 0; d < 6; ++d)
+#pragma unroll
       for (int f = 0; f < 2; ++f)
         w[d] |= (uint32_t)c[4 * d + 2 * f] << (6 * f) | (uint32_t)c[4 * d + 2 * f + 1] << (16 + 6 * f);
+#pragma unroll
     for (int m = 0; m < 4; ++m) {
       const uint32_t c0 = c[24 + 2 * m], c1 = c[25 + 2 * m];
       w[m] |= (c0 & 15u) << 12 | (c1 & 15u) << 28;
@@ -36,50 +41,112 @@ __device__ void encode_block(const uint8_t* c, uint32_t* w) {
       w[4 + m / 2] |= (c0 >> 4) << sh | (c1 >> 4) << (16 + sh);
     }
   } else if constexpr (B == 5) {
+#pragma unroll
     for (int d = 0; d < 5; ++d)
+#pragma unroll
       for (int f = 0; f < 3; ++f)
         w[d] |= (uint32_t)c[6 * d + 2 * f] << (5 * f) | (uint32_t)c[6 * d + 2 * f + 1] << (16 + 5 * f);
+#pragma unroll
     for (int q = 0; q < 5; ++q)
       w[q] |= ((uint32_t)(c[30] >> q) & 1u) << 15 | ((uint32_t)(c[31] >> q) & 1u) << 31;
   } else if constexpr (B == 4) {
+#pragma unroll
     for (int d = 0; d < 4; ++d)
+#pragma unroll
       for (int s = 0; s < 4; ++s)
         w[d] |= (uint32_t)c[8 * d + 2 * s] << (4 * s) | (uint32_t)c[8 * d + 2 * s + 1] << (16 + 4 * s);
   } else if constexpr (B == 2) {
+#pragma unroll
     for (int d = 0; d < 2; ++d)
+#pragma unroll
       for (int s = 0; s < 8; ++s)
         w[d] |= (uint32_t)c[16 * d + 2 * s] << (2 * s) |
                 (uint32_t)c[16 * d + 2 * s + 1] << (16 + 2 * s);
   } else {
+#pragma unroll
     for (int d = 0; d < 3; ++d)
+#pragma unroll
       for (int f = 0; f < 5; ++f)
         w[d] |= (uint32_t)c[10 * d + 2 * f] << (3 * f) |
                 (uint32_t)c[10 * d + 2 * f + 1] << (16 + 3 * f);
+#pragma unroll
     for (int q = 0; q < 3; ++q)
       w[q] |= ((uint32_t)(c[30] >> q) & 1u) << 15 | ((uint32_t)(c[31] >> q) & 1u) << 31;
   }
 }
 
-// one thread per (row, unit): read 4 canonical blocks, write b 16-byte chunks
-template <int B>
-__global__ __launch_bounds__(256) void repack_kernel(const uint8_t* canon, int rows, int K,
-                                                     uint32_t* dev) {
+// One thread per (row, unit), lanes along the 64 rows of a tile so that the
+// chunks leave in whole lines: 4 canonical blocks (16 * B bytes) in, b chunks
+// out, the codes moved between registers with shifts known at compile time.
+// WORDS: the canonical codes are 4-byte aligned (else bytes).
+template <int B, bool WORDS>
+__global__ __launch_bounds__(256) void repack_kernel(const uint8_t* canon, int rows, int K, uint32_t* dev) {
   const int U = K / kUnit;
   const long long gid = (long long)blockIdx.x * 256 + threadIdx.x;
   if (gid >= (long long)rows * U) return;
-  const int r = (int)(gid / U), u = (int)(gid % U);
-  const uint8_t* src = canon + ((size_t)r * (K / kBlock) + 4 * u) * 4 * B;  // 16*B bytes
-  uint8_t c[kUnit];
-  for (int i = 0; i < kUnit; ++i) {
-    const int bit = i * B;
-    const uint32_t lo = src[bit >> 3], hi = (bit >> 3) + 1 < 16 * B ? src[(bit >> 3) + 1] : 0u;
-    c[i] = (uint8_t)(((lo | hi << 8) >> (bit & 7)) & ((1u << B) - 1u));
+  const long long tu = gid / kRowTile;
+  const int r = (int)(tu / U) * kRowTile + (int)(gid % kRowTile), u = (int)(tu % U);
+  const uint8_t* src = canon + ((size_t)r * U + u) * 16 * B;
+  uint32_t cw[4 * B];
+#pragma unroll
+  for (int i = 0; i < 4 * B; ++i) {
+    if constexpr (WORDS)
+      cw[i] = reinterpret_cast<const uint32_t*>(src)[i];
+    else
+      cw[i] = (uint32_t)src[4 * i] | (uint32_t)src[4 * i + 1] << 8 | (uint32_t)src[4 * i + 2] << 16 |
+              (uint32_t)src[4 * i + 3] << 24;
   }
   uint32_t w[4 * B];
-  for (int q = 0; q < 4; ++q) encode_block<B>(c + 32 * q, w + q * B);
-  uint32_t* row = dev + (size_t)r * B * U * 4;
-  for (int j = 0; j < B; ++j)
-    for (int e = 0; e < 4; ++e) row[((size_t)j * U + u) * 4 + e] = w[4 * j + e];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    uint8_t c[kBlock];
+#pragma unroll
+    for (int i = 0; i < kBlock; ++i) {
+      const int bit = i * B, d = q * B + (bit >> 5), s = bit & 31;
+      uint32_t v = cw[d] >> s;
+      if (s + B > 32) v |= cw[d + 1] << (32 - s);
+      c[i] = (uint8_t)(v & ((1u << B) - 1u));
+    }
+    encode_block<B>(c, w + q * B);
+  }
+  u32x4* out = reinterpret_cast<u32x4*>(dev) + (size_t)tu * B * kRowTile + gid % kRowTile;
+#pragma unroll
+  for (int j = 0; j < B; ++j) out[j * kRowTile] = u32x4{w[4 * j], w[4 * j + 1], w[4 * j + 2], w[4 * j + 3]};
+}
+
+__device__ __forceinline__ uint32_t scale_key(uint32_t v) {
+  const uint32_t mag = v & 0x7FFFu;
+  return (v & 0x8000u) || mag == 0 || mag >= 0x7C00u ? 0xFFFFu : mag;
+}
+
+// one thread per (row, pair of units): 8 scales (4 and zeros past an odd row)
+__global__ __launch_bounds__(256) void repack_scales_kernel(const uint16_t* canon, int rows, int K, uint16_t* dev,
+                                                            uint32_t* key) {
+  __shared__ uint32_t wmax[4];
+  const int U = K / kUnit, P = (U + 1) / 2;
+  const long long gid = (long long)blockIdx.x * 256 + threadIdx.x;
+  uint32_t m = 0;
+  if (gid < (long long)rows * P) {
+    const long long tp = gid / kRowTile;
+    const int r = (int)(tp / P) * kRowTile + (int)(gid % kRowTile), p = (int)(tp % P);
+    const uint16_t* src = canon + (size_t)r * (K / kBlock) + 8 * p;
+    const int ns = 2 * p + 1 < U ? 8 : 4;
+    uint32_t v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      v[i] = i < ns ? src[i] : 0u;
+      if (i < ns) m = max(m, scale_key(v[i]));
+    }
+    reinterpret_cast<u32x4*>(dev)[gid] =
+        u32x4{v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16};
+  }
+  for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
+  if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    m = max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3]));
+    if (m) atomicMax(key, m);
+  }
 }
 
 // one thread per (row, unit): the bfloat16-form unpacking of block_pairs
@@ -92,13 +159,13 @@ __global__ __launch_bounds__(256) void dequant_kernel(TensorDev t, float* out) {
   if (gid >= (long long)t.rows * U) return;
   const int r = (int)(gid / U), u = (int)(gid % U);
   uint32_t w[4 * B];
-  load_unit<B>(t.codes + (size_t)r * B * U * 4, U, u, w);
-  const uint16_t* sc = t.scales + (size_t)r * (t.K / kBlock) + 4 * u;
+  load_unit<B>(row_chunks(t.codes, B, U, r), u, w);
+  const u32x2 sc = row_scales(t.scales, U, r)[scale_step(u)];
   const float z = (float)(1 << (B - 1)), unit = (float)(1 << (B <= 7 ? 7 - B : 0));
   float* o = out + (size_t)r * t.K + kUnit * u;
   const PairConsts pk = pair_consts();
   for (int q = 0; q < 4; ++q) {
-    const float d = half_to_float(sc[q]);
+    const float d = half_to_float(((q < 2 ? sc.x : sc.y) >> (16 * (q & 1))) & 0xFFFFu);
     if constexpr (B == 8) {
       uint32_t pl[16], ph[16];
       block_pairs<4>(w + 8 * q, pk, pl);
@@ -132,12 +199,12 @@ __global__ __launch_bounds__(256) void dequant_sub_kernel(TensorDev t, float* ou
   if (gid >= (long long)t.rows * U) return;
   const int r = (int)(gid / U), u = (int)(gid % U);
   uint32_t w[4 * B];
-  load_unit<B>(t.codes + (size_t)r * B * U * 4, U, u, w);
-  const uint16_t* sc = t.scales + (size_t)r * (t.K / kBlock) + 4 * u;
+  load_unit<B>(row_chunks(t.codes, B, U, r), u, w);
+  const u32x2 sc = row_scales(t.scales, U, r)[scale_step(u)];
   const float z = (float)(1 << (B - 1));
   float* o = out + (size_t)r * t.K + kUnit * u;
   for (int q = 0; q < 4; ++q) {
-    const float d = half_to_float(sc[q]);
+    const float d = half_to_float(((q < 2 ? sc.x : sc.y) >> (16 * (q & 1))) & 0xFFFFu);
     uint32_t p[16];
     block_pairs_sub<B>(w + q * B, p);
 #pragma unroll
@@ -256,55 +323,29 @@ hipError_t launch_repack(const uint8_t* canon, int rows, int K, int bits, uint32
                          hipStream_t s) {
   const long long n = (long long)rows * (K / kUnit);
   const int grid = (int)((n + 255) / 256);
+#define REPACK(B)                                             \
+  case B:                                                     \
+    if (((uintptr_t)canon & 3) == 0)                          \
+      repack_kernel<B, true><<<grid, 256, 0, s>>>(canon, rows, K, dev);  \
+    else                                                      \
+      repack_kernel<B, false><<<grid, 256, 0, s>>>(canon, rows, K, dev); \
+    break
   switch (bits) {
-    case 2: repack_kernel<2><<<grid, 256, 0, s>>>(canon, rows, K, dev); break;
-    case 3: repack_kernel<3><<<grid, 256, 0, s>>>(canon, rows, K, dev); break;
-    case 4: repack_kernel<4><<<grid, 256, 0, s>>>(canon, rows, K, dev); break;
-    case 5: repack_kernel<5><<<grid, 256, 0, s>>>(canon, rows, K, dev); break;
-    case 6: repack_kernel<6><<<grid, 256, 0, s>>>(canon, rows, K, dev); break;
-    case 8: repack_kernel<8><<<grid, 256, 0, s>>>(canon, rows, K, dev); break;
+    REPACK(2);
+    REPACK(3);
+    REPACK(4);
+    REPACK(5);
+    REPACK(6);
+    REPACK(8);
     default: return hipErrorInvalidValue;
   }
+#undef REPACK
   return hipGetLastError();
 }
 
-namespace {
-__device__ __forceinline__ uint32_t scale_key(uint32_t v) {
-  const uint32_t mag = v & 0x7FFFu;
-  return (v & 0x8000u) || mag == 0 || mag >= 0x7C00u ? 0xFFFFu : mag;
-}
-
-// 8 scales per thread and load, a workgroup maximum in LDS, one atomic per
-// workgroup
-__global__ __launch_bounds__(256) void scale_key_max_kernel(const uint16_t* sc, size_t n, uint32_t* out) {
-  __shared__ uint32_t wmax[4];
-  uint32_t m = 0;
-  const size_t n8 = n / 8;
-  const u32x4* s8 = reinterpret_cast<const u32x4*>(sc);
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n8; i += (size_t)gridDim.x * 256) {
-    const u32x4 v = s8[i];
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) m = max(m, max(scale_key(w[j] & 0xFFFFu), scale_key(w[j] >> 16)));
-  }
-  for (size_t i = n8 * 8 + (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256)
-    m = max(m, scale_key(sc[i]));
-  for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
-  if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = m;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    m = max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3]));
-    if (m) atomicMax(out, m);
-  }
-}
-}  // namespace
-
-hipError_t launch_scale_key_max(const uint16_t* scales, size_t n, uint32_t* out, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  // the scales are 256-byte aligned in the layer's store (16-byte loads)
-  const size_t want = (n / 8 + 255) / 256 + 1;
-  const int grid = (int)(want < 256 ? want : 256);
-  scale_key_max_kernel<<<grid, 256, 0, s>>>(scales, n, out);
+hipError_t launch_repack_scales(const uint16_t* canon, int rows, int K, uint16_t* dev, uint32_t* key, hipStream_t s) {
+  const long long n = (long long)rows * ((K / kUnit + 1) / 2);
+  repack_scales_kernel<<<(int)((n + 255) / 256), 256, 0, s>>>(canon, rows, K, dev, key);
   return hipGetLastError();
 }
 
