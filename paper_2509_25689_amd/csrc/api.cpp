@@ -431,8 +431,8 @@ moeq_status moeq_layer_create(const moeq_config* cfg, const uint8_t* expert_mask
     for (int p = 0; p < 3; ++p)
       if ((he = upload(E + s, p, shared[s * 3 + p])) != hipSuccess) return bail(he, "weight upload");
 
-  // tensors the grouped GEMMs' register decoder cannot take (wider than 4
-  // bits, or a scale outside (0, rd_scale_limit(bits)])
+  // tensors the grouped GEMMs' register decoder cannot take (a scale outside
+  // (0, rd_scale_limit(bits)])
   {
     std::vector<uint32_t> keys(plan.size());
     if ((he = hipMemcpy(keys.data(), scale_keys, sizeof(uint32_t) * plan.size(), hipMemcpyDeviceToHost)) !=
@@ -441,9 +441,8 @@ moeq_status moeq_layer_create(const moeq_config* cfg, const uint8_t* expert_mask
     for (size_t i = 0; i < plan.size(); ++i) {
       TensorDev& d = L->desc_host[i];
       if (!d.codes) continue;
-      if (d.bits <= 4 && keys[i] > rd_scale_limit(d.bits))
+      if (keys[i] > rd_scale_limit(d.bits)) {
         d.flags |= kTensorOffRegisterDecoder;
-      if (d.bits > 4 || (d.flags & kTensorOffRegisterDecoder)) {
         if (i % 3 == 2)
           L->lds_down = 1;
         else
@@ -586,29 +585,39 @@ moeq_status moeq_forward(moeq_layer* L, const void* x, const float* logits, int3
   const bool self_routed = !prefill && n == 1 && gateup1_routes(rp1);
   if (e == hipSuccess && !self_routed) e = route_and_bucket(L, logits, n, s, prefill || hybrid ? x : nullptr);
   mark(1);
-  if (e == hipSuccess) {
-    if (prefill) {
-      e = launch_prefill_tiles(a, s);
-      if (e == hipSuccess) e = launch_gateup_prefill(a, s);
-    } else if (n > 1) {
-      if (hybrid) e = launch_prefill_tiles(a, s);
-      // fork: the buckets of 2-64 tokens on the layer's second stream, then join
-      if (e == hipSuccess) e = hipEventRecord(L->fork_ev, s);
-      if (e == hipSuccess) e = hipStreamWaitEvent(L->aux, L->fork_ev, 0);
-      if (e == hipSuccess) e = launch_gateup_decode_multi(a, L->aux);
-      if (e == hipSuccess) e = hipEventRecord(L->join_ev, L->aux);
-      if (e == hipSuccess) e = launch_gateup_decode_single(a, s);
-      if (e == hipSuccess && hybrid) e = launch_gateup_prefill(a, s);
-      if (e == hipSuccess) e = hipStreamWaitEvent(s, L->join_ev, 0);
-    } else if (self_routed) {
-      e = launch_gateup_decode_routing(a, rp1, L->ws, s);
-    } else {
-      e = launch_gateup_decode(a, s);
-    }
+  // work beside the caller's stream: fork() orders the auxiliary stream after
+  // it, join() brings it back
+  auto fork = [&] {
+    if (e == hipSuccess) e = hipEventRecord(L->fork_ev, s);
+    if (e == hipSuccess) e = hipStreamWaitEvent(L->aux, L->fork_ev, 0);
+  };
+  auto join = [&] {
+    if (e == hipSuccess) e = hipEventRecord(L->join_ev, L->aux);
+    if (e == hipSuccess) e = hipStreamWaitEvent(s, L->join_ev, 0);
+  };
+  const bool gemms = prefill || hybrid;
+  if (e == hipSuccess && gemms) e = launch_prefill_tiles(a, s);
+  if (self_routed) {
+    if (e == hipSuccess) e = launch_gateup_decode_routing(a, rp1, L->ws, s);
+  } else if (!prefill && n == 1) {
+    if (e == hipSuccess) e = launch_gateup_decode(a, s);
+  } else {
+    // beside each other: the buckets of 2-64 tokens of the decode path and
+    // the small tiles of the grouped GEMMs, and the rest
+    fork();
+    if (e == hipSuccess && gemms) e = launch_gateup_prefill(a, s);
+    if (e == hipSuccess && !prefill) e = launch_gateup_decode_multi(a, L->aux);
+    if (e == hipSuccess && gemms) e = launch_gateup_prefill_small(a, L->aux);
+    if (e == hipSuccess && !prefill) e = launch_gateup_decode_single(a, s);
+    join();
   }
   mark(2);
-  if (e == hipSuccess) e = prefill ? launch_down_prefill(a, s) : launch_down_decode(a, s);
-  if (e == hipSuccess && hybrid) e = launch_down_prefill(a, s);
+  if (e == hipSuccess && gemms) e = launch_h16(a, s);
+  if (gemms) fork();
+  if (e == hipSuccess && gemms) e = launch_down_prefill(a, s);
+  if (e == hipSuccess && gemms) e = launch_down_prefill_small(a, L->aux);
+  if (e == hipSuccess && !prefill) e = launch_down_decode(a, s);
+  if (gemms) join();
   mark(3);
   if (e == hipSuccess && (prefill || !down_combines(a))) e = launch_combine(a, s);
   mark(4);

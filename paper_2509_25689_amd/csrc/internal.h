@@ -145,8 +145,8 @@ struct DecodeArgs {
   // slots with a 5/6/8-bit gate or up (down) tensor: 0 none, 1 shared
   // experts only, 2 routed experts too
   int32_t wide_gateup, wide_down;
-  // many-token path: some kept or shared gate/up (down) tensor is wider than
-  // 4 bits or off the register decoder, so the LDS-decoded GEMM runs too
+  // many-token path: some kept or shared gate/up (down) tensor is off the
+  // register decoder, so the LDS-decoded GEMM runs too
   int32_t lds_gateup, lds_down;
   // buckets of more rows take the grouped GEMMs (prefill path: 0, every
   // bucket; decode path: the large buckets of a skewed routing), the others
@@ -193,18 +193,22 @@ hipError_t launch_expert_importance(const int32_t* offsets, const int32_t* perm,
                                     double alpha, int keep, double* importance, uint8_t* mask, int32_t* counts,
                                     hipStream_t s);
 // prefill.hip
-constexpr int kGemmBM = 128;  // tokens per m-tile of the LDS-decoded (5/6/8-bit) GEMMs
+constexpr int kGemmBM = 128;  // tokens per m-tile of the LDS-decoded GEMMs
 #ifndef MOEQ_RD_TILE
 #define MOEQ_RD_TILE 128
 #endif
-constexpr int kRdTile = MOEQ_RD_TILE;  // tokens per tile of the register-decoded (2-4-bit) GEMMs
+constexpr int kRdTile = MOEQ_RD_TILE;  // tokens per tile of the register-decoded GEMMs
 int prefill_max_mtiles(int n, int k, int S, int n_kept);
 int prefill_max_rtiles(int n, int k, int S, int n_kept);
-// the tile list (and cleared h row maxima), then the gate/up GEMMs, then
-// h in binary16 and the down GEMMs
+// the tile list (and cleared h row maxima), then the gate/up GEMMs, h in
+// binary16 and the down GEMMs; the tiles of up to 32 tokens of 2-4-bit
+// tensors (_small) are kernels of their own, which may run beside the others
 hipError_t launch_prefill_tiles(const DecodeArgs& a, hipStream_t s);
 hipError_t launch_gateup_prefill(const DecodeArgs& a, hipStream_t s);
+hipError_t launch_gateup_prefill_small(const DecodeArgs& a, hipStream_t s);
+hipError_t launch_h16(const DecodeArgs& a, hipStream_t s);
 hipError_t launch_down_prefill(const DecodeArgs& a, hipStream_t s);
+hipError_t launch_down_prefill_small(const DecodeArgs& a, hipStream_t s);
 // the grouped GEMMs' weight decoder: binary16 d * (c - 2^(b-1)) bit patterns
 hipError_t launch_dequant_gemm(const TensorDev& t, uint16_t* out, hipStream_t s);
 

@@ -252,7 +252,7 @@ __device__ __forceinline__ bool rd_tile_of_wg(const int32_t* tiles, int hw, int 
 // hold an even number of units (flags); the LDS-decoded GEMMs take every
 // other tensor.
 __device__ __forceinline__ bool rd_ok(const TensorDev& t) {
-  return t.bits <= 4 && !(t.flags & kTensorOffRegisterDecoder);
+  return !(t.flags & kTensorOffRegisterDecoder);
 }
 
 // (c_lo, c_hi) at bit offset s of each half -> binary16 pair d * (c - z), exact
@@ -801,24 +801,24 @@ constexpr int RD_WAVES = MOEQ_RD_WAVES;
 constexpr int RD_THREADS = 64 * RD_WAVES;
 constexpr int RD_NTMAX = RD_T / 32;   // token tiles of 32 per workgroup tile
 #ifndef MOEQ_RD_RT
-#define MOEQ_RD_RT (RD_T >= 128 && RD_WAVES == 8 ? 1 : 2)
+#define MOEQ_RD_RT 1
 #endif
 constexpr int RD_RT = MOEQ_RD_RT;  // row tiles of 32 per wave
 constexpr int RD_WROWS = 32 * RD_RT;  // weight rows per wave
 constexpr int RD_ROWS = RD_WAVES * RD_WROWS;  // weight rows per workgroup
-constexpr int RD_SUB = RD_T * 256;    // bytes of one activation sub-stage
+constexpr int RD_TSUB = 32 * 256;     // bytes of one activation sub-stage of a token tile
 constexpr int RD_NBUF = 4;            // activation sub-stages resident in LDS
-constexpr int RD_APT = RD_SUB / 16 / RD_THREADS;  // 16-byte staging pieces per thread and sub-stage
+constexpr int RD_APT = RD_NTMAX * RD_TSUB / 16 / RD_THREADS;  // 16-byte staging pieces per thread and sub-stage
 constexpr int RD_RPJ = RD_THREADS / 16;  // token rows per staging piece index
 static_assert(32 % RD_RPJ == 0, "the staging pieces of a token tile are whole");
 // staging pieces per thread for NT token tiles
 template <int NT>
 constexpr int rd_apt() { return NT * 32 / RD_RPJ; }
-constexpr size_t RD_LDS = (size_t)RD_NBUF * RD_SUB;
+constexpr size_t rd_lds(int nt) { return (size_t)RD_NBUF * nt * RD_TSUB; }
 static_assert(RD_WAVES * RD_WROWS == RD_ROWS, "the waves cover the workgroup's rows");
-static_assert(RD_LDS >= (size_t)(RD_WAVES / 2) * RD_RT * RD_NTMAX * 64 * 64,
+static_assert(rd_lds(1) >= (size_t)(RD_WAVES / 2) * RD_RT * 64 * 64,
               "the SwiGLU hand-over must fit the activation buffers");
-static_assert(RD_LDS <= 160 * 1024, "the activation buffers fit a compute unit's LDS");
+static_assert(rd_lds(RD_NTMAX) <= 160 * 1024, "the activation buffers fit a compute unit's LDS");
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
@@ -884,7 +884,20 @@ template <int B, int Q, int M>
 __device__ __forceinline__ half8 rd_piece(const RdUnit<B>& u, const RdConsts& k) {
   const RdScale sc = rd_scale<B, Q>(u);
   uint32_t p[4];
-  if constexpr (B == 4) {
+  auto fma = [&](uint32_t v) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(__builtin_bit_cast(half2_t, v), sc.D, sc.C));
+  };
+  constexpr int A = rd_at<B>();
+  if constexpr (B == 8) {
+    // low nibbles in dword M and high nibbles in dword 4 + M of the block
+    const uint32_t lo = rd_dword(u, 8 * Q + M), hi = rd_dword(u, 8 * Q + 4 + M);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t l = (4 * i >= A ? lo >> (4 * i >= A ? 4 * i - A : 0) : lo << (4 * i >= A ? 0 : A - 4 * i)) & 0x003C003Cu;
+      const uint32_t h = 4 * i >= A + 4 ? hi >> (4 * i >= A + 4 ? 4 * i - A - 4 : 0) : hi << (4 * i >= A + 4 ? 0 : A + 4 - 4 * i);
+      p[i] = fma(and_or(h, 0x03C003C0u, l));
+    }
+  } else if constexpr (B == 4) {
     const uint32_t w = rd_dword(u, 4 * Q + M);
     p[0] = rd_pair<B, 0>(w, k, sc);
     p[1] = rd_pair<B, 4>(w, k, sc);
@@ -897,28 +910,44 @@ __device__ __forceinline__ half8 rd_piece(const RdUnit<B>& u, const RdConsts& k)
     p[1] = rd_pair<B, o + 2>(w, k, sc);
     p[2] = rd_pair<B, o + 4>(w, k, sc);
     p[3] = rd_pair<B, o + 6>(w, k, sc);
+  } else if constexpr (B == 6) {
+    // pairs 4M .. 4M + 3; pair P < 12 sits in dword P / 2 at offset 6 (P % 2),
+    // pair 12 + m keeps its low four bits in bits 12..15 of dword m and its
+    // top two in bits 12 + 2 (m % 2) .. of dword 4 + m / 2
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int P = 4 * M + i;
+      if (P < 12) {
+        const uint32_t w = rd_dword(u, 6 * Q + P / 2);
+        p[i] = P % 2 ? rd_pair<B, 6>(w, k, sc) : rd_pair<B, 0>(w, k, sc);
+      } else {
+        const uint32_t lo = (rd_dword(u, 6 * Q + i) >> (12 - A)) & (0x000F000Fu << A);
+        p[i] = fma(and_or(rd_dword(u, 6 * Q + 4 + i / 2) >> (12 + 2 * (i & 1) - A - 4), 0x00030003u << (A + 4), lo));
+      }
+    }
   } else {
-    // pairs 4M .. 4M + 3 of the block; pair P < 15 sits in dword P / 5 at
-    // offset 3 (P % 5), pair 15 is bit q of each code in bit 15 / 31 of dword q
+    // 3 and 5 bits: pairs 4M .. 4M + 3 of the block; pair P < 15 sits in dword
+    // P / F at offset B (P % F), pair 15 is bit q of each code in bit 15 / 31
+    // of dword q
+    constexpr int F = B == 3 ? 5 : 3;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int P = 4 * M + i;
       if (P < 15) {
-        const uint32_t w = rd_dword(u, 3 * Q + P / 5);
-        switch (P % 5) {
+        const uint32_t w = rd_dword(u, B * Q + P / F);
+        switch (P % F) {
           case 0: p[i] = rd_pair<B, 0>(w, k, sc); break;
-          case 1: p[i] = rd_pair<B, 3>(w, k, sc); break;
-          case 2: p[i] = rd_pair<B, 6>(w, k, sc); break;
-          case 3: p[i] = rd_pair<B, 9>(w, k, sc); break;
+          case 1: p[i] = rd_pair<B, B>(w, k, sc); break;
+          case 2: p[i] = rd_pair<B, 2 * B>(w, k, sc); break;
+          case 3: p[i] = rd_pair<B, 9>(w, k, sc); break;   // (3 bits only)
           default: p[i] = rd_pair<B, 12>(w, k, sc); break;
         }
       } else {
-        constexpr int A = rd_at<B>();
         constexpr uint32_t b0 = (1u << A) | (1u << (A + 16));
-        uint32_t t = (rd_dword(u, 3 * Q) >> (15 - A)) & b0;
-        t = and_or(rd_dword(u, 3 * Q + 1) >> (14 - A), b0 << 1, t);
-        t = and_or(rd_dword(u, 3 * Q + 2) >> (13 - A), b0 << 2, t);
-        p[i] = __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(__builtin_bit_cast(half2_t, t), sc.D, sc.C));
+        uint32_t v = (rd_dword(u, B * Q) >> (15 - A)) & b0;
+#pragma unroll
+        for (int q = 1; q < B; ++q) v = and_or(rd_dword(u, B * Q + q) >> (15 - A - q), b0 << q, v);
+        p[i] = fma(v);
       }
     }
   }
@@ -967,7 +996,7 @@ __device__ __forceinline__ void rd_kloop(const MOEQ_GLOBAL u32x4* const (&rc)[RD
   auto astore = [&](const u32x4 (&v)[RD_APT], int buf) {
 #pragma unroll
     for (int j = 0; j < rd_apt<NT>(); ++j)
-      *reinterpret_cast<u32x4*>(wdst + buf * RD_SUB + j * (RD_THREADS * 16)) = v[j];
+      *reinterpret_cast<u32x4*>(wdst + buf * (NT * RD_TSUB) + j * (RD_THREADS * 16)) = v[j];
   };
   // chunk j / scale half h of this lane's two units in stage V, every row
   // tile, into one ring slot.  Plain (not streaming) loads: a stage reads 64
@@ -984,17 +1013,14 @@ __device__ __forceinline__ void rd_kloop(const MOEQ_GLOBAL u32x4* const (&rc)[RD
       }
     }
   };
-  // the chunks that sub-stage f of stage V uses first (4 bits: chunk f;
-  // 3 bits: chunk f for f < 3, used again in sub-stage f + 1; 2 bits: chunk
-  // f / 2 for even f, used in f and f + 1)
+  // the chunks that sub-stage f of stage V uses first: those holding dwords
+  // [f B, f B + B) of the unit that no earlier block reaches (a block's last
+  // chunk can serve the next block too, never a later one)
   auto rload_first = [&](RdUnit<B> (&dst)[RD_RT][2], int f, int V) {
-    if constexpr (B == 4) rload_chunk(dst, f, V);
-    if constexpr (B == 3) {
-      if (f < 3) rload_chunk(dst, f, V);
-    }
-    if constexpr (B == 2) {
-      if ((f & 1) == 0) rload_chunk(dst, f >> 1, V);
-    }
+    const int c0 = f == 0 ? 0 : (f * B - 1) / 4 + 1, c1 = (f * B + B - 1) / 4;
+#pragma unroll
+    for (int c = 0; c < B; ++c)
+      if (c >= c0 && c <= c1) rload_chunk(dst, c, V);
   };
   // the scales of this lane's two units of stage V (units 2g and 2g + 1 of
   // the stage, four binary16 scales each: 16 contiguous bytes, as rows hold
@@ -1053,7 +1079,7 @@ __device__ __forceinline__ void rd_kloop(const MOEQ_GLOBAL u32x4* const (&rc)[RD
   do {                                                                                                  \
     if constexpr (ACT) {                                                                                \
       _Pragma("unroll") for (int T = 0; T < NT; ++T) FB[T] =                                            \
-          *reinterpret_cast<const half8*>(lds + (Q) * RD_SUB + T * (32 * 256) + (fbase ^ (16 * (TS))));  \
+          *reinterpret_cast<const half8*>(lds + (Q) * (NT * RD_TSUB) + T * RD_TSUB + (fbase ^ (16 * (TS))));  \
       _Pragma("unroll") for (int r = 0; r < RD_RT; ++r) FA[r] =                                         \
           rd_piece<B, Q, (TS) & 3>(raw[W][r][(TS) >> 2], kc);                                           \
     }                                                                                                   \
@@ -1149,21 +1175,31 @@ __device__ __forceinline__ void rd_kloop(const MOEQ_GLOBAL u32x4* const (&rc)[RD
 #endif
 
 // Width dispatch of one wave's K loop (B is uniform per wave: one tensor).
-template <int NT>
+template <int NT, bool WIDE>
 __device__ __forceinline__ void rd_kloop_any(int bits, bool act, const MOEQ_GLOBAL u32x4* const (&rc)[RD_RT],
                                              const MOEQ_GLOBAL u32x2* const (&rs)[RD_RT], int Uk,
                                              const MOEQ_GLOBAL u32x4* const (&arow)[RD_APT], int su, int sm,
                                              const MOEQ_GLOBAL uint32_t* zero, char* lds, int tid, int lane,
                                              f32x16 (&acc)[RD_RT][NT]) {
   constexpr int AL = MOEQ_RD_AL, WL = MOEQ_RD_WL;
+#define RD_KLOOP(B, ACT) rd_kloop<B, NT, ACT, AL, WL>(rc, rs, Uk, arow, su, sm, zero, lds, tid, lane, acc)
   if (!act)
-    rd_kloop<2, NT, false, AL, WL>(rc, rs, Uk, arow, su, sm, zero, lds, tid, lane, acc);
+    RD_KLOOP(2, false);
   else if (bits == 2)
-    rd_kloop<2, NT, true, AL, WL>(rc, rs, Uk, arow, su, sm, zero, lds, tid, lane, acc);
+    RD_KLOOP(2, true);
   else if (bits == 3)
-    rd_kloop<3, NT, true, AL, WL>(rc, rs, Uk, arow, su, sm, zero, lds, tid, lane, acc);
-  else
-    rd_kloop<4, NT, true, AL, WL>(rc, rs, Uk, arow, su, sm, zero, lds, tid, lane, acc);
+    RD_KLOOP(3, true);
+  else if (!WIDE || bits == 4)
+    RD_KLOOP(4, true);
+  else if constexpr (WIDE) {
+    if (bits == 5)
+      RD_KLOOP(5, true);
+    else if (bits == 6)
+      RD_KLOOP(6, true);
+    else
+      RD_KLOOP(8, true);
+  }
+#undef RD_KLOOP
 }
 
 // Accumulator element v (0..15) of lane l in a 32 x 32 tile: row (weight row)
@@ -1172,7 +1208,7 @@ __device__ __forceinline__ int rd_acc_row(int v, int lane) { return 8 * (v >> 2)
 
 // Gate/up tile: features [f0, f0 + 256) of one slot, tokens [m0, m0 + 64)
 // of its bucket (Mt of them real).  NT token tiles of 32 are multiplied.
-template <int NT>
+template <int NT, bool WIDE>
 __device__ void rd_gateup_tile(const GemmArgs& a, const SlotInfo& sl, int m0, int Mt, int f0, const TensorDev& tg,
                                const TensorDev& tu, char* lds) {
   const int tid = threadIdx.x, lane = tid & 63;
@@ -1210,7 +1246,7 @@ __device__ void rd_gateup_tile(const GemmArgs& a, const SlotInfo& sl, int m0, in
     for (int T = 0; T < NT; ++T)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[r][T][v] = 0.f;
-  rd_kloop_any<NT>(bits, act, rc, rs, Uk, arow, lp >> 2, lp & 3, gptr(a.zeros), lds, tid, lane, acc);
+  rd_kloop_any<NT, WIDE>(bits, act, rc, rs, Uk, arow, lp >> 2, lp & 3, gptr(a.zeros), lds, tid, lane, acc);
 
   // SwiGLU: the up waves hand their accumulators to the gate waves of the
   // same features (the buffers are free after the loop's last barrier)
@@ -1219,7 +1255,7 @@ __device__ void rd_gateup_tile(const GemmArgs& a, const SlotInfo& sl, int m0, in
 #pragma unroll
     for (int r = 0; r < RD_RT; ++r)
 #pragma unroll
-      for (int T = 0; T < NT; ++T) xch[(((wave - HW) * RD_RT + r) * RD_NTMAX + T) * 64 + lane] = acc[r][T];
+      for (int T = 0; T < NT; ++T) xch[(((wave - HW) * RD_RT + r) * NT + T) * 64 + lane] = acc[r][T];
   }
   __syncthreads();
   if (wave >= HW || !act) return;
@@ -1237,7 +1273,7 @@ __device__ void rd_gateup_tile(const GemmArgs& a, const SlotInfo& sl, int m0, in
     float rmax = 0.0f;
 #pragma unroll
     for (int r = 0; r < RD_RT; ++r) {
-      const f32x16 u = xch[((wave * RD_RT + r) * RD_NTMAX + T) * 64 + lane];
+      const f32x16 u = xch[((wave * RD_RT + r) * NT + T) * 64 + lane];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         f32x4 hv;
@@ -1258,7 +1294,7 @@ __device__ void rd_gateup_tile(const GemmArgs& a, const SlotInfo& sl, int m0, in
 // Down tile: output features [n0, n0 + 512) (rows of the down tensor) of one
 // slot, tokens [m0, m0 + 64); results times the routing weight are the
 // slot's partial rows.
-template <int NT>
+template <int NT, bool WIDE>
 __device__ void rd_down_tile(const GemmArgs& a, const SlotInfo& sl, int m0, int Mt, int n0, const TensorDev& td,
                              char* lds) {
   const int tid = threadIdx.x, lane = tid & 63;
@@ -1290,7 +1326,7 @@ __device__ void rd_down_tile(const GemmArgs& a, const SlotInfo& sl, int m0, int 
     for (int T = 0; T < NT; ++T)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[r][T][v] = 0.f;
-  rd_kloop_any<NT>(bits, act, rc, rs, Uk, arow, lp >> 2, lp & 3, gptr(a.zeros), lds, tid, lane, acc);
+  rd_kloop_any<NT, WIDE>(bits, act, rc, rs, Uk, arow, lp >> 2, lp & 3, gptr(a.zeros), lds, tid, lane, acc);
   if (!act) return;
 
   const MOEQ_GLOBAL uint32_t* rowmax = gptr((const uint32_t*)a.rowmax);
@@ -1323,9 +1359,17 @@ __device__ void rd_down_tile(const GemmArgs& a, const SlotInfo& sl, int m0, int 
   }
 }
 
-// grid: tile_grid(max m-tiles, n-tiles); tiles of slots whose gate and up
-// (down) tensors are both 2-4 bits wide
-__global__ __launch_bounds__(RD_THREADS, 1) void gateup_rd_kernel(DecodeArgs a) {
+// The tiles of up to 32 tokens of 2-4-bit tensors have a kernel of their own
+// (SMALL): they are bound by the weights they stream, and with 128 registers
+// and 32 KB of LDS two workgroups share a compute unit, each filling the
+// other's waits (512 tokens, 192 experts of about 21 tokens, 3-bit gate/up:
+// 657 us with one workgroup per compute unit for every tile, 548 + 65 us in two
+// kernels one after the other).  Both kernels walk the same list.
+__device__ __forceinline__ bool rd_small(int Mt, int bits) { return Mt <= 32 && bits <= 4; }
+
+// grid: tile_grid(max m-tiles, n-tiles)
+template <bool SMALL>
+__global__ __launch_bounds__(RD_THREADS, SMALL ? 4 : 1) void gateup_rd_kernel(DecodeArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds_c[];
   const int nN = (a.I + RD_ROWS / 2 - 1) / (RD_ROWS / 2);
   int mt, nt;
@@ -1335,21 +1379,25 @@ __global__ __launch_bounds__(RD_THREADS, 1) void gateup_rd_kernel(DecodeArgs a) 
   const TensorDev tg = a.desc[sl.desc * 3 + 0], tu = a.desc[sl.desc * 3 + 1];
   if (!tg.codes || !tu.codes || !rd_ok(tg) || !rd_ok(tu)) return;
   const int Mt = min(RD_T, sl.M - m0);
+  if (rd_small(Mt, max(tg.bits, tu.bits)) != SMALL) return;
   const GemmArgs g = gemm_args(a);
   const int f0 = nt * (RD_ROWS / 2);
-  if (Mt <= 32)
-    rd_gateup_tile<1>(g, sl, m0, Mt, f0, tg, tu, lds_c);
-  else if (RD_NTMAX == 2 || Mt <= 64)
-    rd_gateup_tile<2>(g, sl, m0, Mt, f0, tg, tu, lds_c);
-  else if constexpr (RD_NTMAX == 4) {
-    if (Mt <= 96)
-      rd_gateup_tile<3>(g, sl, m0, Mt, f0, tg, tu, lds_c);
+  if constexpr (SMALL) {
+    rd_gateup_tile<1, false>(g, sl, m0, Mt, f0, tg, tu, lds_c);
+  } else {
+    if (Mt <= 32)
+      rd_gateup_tile<1, true>(g, sl, m0, Mt, f0, tg, tu, lds_c);
+    else if (Mt <= 64)
+      rd_gateup_tile<2, true>(g, sl, m0, Mt, f0, tg, tu, lds_c);
+    else if (Mt <= 96)
+      rd_gateup_tile<3, true>(g, sl, m0, Mt, f0, tg, tu, lds_c);
     else
-      rd_gateup_tile<4>(g, sl, m0, Mt, f0, tg, tu, lds_c);
+      rd_gateup_tile<4, true>(g, sl, m0, Mt, f0, tg, tu, lds_c);
   }
 }
 
-__global__ __launch_bounds__(RD_THREADS, 1) void down_rd_kernel(DecodeArgs a) {
+template <bool SMALL>
+__global__ __launch_bounds__(RD_THREADS, SMALL ? 4 : 1) void down_rd_kernel(DecodeArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds_c[];
   const int nN = (a.H + RD_ROWS - 1) / RD_ROWS;
   int mt, nt;
@@ -1359,17 +1407,20 @@ __global__ __launch_bounds__(RD_THREADS, 1) void down_rd_kernel(DecodeArgs a) {
   const TensorDev td = a.desc[sl.desc * 3 + 2];
   if (!td.codes || !rd_ok(td)) return;
   const int Mt = min(RD_T, sl.M - m0);
+  if (rd_small(Mt, td.bits) != SMALL) return;
   const GemmArgs g = gemm_args(a);
   const int n0 = nt * RD_ROWS;
-  if (Mt <= 32)
-    rd_down_tile<1>(g, sl, m0, Mt, n0, td, lds_c);
-  else if (RD_NTMAX == 2 || Mt <= 64)
-    rd_down_tile<2>(g, sl, m0, Mt, n0, td, lds_c);
-  else if constexpr (RD_NTMAX == 4) {
-    if (Mt <= 96)
-      rd_down_tile<3>(g, sl, m0, Mt, n0, td, lds_c);
+  if constexpr (SMALL) {
+    rd_down_tile<1, false>(g, sl, m0, Mt, n0, td, lds_c);
+  } else {
+    if (Mt <= 32)
+      rd_down_tile<1, true>(g, sl, m0, Mt, n0, td, lds_c);
+    else if (Mt <= 64)
+      rd_down_tile<2, true>(g, sl, m0, Mt, n0, td, lds_c);
+    else if (Mt <= 96)
+      rd_down_tile<3, true>(g, sl, m0, Mt, n0, td, lds_c);
     else
-      rd_down_tile<4>(g, sl, m0, Mt, n0, td, lds_c);
+      rd_down_tile<4, true>(g, sl, m0, Mt, n0, td, lds_c);
   }
 }
 
@@ -1387,7 +1438,6 @@ __global__ __launch_bounds__(256) void dequant_gemm_kernel(TensorDev t, uint16_t
   const MOEQ_GLOBAL u32x2* rs = row_scales(t.scales, U, r);
   u32x4* o = reinterpret_cast<u32x4*>(out + (size_t)r * t.K + kUnit * u);
   if (rd_ok(t)) {
-    if constexpr (B <= 4) {
     RdUnit<B> un;
 #pragma unroll
     for (int j = 0; j < B; ++j) un.c[j] = rc[(u * B + j) * kRowTile];
@@ -1399,7 +1449,6 @@ __global__ __launch_bounds__(256) void dequant_gemm_kernel(TensorDev t, uint16_t
     DQG(2, 0); DQG(2, 1); DQG(2, 2); DQG(2, 3);
     DQG(3, 0); DQG(3, 1); DQG(3, 2); DQG(3, 3);
 #undef DQG
-    }
   } else {
     __attribute__((aligned(16))) _Float16 blk[32];
 #define DQW(Q)                                                                    \
@@ -1476,8 +1525,8 @@ hipError_t launch_prefill_tiles(const DecodeArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_gateup_prefill(const DecodeArgs& a, hipStream_t s) {
-  hipError_t e = launch_gemm(gateup_rd_kernel, g_attr_gu_rd, RD_THREADS, tile_grid(a.max_rtiles, (a.I + RD_ROWS / 2 - 1) / (RD_ROWS / 2)),
-                             RD_LDS, s, a);
+  hipError_t e = launch_gemm(gateup_rd_kernel<false>, g_attr_gu_rd, RD_THREADS,
+                             tile_grid(a.max_rtiles, (a.I + RD_ROWS / 2 - 1) / (RD_ROWS / 2)), rd_lds(RD_NTMAX), s, a);
   if (e == hipSuccess && a.lds_gateup) {
     const size_t lds = (size_t)2 * (BM + 2 * BN) * LDS_STRIDE * sizeof(_Float16);
     e = launch_gemm(gateup_gemm8_kernel, g_attr_gu_w, 512, tile_grid(a.max_mtiles, a.I / BN), lds, s, a);
@@ -1485,18 +1534,31 @@ hipError_t launch_gateup_prefill(const DecodeArgs& a, hipStream_t s) {
   return e;
 }
 
-hipError_t launch_down_prefill(const DecodeArgs& a, hipStream_t s) {
+hipError_t launch_gateup_prefill_small(const DecodeArgs& a, hipStream_t s) {
+  gateup_rd_kernel<true><<<tile_grid(a.max_rtiles, (a.I + RD_ROWS / 2 - 1) / (RD_ROWS / 2)), RD_THREADS, rd_lds(1),
+                           s>>>(a);
+  return hipGetLastError();
+}
+
+hipError_t launch_h16(const DecodeArgs& a, hipStream_t s) {
   const int rows = a.n * (a.k + a.S);
   h16_kernel<<<(rows + 3) / 4, 256, 0, s>>>(a.h, a.rowmax, rows, a.I, a.h16);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  e = launch_gemm(down_rd_kernel, g_attr_dn_rd, RD_THREADS, tile_grid(a.max_rtiles, (a.H + RD_ROWS - 1) / RD_ROWS),
-                  RD_LDS, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_down_prefill(const DecodeArgs& a, hipStream_t s) {
+  hipError_t e = launch_gemm(down_rd_kernel<false>, g_attr_dn_rd, RD_THREADS,
+                             tile_grid(a.max_rtiles, (a.H + RD_ROWS - 1) / RD_ROWS), rd_lds(RD_NTMAX), s, a);
   if (e == hipSuccess && a.lds_down) {
     const size_t lds = (size_t)2 * (BM + BN) * LDS_STRIDE * sizeof(_Float16);
     e = launch_gemm(down_gemm8_kernel, g_attr_dn_w, 512, tile_grid(a.max_mtiles, a.H / BN), lds, s, a);
   }
   return e;
+}
+
+hipError_t launch_down_prefill_small(const DecodeArgs& a, hipStream_t s) {
+  down_rd_kernel<true><<<tile_grid(a.max_rtiles, (a.H + RD_ROWS - 1) / RD_ROWS), RD_THREADS, rd_lds(1), s>>>(a);
+  return hipGetLastError();
 }
 
 }  // namespace moeq
