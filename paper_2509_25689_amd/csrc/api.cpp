@@ -597,26 +597,20 @@ moeq_status moeq_forward(moeq_layer* L, const void* x, const float* logits, int3
   };
   const bool gemms = prefill || hybrid;
   if (e == hipSuccess && gemms) e = launch_prefill_tiles(a, s);
-  if (self_routed) {
-    if (e == hipSuccess) e = launch_gateup_decode_routing(a, rp1, L->ws, s);
-  } else if (!prefill && n == 1) {
-    if (e == hipSuccess) e = launch_gateup_decode(a, s);
-  } else {
-    // beside each other: the buckets of 2-64 tokens of the decode path and
-    // the small tiles of the grouped GEMMs, and the rest
-    fork();
-    if (e == hipSuccess && gemms) e = launch_gateup_prefill(a, s);
-    if (e == hipSuccess && !prefill) e = launch_gateup_decode_multi(a, L->aux);
-    if (e == hipSuccess && gemms) e = launch_gateup_prefill_small(a, L->aux);
-    if (e == hipSuccess && !prefill) e = launch_gateup_decode_single(a, s);
-    join();
-  }
+  if (gemms) fork();
+  if (e == hipSuccess && gemms) e = launch_gateup_prefill(a, s);
+  if (e == hipSuccess && gemms) e = launch_gateup_prefill_small(a, L->aux);
+  if (e == hipSuccess && !prefill)
+    e = self_routed ? launch_gateup_decode_routing(a, rp1, L->ws, s) : launch_gateup_decode(a, s);
+  if (e == hipSuccess && !prefill) e = launch_wide_gateup(a, s);
+  if (gemms) join();
   mark(2);
   if (e == hipSuccess && gemms) e = launch_h16(a, s);
   if (gemms) fork();
   if (e == hipSuccess && gemms) e = launch_down_prefill(a, s);
   if (e == hipSuccess && gemms) e = launch_down_prefill_small(a, L->aux);
   if (e == hipSuccess && !prefill) e = launch_down_decode(a, s);
+  if (e == hipSuccess && !prefill) e = launch_wide_down(a, s);
   if (gemms) join();
   mark(3);
   if (e == hipSuccess && (prefill || !down_combines(a))) e = launch_combine(a, s);

@@ -147,11 +147,16 @@ __device__ __forceinline__ float block_dot_sub(const uint32_t (&p)[16], const ui
   return fmaf(ds * xf.y, fmaf(-zs, xf.x, dot), acc_out);
 }
 
+// A block's prescale exponent from its largest magnitude am: am * 2^-e lies in
+// [2^14, 2^15); e >= -100 keeps 2^-e finite for an all-zero block.
+__device__ __forceinline__ int block_exp(float am) {
+  return max((int)((__float_as_uint(am) >> 23) & 0xFFu) - 141, -100);
+}
+
 // One thread's 16-byte piece (8 values) of a block of 32, whose four pieces
 // are held by four consecutive threads of one wave (all active): binary16
-// after the block's power-of-two prescale 2^-e, e from the block's largest
-// magnitude so that it lands in [2^14, 2^15) (no overflow, 11 significant
-// bits at any scale; e >= -100 keeps 2^-e finite for an all-zero block).
+// after the block's power-of-two prescale 2^-e (no overflow, 11 significant
+// bits at any scale).
 // The piece goes to dst; the block's first thread (first) writes
 // (X, 2^e) to *xf, X the sum of the staged values.
 __device__ __forceinline__ void stage_piece(const float (&f)[8], uint32_t* dst, float2* xf, bool first) {
@@ -160,7 +165,7 @@ __device__ __forceinline__ void stage_piece(const float (&f)[8], uint32_t* dst, 
   for (int i = 0; i < 8; ++i) am = fmaxf(am, fabsf(f[i]));
   am = fmaxf(am, __shfl_xor(am, 1, 64));
   am = fmaxf(am, __shfl_xor(am, 2, 64));
-  const int e = max((int)((__float_as_uint(am) >> 23) & 0xFFu) - 141, -100);
+  const int e = block_exp(am);
   const float sc = __builtin_amdgcn_ldexpf(1.0f, -e);
   uint32_t hv[4];
   float sum = 0.0f;
@@ -185,6 +190,14 @@ __device__ __forceinline__ void bf16x8_to_f32(const u32x4 v, float (&f)[8]) {
 template <int CTRL, int ROW_MASK = 0xF>
 __device__ __forceinline__ float dpp_f(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROW_MASK, 0xF, false));
+}
+
+// sum over 8 lanes (half a DPP row); every lane holds it
+__device__ __forceinline__ float half_sum8(float v) {
+  v += dpp_f<0xB1>(v);   // quad_perm [1,0,3,2]
+  v += dpp_f<0x4E>(v);   // quad_perm [2,3,0,1]
+  v += dpp_f<0x141>(v);  // row_half_mirror: the other quad of the half row
+  return v;
 }
 
 // Sum over the lanes l % R of a wave (R = 8, 16, 32 or 64), in a fixed order;
@@ -267,12 +280,10 @@ __device__ __forceinline__ void row_dots(const RowPtr& r, int U, int u0, int ste
 
 // ---------------------------------------------------------------------------
 // Down x routing weight, one partial row per (token, slot).  A workgroup owns
-// 128 rows of one slot, a wave 32 of them with two units per step.
-constexpr int kDownTokens = 4;  // staged per pass
-
-template <int B>
+// 4 R rows of one slot, a wave R of them with 64 / R units per step; TM tokens
+// are staged per pass.
+template <int B, int TM, int R>
 __device__ __forceinline__ void down_body(const DecodeArgs& a, const Slot sl, const TensorDev& td, uint32_t* smem) {
-  constexpr int TM = kDownTokens, R = 32;
   const int H = a.H, I = a.I, U = I / kUnit;
   const int xts = U * kXStride, sts = U * 4;  // per-token LDS strides (dwords, float2)
   uint32_t* xl = smem;
@@ -320,7 +331,8 @@ __device__ __forceinline__ void down_body(const DecodeArgs& a, const Slot sl, co
   }
 }
 
-// grid = (H / 128, S + max_active), 256 threads
+// grid = (H / (4 R), S + max_active), 256 threads
+template <int TM, int R>
 __global__ __launch_bounds__(256, 4) void down_kernel(DecodeArgs a) {
   extern __shared__ uint32_t smem[];
   const Slot sl = slot_info(a, blockIdx.y);
@@ -328,9 +340,9 @@ __global__ __launch_bounds__(256, 4) void down_kernel(DecodeArgs a) {
   const TensorDev td = a.desc[sl.desc * 3 + 2];
   if (!td.codes) return;
   switch (td.bits) {
-    case 2: down_body<2>(a, sl, td, smem); break;
-    case 3: down_body<3>(a, sl, td, smem); break;
-    case 4: down_body<4>(a, sl, td, smem); break;
+    case 2: down_body<2, TM, R>(a, sl, td, smem); break;
+    case 3: down_body<3, TM, R>(a, sl, td, smem); break;
+    case 4: down_body<4, TM, R>(a, sl, td, smem); break;
     default: break;
   }
 }
@@ -341,14 +353,14 @@ __global__ __launch_bounds__(256, 4) void down_kernel(DecodeArgs a) {
 // width BD, or (BD = 0) widths that differ between tensors, where every
 // unit is fetched as four chunk loads, those past the slot's width from 16
 // zero bytes that stay in the vector cache, and the slot's width picks the
-// decoder.  A workgroup of NT threads owns R = NT / 16 rows of y across every
-// slot (the token's k choices in choice order, then the shared experts): lane
-// l of wave w holds row l % R and unit w * 64 / R + l / R of it in every slot,
-// with D slots' codes in flight.  The lane accumulates w_j * (its partial dot
-// of slot j) in slot order and the 16 lanes of a row are summed in a fixed
-// order: no partial rows, no combine launch.  All h rows are staged once per
-// workgroup (binary16 with per-block prescales, as in the down kernel), their
-// loads issued in batches so a batch costs one memory round trip.
+// decoder.  A workgroup of 512 threads owns 32 rows of y across every slot
+// (the token's k choices in choice order, then the shared experts): lane l of
+// wave w holds row l % 32 and unit 2 w + l / 32 of it in every slot, with D
+// slots' codes in flight.  A wave stages its own two units of every h row
+// (binary16 with per-block prescales, as in the down kernel), so no barrier
+// parts the staging from the products.  The lane accumulates w_j * (its partial
+// dot of slot j) in slot order and the 16 lanes of a row are summed in a fixed
+// order: no partial rows, no combine launch.
 struct DownSlot {
   const uint32_t* codes;
   const uint16_t* scales;
@@ -365,18 +377,15 @@ __device__ __forceinline__ float down1_unit_dot(const uint32_t* w, u32x2 sc, con
   return o[0];
 }
 
-constexpr int kDown1Batch = 6;  // staged 32-byte pieces per thread per round trip
+constexpr int kDown1Batch = 12;  // slots whose h a wave requests together
 
-template <int BD, int NT, int D>
-__global__ __launch_bounds__(NT) void down1_kernel(DecodeArgs a) {
+template <int BD, int D>
+__global__ __launch_bounds__(512) void down1_kernel(DecodeArgs a) {
   extern __shared__ uint32_t smem[];
   __shared__ DownSlot slots[kMaxTopK + kMaxShared];
-  constexpr int R = NT / 16, NW = NT / 64;
+  constexpr int R = 32, NW = 8;
   __shared__ float red[NW][R];
   const int H = a.H, I = a.I, U = I / kUnit, k = a.k, NS = a.k + a.S;
-  const int xts = U * kXStride, sts = U * 4;
-  uint32_t* xl = smem;
-  float2* xs = reinterpret_cast<float2*>(smem + NS * xts);
   if ((int)threadIdx.x < NS) {
     const int j = threadIdx.x;
     DownSlot v;
@@ -402,10 +411,12 @@ __global__ __launch_bounds__(NT) void down1_kernel(DecodeArgs a) {
   __syncthreads();
 
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int u = wave * (64 / R) + lane / R;
+  const int u = 2 * wave + lane / R;
   const int row = blockIdx.x * R + lane % R;  // (H is a multiple of 128)
   const int uc = min(u, U - 1);
   constexpr int BL = BD == 0 ? 4 : BD;  // chunks loaded per unit
+  // (one width: the unit's place is the same in every slot)
+  const size_t c_at = chunk_index(BL, U, row) + uc * BL * kRowTile, s_at = scale_index(U, row) + scale_step(uc);
   auto load_slot = [&](UnitBuf<BL>& b, int j) {
     const DownSlot& sl = slots[min(j, NS - 1)];
     if constexpr (BD == 0) {
@@ -421,51 +432,55 @@ __global__ __launch_bounds__(NT) void down1_kernel(DecodeArgs a) {
         b.w[4 * c + 3] = v.w;
       }
     } else {
-      load_unit<BD>(row_chunks(sl.codes, BD, U, row), uc, b.w);
+      load_unit<BD>(gptr(reinterpret_cast<const u32x4*>(sl.codes)) + c_at, 0, b.w);
     }
-    b.s = row_scales(sl.scales, U, row)[scale_step(uc)];
+    b.s = gptr(reinterpret_cast<const u32x2*>(sl.scales))[s_at];
   };
   UnitBuf<BL> buf[D];
 #pragma unroll
   for (int i = 0; i < D - 1; ++i) load_slot(buf[i], i);
 
-  // stage every slot's h row: piece p (8 values) of slot p / (I / 8); a
-  // batch's loads all go out before its first piece is converted
-  const int PPS = I / 8, NP = NS * PPS;
-  for (int p0 = 0; p0 < NP; p0 += NT * kDown1Batch) {
-    f32x4 v[kDown1Batch][2];
+  // This wave's two units of every slot's h row: lane l converts values 4 l ..
+  // of them, a block of 32 in 8 lanes.  (a unit past the row repeats the last
+  // one; waves past the row stage nothing and add zeros)
+  constexpr int kHs = 2 * kXStride;  // dwords per slot and wave
+  const int nw = (U + 1) / 2;        // waves with units
+  uint32_t* xl = smem + wave * NS * kHs;
+  float2* xs = reinterpret_cast<float2*>(smem + nw * NS * kHs) + wave * NS * 8;
+  if (wave < nw) {
+    const int hu = lane >> 5, at = min(2 * wave + hu, U - 1) * kUnit + 4 * (lane & 31);
+    for (int j0 = 0; j0 < NS; j0 += kDown1Batch) {
+      f32x4 v[kDown1Batch];
 #pragma unroll
-    for (int i = 0; i < kDown1Batch; ++i) {
-      if (p0 + i * NT < NP) {
-        // pieces past the end repeat the last block's (same values, same place)
-        int p = p0 + i * NT + (int)threadIdx.x;
-        p = p < NP ? p : NP - 4 + (p & 3);
-        const MOEQ_GLOBAL f32x4* src =
-            gptr(reinterpret_cast<const f32x4*>(a.h + (size_t)slots[p / PPS].hrow * I)) + 2 * (p % PPS);
-        v[i][0] = src[0];
-        v[i][1] = src[1];
-      }
-    }
+      for (int i = 0; i < kDown1Batch; ++i)
+        v[i] = *gptr(reinterpret_cast<const f32x4*>(a.h + (size_t)slots[min(j0 + i, NS - 1)].hrow * I + at));
 #pragma unroll
-    for (int i = 0; i < kDown1Batch; ++i) {
-      if (p0 + i * NT < NP) {
-        int p = p0 + i * NT + (int)threadIdx.x;
-        p = p < NP ? p : NP - 4 + (p & 3);
-        const int m = p / PPS, c = p % PPS;
-        const float f[8] = {v[i][0].x, v[i][0].y, v[i][0].z, v[i][0].w,
-                            v[i][1].x, v[i][1].y, v[i][1].z, v[i][1].w};
-        const int uu = c >> 4, cq = c & 15;
-        stage_piece(f, xl + m * xts + uu * kXStride + cq * 4, xs + m * sts + uu * 4 + (cq >> 2), (cq & 3) == 0);
+      for (int i = 0; i < kDown1Batch; ++i) {
+        if (j0 + i < NS) {
+          float am = fmaxf(fmaxf(fabsf(v[i].x), fabsf(v[i].y)), fmaxf(fabsf(v[i].z), fabsf(v[i].w)));
+          am = fmaxf(am, dpp_f<0xB1>(am));   // quad_perm [1,0,3,2]
+          am = fmaxf(am, dpp_f<0x4E>(am));   // quad_perm [2,3,0,1]
+          am = fmaxf(am, dpp_f<0x141>(am));  // row_half_mirror: the other quad of the 8 lanes
+          const int e = block_exp(am);
+          const float sc = __builtin_amdgcn_ldexpf(1.0f, -e);
+          const _Float16 h0 = (_Float16)(v[i].x * sc), h1 = (_Float16)(v[i].y * sc), h2 = (_Float16)(v[i].z * sc),
+                         h3 = (_Float16)(v[i].w * sc);
+          const float sum = half_sum8(((float)h0 + (float)h1) + ((float)h2 + (float)h3));
+          *reinterpret_cast<u32x2*>(xl + (j0 + i) * kHs + hu * kXStride + (lane & 31) * 2) =
+              u32x2{(uint32_t)__builtin_bit_cast(uint16_t, h0) | (uint32_t)__builtin_bit_cast(uint16_t, h1) << 16,
+                    (uint32_t)__builtin_bit_cast(uint16_t, h2) | (uint32_t)__builtin_bit_cast(uint16_t, h3) << 16};
+          if ((lane & 7) == 0) xs[(j0 + i) * 8 + (lane >> 3)] = make_float2(sum, __builtin_amdgcn_ldexpf(1.0f, e));
+        }
       }
     }
   }
-  __syncthreads();
+  wave_sync();  // (the wave reads only what it wrote)
 
-  const uint32_t* xu = xl + uc * kXStride;
-  const float2* su4 = xs + uc * 4;
+  const uint32_t* xu = xl + (lane / R) * kXStride;
+  const float2* su4 = xs + (lane / R) * 4;
   float acc = 0.0f;
 #pragma unroll 1
-  for (int j0 = 0; j0 < NS; j0 += D) {
+  for (int j0 = 0; j0 < (wave < nw ? NS : 0); j0 += D) {
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int b = 0; b < D; ++b) {
@@ -476,12 +491,12 @@ __global__ __launch_bounds__(NT) void down1_kernel(DecodeArgs a) {
         float o;
         if constexpr (BD == 0) {
           switch (__builtin_amdgcn_readfirstlane(slots[j].bits)) {
-            case 2: o = down1_unit_dot<2>(buf[b].w, buf[b].s, xu + j * xts, su4 + j * sts); break;
-            case 3: o = down1_unit_dot<3>(buf[b].w, buf[b].s, xu + j * xts, su4 + j * sts); break;
-            default: o = down1_unit_dot<4>(buf[b].w, buf[b].s, xu + j * xts, su4 + j * sts); break;
+            case 2: o = down1_unit_dot<2>(buf[b].w, buf[b].s, xu + j * kHs, su4 + j * 8); break;
+            case 3: o = down1_unit_dot<3>(buf[b].w, buf[b].s, xu + j * kHs, su4 + j * 8); break;
+            default: o = down1_unit_dot<4>(buf[b].w, buf[b].s, xu + j * kHs, su4 + j * 8); break;
           }
         } else {
-          o = down1_unit_dot<BD>(buf[b].w, buf[b].s, xu + j * xts, su4 + j * sts);
+          o = down1_unit_dot<BD>(buf[b].w, buf[b].s, xu + j * kHs, su4 + j * 8);
         }
         acc = fmaf(slots[j].w, u < U ? o : 0.0f, acc);
       }
@@ -530,61 +545,49 @@ __global__ __launch_bounds__(256) void combine_kernel(DecodeArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Gate/up + SwiGLU.  A workgroup of kGuWaves waves owns kGuRows features of one
-// slot: the first half of the waves takes their gate rows, the other half
-// their up rows (a wave decodes one width), each wave kGuRows rows at 64 /
-// kGuRows units per step, the units of a row dealt to the waves of its tensor.
-// The partial sums meet in LDS in wave order.
-#ifndef MOEQ_GU_WAVES
-#define MOEQ_GU_WAVES 4
-#endif
-#ifndef MOEQ_GU_ROWS
-#define MOEQ_GU_ROWS 16
-#endif
-#ifndef MOEQ_GU_OCC
-#define MOEQ_GU_OCC 5
-#endif
-constexpr int kGuWaves = MOEQ_GU_WAVES, kGuRows = MOEQ_GU_ROWS, kGuThreads = 64 * kGuWaves;
-constexpr int kGuHalf = kGuWaves / 2;  // waves per tensor
-static_assert(128 % kGuRows == 0, "a workgroup's features are all in or all out");
+// Gate/up + SwiGLU.  A workgroup of four waves owns R features of one slot: two
+// waves take their gate rows, two their up rows (a wave decodes one width),
+// each wave R rows at 64 / R units per step, the units of a row dealt to the
+// two waves of its tensor.  The partial sums meet in LDS in wave order.
+// One token: R = 16, so that the nine slots of the benchmark's layer make 1152
+// workgroups, all resident at once (R = 32: 27.4 instead of 26.4 us; eight
+// waves of 32 rows: 29.6).  More tokens: R = 32, which halves the staging of
+// x per weight (16 tokens: 297 -> 270 us beside the one-token buckets).
+constexpr int kGuWaves = 4, kGuThreads = 64 * kGuWaves, kGuHalf = kGuWaves / 2;
+constexpr int kGuRows1 = 16, kGuRowsN = 32;
 
 struct GateUpShared {
-  float red[kGuWaves][4][kGuRows];
-};
-
-template <int TM>
-struct Dots {
-  float v[TM];
+  float red[kGuWaves][2][32];
 };
 
 // this lane's share of its row (of the tensor its wave takes); the first
 // unit is requested before `stage` brings the tokens into LDS
-template <int B, int TM, typename F>
+template <int B, int TM, int R, typename F>
 __device__ __forceinline__ void gateup_dots(const TensorDev& t, int row, int U, int u0, const uint32_t* xl,
                                             const float2* xs, int xts, int sts, int mc, F stage, float (&acc)[TM]) {
   const RowPtr rp = row_ptr(t, B, U, row);
   UnitBuf<B> first;
   load_unit_buf<B>(first, rp, min(u0, U - 1));
   stage();
-  row_dots<B, TM>(rp, U, u0, kGuHalf * (64 / kGuRows), xl, xs, xts, sts, mc, first, acc);
+  row_dots<B, TM>(rp, U, u0, kGuHalf * (64 / R), xl, xs, xts, sts, mc, first, acc);
 }
 
-// features [f0, f0 + kGuRows) of one slot for mc <= TM tokens, which `stage`
+// features [f0, f0 + R) of one slot for mc <= TM tokens, which `stage`
 // brings into LDS (with a barrier at its end); h rows hrow .. hrow + mc - 1
-template <int TM, typename F>
+template <int TM, int R, typename F>
 __device__ __forceinline__ void gateup_rows(const DecodeArgs& a, const TensorDev& tg, const TensorDev& tu, int f0,
                                             int hrow, int mc, const uint32_t* xl, const float2* xs, int xts, int sts,
                                             GateUpShared& sh, F stage) {
-  constexpr int R = kGuRows;
+  static_assert(128 % R == 0 && R <= 32 && TM <= 2, "whole workgroups, and their sums fit");
   const int H = a.H, I = a.I, U = H / kUnit;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const TensorDev& t = wave < kGuHalf ? tg : tu;
   const int row = f0 + lane % R, u0 = (wave % kGuHalf) * (64 / R) + lane / R;
   float acc[TM];
   switch (__builtin_amdgcn_readfirstlane(t.bits)) {
-    case 2: gateup_dots<2, TM>(t, row, U, u0, xl, xs, xts, sts, mc, stage, acc); break;
-    case 3: gateup_dots<3, TM>(t, row, U, u0, xl, xs, xts, sts, mc, stage, acc); break;
-    default: gateup_dots<4, TM>(t, row, U, u0, xl, xs, xts, sts, mc, stage, acc); break;
+    case 2: gateup_dots<2, TM, R>(t, row, U, u0, xl, xs, xts, sts, mc, stage, acc); break;
+    case 3: gateup_dots<3, TM, R>(t, row, U, u0, xl, xs, xts, sts, mc, stage, acc); break;
+    default: gateup_dots<4, TM, R>(t, row, U, u0, xl, xs, xts, sts, mc, stage, acc); break;
   }
 #pragma unroll
   for (int m = 0; m < TM; ++m) {
@@ -604,13 +607,9 @@ __device__ __forceinline__ void gateup_rows(const DecodeArgs& a, const TensorDev
   }
 }
 
-// the token's x into LDS in binary16 with per-block prescales (16-byte
-// pieces, 4 per block)
-__device__ __forceinline__ void stage_x1(const DecodeArgs& a, const Slot sl, uint32_t* xl, float2* xs) {
+// token t's x into LDS at xl / xs (binary16 with per-block prescales)
+__device__ __forceinline__ void stage_x_token(const DecodeArgs& a, int t, uint32_t* xl, float2* xs) {
   const int H = a.H;
-  // (one token: token 0, without reading the bucket permutation, which the
-  // routing workgroup of gateup1_route_kernel may still be writing)
-  const int t = sl.shared >= 0 || a.n == 1 ? 0 : a.perm[sl.base] / a.k;
   const MOEQ_GLOBAL u32x4* src = gptr(reinterpret_cast<const u32x4*>(a.x + (size_t)t * H));
   for (int q = threadIdx.x; q < H / 8; q += kGuThreads) {
     float f[8];
@@ -640,26 +639,20 @@ __device__ __forceinline__ bool narrow_gateup(const TensorDev& tg, const TensorD
 
 // one workgroup's share of the gate/up of a bucket of one token (STAGED: x is
 // in LDS already)
-template <bool STAGED = false>
+template <int R, bool STAGED>
 __device__ __forceinline__ void gateup1_slot(const DecodeArgs& a, const Slot& sl, uint32_t* smem, GateUpShared& sh) {
-  if (sl.M != 1) return;  // the buckets of one token, of any batch
   const TensorDev tg = a.desc[sl.desc * 3 + 0], tu = a.desc[sl.desc * 3 + 1];
   if (!narrow_gateup(tg, tu)) return;
   uint32_t* xl = smem;
   float2* xs = reinterpret_cast<float2*>(smem + a.H / kUnit * kXStride);
-  gateup_rows<1>(a, tg, tu, blockIdx.x * kGuRows, sl.base, 1, xl, xs, 0, 0, sh, [&] {
+  gateup_rows<1, R>(a, tg, tu, blockIdx.x * R, sl.base, 1, xl, xs, 0, 0, sh, [&] {
     if constexpr (!STAGED) {
-      stage_x1(a, sl, xl, xs);
+      // (one token: token 0, without reading the bucket permutation, which the
+      // routing workgroup of gateup1_route_kernel may still be writing)
+      stage_x_token(a, sl.shared >= 0 || a.n == 1 ? 0 : a.perm[sl.base] / a.k, xl, xs);
       __syncthreads();
     }
   });
-}
-
-// grid = (I / kGuRows, S + max_active), kGuThreads threads; the buckets of one token
-__global__ __launch_bounds__(kGuThreads, MOEQ_GU_OCC) void gateup1_kernel(DecodeArgs a) {
-  extern __shared__ uint32_t smem[];
-  __shared__ GateUpShared sh;
-  gateup1_slot(a, slot_info(a, blockIdx.y), smem, sh);
 }
 
 // The same for a forward of one token that needs no routing launch: wave 0
@@ -671,9 +664,9 @@ __global__ __launch_bounds__(kGuThreads, MOEQ_GU_OCC) void gateup1_kernel(Decode
 // them.  Workgroup (0, S) also writes what the routing launch would have:
 // idx and w in choice order, offsets, the active list and the permutation,
 // which the down kernel and any 5/6/8-bit gate/up kernel read after this
-// launch.  grid = (I / kGuRows, S + k), kGuThreads threads.
+// launch.  grid = (I / kGuRows1, S + k), kGuThreads threads.
 template <int EPL>
-__global__ __launch_bounds__(kGuThreads, MOEQ_GU_OCC) void gateup1_route_kernel(DecodeArgs a, RouterParams rp,
+__global__ __launch_bounds__(kGuThreads, 5) void gateup1_route_kernel(DecodeArgs a, RouterParams rp,
                                                                                 Workspace ws) {
   extern __shared__ uint32_t smem[];
   __shared__ GateUpShared sh;
@@ -722,36 +715,28 @@ __global__ __launch_bounds__(kGuThreads, MOEQ_GU_OCC) void gateup1_route_kernel(
     sl.base = i;
     sl.M = 1;
     sl.shared = -1;
-    gateup1_slot<true>(a, sl, smem, sh);
+    gateup1_slot<kGuRows1, true>(a, sl, smem, sh);
     return;
   }
-  gateup1_slot(a, sl, smem, sh);
+  gateup1_slot<kGuRows1, false>(a, sl, smem, sh);
 }
 
 // ---------------------------------------------------------------------------
-// Buckets of 2 or more tokens, in the one-token kernel's layout, TM tokens
-// staged per pass: each unit's code pairs are unpacked once and multiplied
-// with every staged token.
-
-// token t's x into LDS at xl / xs (binary16 with per-block prescales)
-__device__ __forceinline__ void stage_x_token(const DecodeArgs& a, int t, uint32_t* xl, float2* xs) {
-  const int H = a.H;
-  const MOEQ_GLOBAL u32x4* src = gptr(reinterpret_cast<const u32x4*>(a.x + (size_t)t * H));
-  for (int q = threadIdx.x; q < H / 8; q += kGuThreads) {
-    float f[8];
-    bf16x8_to_f32(src[q], f);
-    const int uu = q >> 4, cq = q & 15;
-    stage_piece(f, xl + uu * kXStride + cq * 4, xs + uu * 4 + (cq >> 2), (cq & 3) == 0);
-  }
-}
-
-// grid = (I / kGuRows, S + max_active), kGuThreads threads; buckets of 2 .. gemm_above tokens
+// The buckets of 1 .. gemm_above tokens, TM tokens staged per pass: each unit's
+// code pairs are unpacked once and multiplied with every staged token.  One
+// launch: two, the larger buckets' on a second stream, cost as much at 16
+// tokens (the streams' events take about 20 us each way) and more below.
+// grid = (I / kGuRowsN, S + max_active), kGuThreads threads
 template <int TM>
 __global__ __launch_bounds__(kGuThreads, TM <= 2 ? 4 : 2) void gateupn_kernel(DecodeArgs a) {
   extern __shared__ uint32_t smem[];
   __shared__ GateUpShared sh;
   const Slot sl = slot_info(a, blockIdx.y);
-  if (sl.M < 2 || sl.M > a.gemm_above) return;
+  if (sl.M < 1 || sl.M > a.gemm_above) return;
+  if (sl.M == 1) {
+    gateup1_slot<kGuRowsN, false>(a, sl, smem, sh);
+    return;
+  }
   const TensorDev tg = a.desc[sl.desc * 3 + 0], tu = a.desc[sl.desc * 3 + 1];
   if (!narrow_gateup(tg, tu)) return;
   const int U = a.H / kUnit, xts = U * kXStride, sts = U * 4;  // per-token LDS strides (dwords, float2)
@@ -761,7 +746,7 @@ __global__ __launch_bounds__(kGuThreads, TM <= 2 ? 4 : 2) void gateupn_kernel(De
     const int mc = min(TM, sl.M - m0);
     // (the previous pass's last barrier came after its reads of x; its sums
     // are read before the barrier that ends the staging)
-    gateup_rows<TM>(a, tg, tu, blockIdx.x * kGuRows, sl.base + m0, mc, xl, xs, xts, sts, sh, [&] {
+    gateup_rows<TM, kGuRowsN>(a, tg, tu, blockIdx.x * kGuRowsN, sl.base + m0, mc, xl, xs, xts, sts, sh, [&] {
       for (int m = 0; m < mc; ++m) {
         const int t = sl.shared >= 0 ? m0 + m : a.perm[sl.base + m0 + m] / a.k;
         stage_x_token(a, t, xl + m * xts, xs + m * sts);
@@ -774,12 +759,12 @@ __global__ __launch_bounds__(kGuThreads, TM <= 2 ? 4 : 2) void gateupn_kernel(De
 // ---------------------------------------------------------------------------
 // Wide tensors (5, 6 and 8 bits).  The kernels above skip a slot whose gate or
 // up (down) tensor is wide; these take exactly those slots.  A workgroup of
-// NW waves owns 16 rows of the tensor, a wave 4 units of each per step, the
-// units of a row dealt to the waves, for up to TM tokens per pass (1 for a
+// NW waves owns R rows of the tensor, a wave 64 / R units of each per step,
+// the units of a row dealt to the waves, for up to TM tokens per pass (1 for a
 // single token, else 4).  Gate, up and down are reduced one tensor at a time,
 // so a wave decodes one width at a time.  Few slots (shared experts only)
-// take more waves, so that the grid still covers the chip.
-constexpr int kWideRows = 16;
+// take 16 rows and, in gate/up, eight waves, so that the grid still covers the
+// chip; many take 32 rows, which halves the staging.
 __device__ __forceinline__ bool wide_bits(int b) { return b > 4; }
 
 // acc[m] += d * sum (c - z) x_m over one unit, for the mc staged tokens
@@ -872,24 +857,24 @@ __device__ __forceinline__ WideAcc<TM> wide_row_dot_any(const TensorDev& t, int 
 
 // The row totals of a workgroup's waves: red[tensor][wave][token][row], summed
 // over the waves in order by the threads that store them.
-template <int TM, int NW>
-__device__ __forceinline__ void wide_put(const WideAcc<TM>& v, float (*red)[TM][kWideRows], int wave, int lane) {
+template <int TM, int R>
+__device__ __forceinline__ void wide_put(const WideAcc<TM>& v, float (*red)[TM][R], int wave, int lane) {
 #pragma unroll
   for (int m = 0; m < TM; ++m) {
-    const float s = row_sum<kWideRows>(v.v[m]);
-    if (lane < kWideRows) red[wave][m][lane] = s;
+    const float s = row_sum<R>(v.v[m]);
+    if (lane < R) red[wave][m][lane] = s;
   }
 }
-template <int TM, int NW>
-__device__ __forceinline__ float wide_total(float (*red)[TM][kWideRows], int m, int r) {
+template <int TM, int NW, int R>
+__device__ __forceinline__ float wide_total(float (*red)[TM][R], int m, int r) {
   float s = red[0][m][r];
 #pragma unroll
   for (int w = 1; w < NW; ++w) s += red[w][m][r];
   return s;
 }
 
-// grid = (I / kWideRows, slots), 64 * NW threads
-template <int TM, int NW>
+// grid = (I / R, slots), 64 * NW threads
+template <int TM, int NW, int R>
 __global__ __launch_bounds__(64 * NW) void wide_gateup_kernel(DecodeArgs a) {
   const Slot sl = slot_info(a, blockIdx.y);
   if (sl.M < 0 || sl.M > a.gemm_above) return;  // (large buckets: the grouped GEMMs)
@@ -901,9 +886,9 @@ __global__ __launch_bounds__(64 * NW) void wide_gateup_kernel(DecodeArgs a) {
   uint32_t* xl = wide_lds;
   float* xs = reinterpret_cast<float*>(wide_lds + TM * xts);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  constexpr int ULANES = 64 / kWideRows;  // units of a row per wave and step
-  __shared__ float red[2][NW][TM][kWideRows];
-  const int row = blockIdx.x * kWideRows + lane % kWideRows, j = wave * ULANES + lane / kWideRows;
+  constexpr int ULANES = 64 / R;  // units of a row per wave and step
+  __shared__ float red[2][NW][TM][R];
+  const int row = blockIdx.x * R + lane % R, j = wave * ULANES + lane / R;
   for (int m0 = 0; m0 < sl.M; m0 += TM) {
     const int mc = min(TM, sl.M - m0);
     __syncthreads();
@@ -923,19 +908,26 @@ __global__ __launch_bounds__(64 * NW) void wide_gateup_kernel(DecodeArgs a) {
       }
     }
     __syncthreads();
-    wide_put<TM, NW>(wide_row_dot_any<1, TM>(tg, row, U, j, NW * ULANES, xts, 0, sts, mc), red[0], wave, lane);
-    wide_put<TM, NW>(wide_row_dot_any<1, TM>(tu, row, U, j, NW * ULANES, xts, 0, sts, mc), red[1], wave, lane);
+    wide_put<TM, R>(wide_row_dot_any<1, TM>(tg, row, U, j, NW * ULANES, xts, 0, sts, mc), red[0], wave, lane);
+    wide_put<TM, R>(wide_row_dot_any<1, TM>(tu, row, U, j, NW * ULANES, xts, 0, sts, mc), red[1], wave, lane);
     __syncthreads();
-    for (int i = threadIdx.x; i < kWideRows * mc; i += 64 * NW) {
-      const int m = i / kWideRows, r = i % kWideRows;
-      a.h[(size_t)(sl.base + m0 + m) * I + blockIdx.x * kWideRows + r] =
-          silu(wide_total<TM, NW>(red[0], m, r)) * wide_total<TM, NW>(red[1], m, r);
+    for (int i = threadIdx.x; i < R * mc; i += 64 * NW) {
+      const int m = i / R, r = i % R;
+      a.h[(size_t)(sl.base + m0 + m) * I + blockIdx.x * R + r] =
+          silu(wide_total<TM, NW, R>(red[0], m, r)) * wide_total<TM, NW, R>(red[1], m, r);
     }
   }
 }
 
-// grid = (H / kWideRows, slots), 64 * NW threads
-template <int TM, int NW>
+// One token and one shared expert, whose down tensor alone is wide: the kernel
+// adds the routed experts' partial rows (written by the launch before it) in
+// slot order and writes y, which saves the combine launch.
+__host__ __device__ __forceinline__ bool wide_down_combines(const DecodeArgs& a) {
+  return a.n == 1 && a.wide_down == 1 && a.S == 1;
+}
+
+// grid = (H / R, slots), 64 * NW threads
+template <int TM, int NW, int R>
 __global__ __launch_bounds__(64 * NW) void wide_down_kernel(DecodeArgs a) {
   const Slot sl = slot_info(a, blockIdx.y);
   if (sl.M < 0 || sl.M > a.gemm_above) return;  // (large buckets: the grouped GEMMs)
@@ -946,9 +938,14 @@ __global__ __launch_bounds__(64 * NW) void wide_down_kernel(DecodeArgs a) {
   uint32_t* xl = wide_lds;
   float* xs = reinterpret_cast<float*>(wide_lds + TM * xts);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  constexpr int ULANES = 64 / kWideRows;  // units of a row per wave and step
-  __shared__ float red[NW][TM][kWideRows];
-  const int row0 = blockIdx.x * kWideRows, row = row0 + lane % kWideRows, j = wave * ULANES + lane / kWideRows;
+  constexpr int ULANES = 64 / R;  // units of a row per wave and step
+  __shared__ float red[NW][TM][R];
+  const int row0 = blockIdx.x * R, row = row0 + lane % R, j = wave * ULANES + lane / R;
+  // (one token, the only shared expert wide: this launch ends the forward)
+  const bool combine = TM == 1 && wide_down_combines(a);
+  float others = 0.0f;
+  if (combine && (int)threadIdx.x < R)
+    for (int j = 0; j < a.k; ++j) others += a.partial[(size_t)j * H + row0 + threadIdx.x];
   for (int m0 = 0; m0 < sl.M; m0 += TM) {
     const int mc = min(TM, sl.M - m0);
     __syncthreads();
@@ -980,10 +977,10 @@ __global__ __launch_bounds__(64 * NW) void wide_down_kernel(DecodeArgs a) {
       }
     }
     __syncthreads();
-    wide_put<TM, NW>(wide_row_dot_any<2, TM>(td, row, U, j, NW * ULANES, xts, lo, sts, mc), red, wave, lane);
+    wide_put<TM, R>(wide_row_dot_any<2, TM>(td, row, U, j, NW * ULANES, xts, lo, sts, mc), red, wave, lane);
     __syncthreads();
-    for (int i = threadIdx.x; i < kWideRows * mc; i += 64 * NW) {
-      const int m = i / kWideRows, r = i % kWideRows;
+    for (int i = threadIdx.x; i < R * mc; i += 64 * NW) {
+      const int m = i / R, r = i % R;
       int prow;
       float wv;
       if (sl.shared >= 0) {
@@ -993,7 +990,11 @@ __global__ __launch_bounds__(64 * NW) void wide_down_kernel(DecodeArgs a) {
         prow = a.perm[sl.base + m0 + m];
         wv = a.w[prow];
       }
-      a.partial[(size_t)prow * H + row0 + r] = wv * wide_total<TM, NW>(red, m, r);
+      const float v = wv * wide_total<TM, NW, R>(red, m, r);
+      if (combine)
+        a.y[row0 + r] = others + v;
+      else
+        a.partial[(size_t)prow * H + row0 + r] = v;
     }
   }
 }
@@ -1009,61 +1010,44 @@ hipError_t launch_lds(K kernel, dim3 grid, size_t lds, hipStream_t s, const Deco
   return hipGetLastError();
 }
 
-template <int TM, int NW>
+template <int TM, int NW, int R>
 hipError_t launch_wide_gateup_tm(const DecodeArgs& a, hipStream_t s) {
   const int U = a.H / kUnit;
   const size_t lds = (size_t)TM * (U * kXStride + U * 4) * 4;
-  dim3 grid(a.I / kWideRows, a.wide_gateup == 1 ? a.S : a.S + a.max_active);
-  return launch_lds(wide_gateup_kernel<TM, NW>, grid, lds, s, a, 64 * NW);
+  dim3 grid(a.I / R, a.wide_gateup == 1 ? a.S : a.S + a.max_active);
+  return launch_lds(wide_gateup_kernel<TM, NW, R>, grid, lds, s, a, 64 * NW);
 }
 
-template <int TM, int NW>
+template <int TM, int NW, int R>
 hipError_t launch_wide_down_tm(const DecodeArgs& a, hipStream_t s) {
   const int U = a.I / kUnit;
   const size_t lds = (size_t)TM * (2 * U * kXStride + U * 4) * 4;
-  dim3 grid(a.H / kWideRows, a.wide_down == 1 ? a.S : a.S + a.max_active);
-  return launch_lds(wide_down_kernel<TM, NW>, grid, lds, s, a, 64 * NW);
-}
-
-// shared experts only: eight waves share a row's units in gate/up (long rows,
-// few workgroups), else four
-hipError_t launch_wide_gateup(const DecodeArgs& a, hipStream_t s) {
-  if (!a.wide_gateup) return hipSuccess;
-  const bool few = a.wide_gateup == 1;
-  if (a.n == 1) return few ? launch_wide_gateup_tm<1, 8>(a, s) : launch_wide_gateup_tm<1, 4>(a, s);
-  return few ? launch_wide_gateup_tm<4, 8>(a, s) : launch_wide_gateup_tm<4, 4>(a, s);
-}
-
-hipError_t launch_wide_down(const DecodeArgs& a, hipStream_t s) {
-  if (!a.wide_down) return hipSuccess;
-  return a.n == 1 ? launch_wide_down_tm<1, 4>(a, s) : launch_wide_down_tm<4, 4>(a, s);
+  dim3 grid(a.H / R, a.wide_down == 1 ? a.S : a.S + a.max_active);
+  return launch_lds(wide_down_kernel<TM, NW, R>, grid, lds, s, a, 64 * NW);
 }
 
 }  // namespace
 
-// Gate/up: buckets of one token (every bucket when n = 1) take the
-// one-token kernel, the others (n > 1) the kernel that stages 4 tokens at a
-// time.  Down: one kernel per batch size (measured: splitting it the same way
-// gains nothing at 16 tokens and costs 3 % at 64).
-hipError_t launch_gateup_decode_single(const DecodeArgs& a, hipStream_t s) {
-  const int U = a.H / kUnit;
-  const size_t lds = (size_t)(U * kXStride + U * 8) * 4;
-  dim3 grid(a.I / kGuRows, a.S + a.max_active);
-  gateup1_kernel<<<grid, kGuThreads, lds, s>>>(a);
-  const hipError_t e = hipGetLastError();
-  return e == hipSuccess ? launch_wide_gateup(a, s) : e;
+hipError_t launch_wide_gateup(const DecodeArgs& a, hipStream_t s) {
+  if (!a.wide_gateup) return hipSuccess;
+  const bool few = a.wide_gateup == 1;  // shared experts only
+  if (a.n == 1) return few ? launch_wide_gateup_tm<1, 4, 8>(a, s) : launch_wide_gateup_tm<1, 4, 32>(a, s);
+  return few ? launch_wide_gateup_tm<4, 8, 16>(a, s) : launch_wide_gateup_tm<4, 4, 32>(a, s);
 }
 
-// tokens staged per pass of the 2-64-token gate/up kernel
-#ifndef MOEQ_GATEUPN_TOKENS
-#define MOEQ_GATEUPN_TOKENS 2
-#endif
-hipError_t launch_gateup_decode_multi(const DecodeArgs& a, hipStream_t s2) {
-  constexpr int TM = MOEQ_GATEUPN_TOKENS;
+hipError_t launch_wide_down(const DecodeArgs& a, hipStream_t s) {
+  if (!a.wide_down) return hipSuccess;
+  const bool few = a.wide_down == 1;
+  if (a.n == 1) return few ? launch_wide_down_tm<1, 8, 32>(a, s) : launch_wide_down_tm<1, 4, 32>(a, s);
+  return few ? launch_wide_down_tm<4, 4, 16>(a, s) : launch_wide_down_tm<4, 4, 32>(a, s);
+}
+
+hipError_t launch_gateup_decode(const DecodeArgs& a, hipStream_t s) {
+  constexpr int TM = 2;
   const int U = a.H / kUnit;
-  const size_t lds = (size_t)TM * (U * kXStride + U * 8) * 4;
-  dim3 grid(a.I / kGuRows, a.S + a.max_active);
-  return launch_lds(gateupn_kernel<TM>, grid, lds, s2, a, kGuThreads);
+  const size_t lds = (size_t)(a.n == 1 ? 1 : TM) * (U * kXStride + U * 8) * 4;
+  dim3 grid(a.I / kGuRowsN, a.S + a.max_active);
+  return launch_lds(gateupn_kernel<TM>, grid, lds, s, a, kGuThreads);
 }
 
 bool gateup1_routes(const RouterParams& rp) { return !rp.kept_ids && !rp.x && rp.E_row <= 256 && rp.k <= kMaxTopK; }
@@ -1072,52 +1056,39 @@ hipError_t launch_gateup_decode_routing(const DecodeArgs& a, const RouterParams&
                                         hipStream_t s) {
   const int U = a.H / kUnit;
   const size_t lds = (size_t)(U * kXStride + U * 8) * 4;
-  dim3 grid(a.I / kGuRows, a.S + rp.k);
+  dim3 grid(a.I / kGuRows1, a.S + rp.k);
   if (rp.E_row <= 64)
     gateup1_route_kernel<1><<<grid, kGuThreads, lds, s>>>(a, rp, ws);
   else if (rp.E_row <= 128)
     gateup1_route_kernel<2><<<grid, kGuThreads, lds, s>>>(a, rp, ws);
   else
     gateup1_route_kernel<4><<<grid, kGuThreads, lds, s>>>(a, rp, ws);
-  const hipError_t e = hipGetLastError();
-  return e == hipSuccess ? launch_wide_gateup(a, s) : e;
-}
-
-hipError_t launch_gateup_decode(const DecodeArgs& a, hipStream_t s) {
-  hipError_t e = launch_gateup_decode_single(a, s);
-  if (e == hipSuccess && a.n > 1) e = launch_gateup_decode_multi(a, s);
-  return e;
+  return hipGetLastError();
 }
 
 namespace {
-// threads per workgroup (NT / 16 rows) and slots in flight per lane (D) of
-// the one-token down + combine kernel
-#ifndef MOEQ_DOWN1_THREADS
-#define MOEQ_DOWN1_THREADS 512
-#endif
-#ifndef MOEQ_DOWN1_DEPTH
-#define MOEQ_DOWN1_DEPTH 3
-#endif
 size_t down1_lds(const DecodeArgs& a) {
-  const size_t U = a.I / kUnit, NS = a.k + a.S;
-  return NS * (U * kXStride * 4 + U * 4 * sizeof(float2));
+  const size_t units = (a.I / kUnit + 1) / 2 * 2, NS = a.k + a.S;
+  return NS * units * (kXStride * 4 + 4 * sizeof(float2));
 }
 
+// three slots in flight per lane (two: the same; four: 19.5 instead of 18.3 us)
 template <int BD>
 hipError_t launch_down1_b(const DecodeArgs& a, hipStream_t s) {
-  constexpr int NT = MOEQ_DOWN1_THREADS, R = NT / 16;
-  down1_kernel<BD, NT, MOEQ_DOWN1_DEPTH><<<(a.H + R - 1) / R, NT, down1_lds(a), s>>>(a);
+  down1_kernel<BD, 3><<<a.H / 32, 512, down1_lds(a), s>>>(a);
   return hipGetLastError();
 }
 }  // namespace
 
-bool down_combines(const DecodeArgs& a) {
+static bool down1_serves(const DecodeArgs& a) {
   return a.n == 1 && a.wide_down == 0 && a.down_bits <= 4 && a.I / kUnit <= 16 &&
          down1_lds(a) <= 65536;
 }
 
+bool down_combines(const DecodeArgs& a) { return down1_serves(a) || wide_down_combines(a); }
+
 hipError_t launch_down_decode(const DecodeArgs& a, hipStream_t s) {
-  if (down_combines(a)) {
+  if (down1_serves(a)) {
     switch (a.down_bits) {
       case 0: return launch_down1_b<0>(a, s);  // widths differ between tensors
       case 2: return launch_down1_b<2>(a, s);
@@ -1125,10 +1096,19 @@ hipError_t launch_down_decode(const DecodeArgs& a, hipStream_t s) {
       default: return launch_down1_b<4>(a, s);
     }
   }
-  const int U = a.I / kUnit;
-  const size_t lds = (size_t)kDownTokens * (U * kXStride + U * 8) * 4;
-  const hipError_t e = launch_lds(down_kernel, dim3(a.H / 128, a.S + a.max_active), lds, s, a);
-  return e == hipSuccess ? launch_wide_down(a, s) : e;
+  // R = 32 halves the staging of h per weight; few slots take R = 16, whose
+  // twice as many workgroups cover the chip (2 tokens of the benchmark's layer,
+  // 17 slots: 99.9 us per step against 101.4; 16 tokens: 431 against 426)
+  const size_t lds1 = (size_t)(a.I / kUnit) * (kXStride + 8) * 4;  // per staged token
+  const int slots = a.S + a.max_active;
+  hipError_t e;
+  if (a.n == 1)
+    e = launch_lds(down_kernel<1, 16>, dim3(a.H / 64, slots), lds1, s, a);
+  else if (a.H / 128 * slots < 2048)
+    e = launch_lds(down_kernel<4, 16>, dim3(a.H / 64, slots), 4 * lds1, s, a);
+  else
+    e = launch_lds(down_kernel<4, 32>, dim3(a.H / 128, slots), 4 * lds1, s, a);
+  return e;
 }
 
 hipError_t launch_combine(const DecodeArgs& a, hipStream_t s) {

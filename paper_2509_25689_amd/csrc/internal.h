@@ -153,21 +153,21 @@ struct DecodeArgs {
   // the dequant-GEMV kernels
   int32_t gemm_above;
 };
+// gate/up of the buckets of 1 .. gemm_above tokens with 2-4-bit tensors, and
+// (if any) of those with a 5/6/8-bit one
 hipError_t launch_gateup_decode(const DecodeArgs& a, hipStream_t s);
-// the same work split over two streams: the one-token buckets (and the wide
-// kernels) on s, the buckets of 2-64 tokens on s2 (n > 1; the caller orders
-// s2 after the routing and joins it back into s)
-hipError_t launch_gateup_decode_single(const DecodeArgs& a, hipStream_t s);
-hipError_t launch_gateup_decode_multi(const DecodeArgs& a, hipStream_t s2);
+hipError_t launch_wide_gateup(const DecodeArgs& a, hipStream_t s);
 // One token without a routing launch: the gate/up workgroups route the
 // token themselves and one of them writes the routing and bucket outputs
 // (gateup1_routes: the mask-based router with at most 256 experts)
 bool gateup1_routes(const RouterParams& rp);
 hipError_t launch_gateup_decode_routing(const DecodeArgs& a, const RouterParams& rp, const Workspace& ws,
                                         hipStream_t s);
-// down x routing weight; for one token with 2-4-bit down tensors (down_combines)
-// it also sums the slots into y, and the combine is not launched
+// down x routing weight; for one token (down_combines) with 2-4-bit down tensors,
+// or with one shared expert whose down tensor alone is wider, the last of the
+// two launches also sums the slots into y, and the combine is not launched
 hipError_t launch_down_decode(const DecodeArgs& a, hipStream_t s);
+hipError_t launch_wide_down(const DecodeArgs& a, hipStream_t s);
 bool down_combines(const DecodeArgs& a);
 hipError_t launch_combine(const DecodeArgs& a, hipStream_t s);
 // gate.hip: logits = x W_r^T (bf16 x [n x H], float32 W_r [E x H]); up to

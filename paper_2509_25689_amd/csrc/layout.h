@@ -251,16 +251,24 @@ __device__ __forceinline__ void block_pairs_sub(const uint32_t* w, uint32_t (&p)
 // a wave of the grouped GEMMs (32 rows) streams one contiguous region.
 constexpr int kRowTile = 64;
 
-// chunk 0 of unit 0 of `row`; chunk j of unit u follows at [(u * bits + j) * 64]
-__device__ __forceinline__ const MOEQ_GLOBAL u32x4* row_chunks(const uint32_t* codes, int bits, int U, int row) {
-  return gptr(reinterpret_cast<const u32x4*>(codes)) + (size_t)(row / kRowTile) * U * bits * kRowTile + row % kRowTile;
+// Chunk 0 of unit 0 of `row` is the tensor's chunk_index-th; chunk j of unit u
+// follows (u * bits + j) * 64 further.
+__device__ __forceinline__ size_t chunk_index(int bits, int U, int row) {
+  return (size_t)(row / kRowTile) * U * bits * kRowTile + row % kRowTile;
 }
-// the four binary16 scales of unit 0 of `row`; unit u's at [scale_step(u)]
-__device__ __forceinline__ const MOEQ_GLOBAL u32x2* row_scales(const uint16_t* scales, int U, int row) {
-  return gptr(reinterpret_cast<const u32x2*>(scales)) + (size_t)(row / kRowTile) * ((U + 1) / 2) * (2 * kRowTile) +
-         row % kRowTile * 2;
+// The four binary16 scales of unit 0 of `row` are the scale_index-th; unit
+// u's follow scale_step(u) further.
+__device__ __forceinline__ size_t scale_index(int U, int row) {
+  return (size_t)(row / kRowTile) * ((U + 1) / 2) * (2 * kRowTile) + row % kRowTile * 2;
 }
 __device__ __forceinline__ int scale_step(int u) { return (u >> 1) * (2 * kRowTile) + (u & 1); }
+
+__device__ __forceinline__ const MOEQ_GLOBAL u32x4* row_chunks(const uint32_t* codes, int bits, int U, int row) {
+  return gptr(reinterpret_cast<const u32x4*>(codes)) + chunk_index(bits, U, row);
+}
+__device__ __forceinline__ const MOEQ_GLOBAL u32x2* row_scales(const uint16_t* scales, int U, int row) {
+  return gptr(reinterpret_cast<const u32x2*>(scales)) + scale_index(U, row);
+}
 
 // The 4 * B dwords of unit u of the row whose chunks start at rc.
 template <int B>
