@@ -30,25 +30,7 @@ using namespace moeq;
 namespace {
 thread_local std::string g_last_error;
 
-// One auxiliary stream per device (default priority, non-blocking), shared by
-// every layer on that device and created on first use.  A forward forks part
-// of its work onto it and joins it back with the layer's own two events, so
-// layers never wait on each other's auxiliary work except by sharing this
-// queue.
 constexpr int kMaxDevices = 64;
-std::mutex g_aux_mu;
-hipStream_t g_aux[kMaxDevices] = {};
-
-hipError_t aux_stream(int dev, hipStream_t* out) {
-  if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-  std::lock_guard<std::mutex> lk(g_aux_mu);
-  if (!g_aux[dev]) {
-    const hipError_t e = hipStreamCreateWithFlags(&g_aux[dev], hipStreamNonBlocking);
-    if (e != hipSuccess) return e;
-  }
-  *out = g_aux[dev];
-  return hipSuccess;
-}
 }  // namespace
 
 moeq_status moeq::vset_error(moeq_status st, const char* fmt, va_list ap) {
@@ -109,11 +91,6 @@ struct moeq_layer {
   void* ws_mem = nullptr;
   Workspace ws{};
   hipEvent_t stage_events[MOEQ_STAGE_EVENTS] = {};
-  // the device's auxiliary stream (shared, not owned) and two events: for
-  // 2-64 tokens the gate/up GEMVs of one-token buckets and of larger buckets
-  // run side by side
-  hipStream_t aux = nullptr;
-  hipEvent_t fork_ev = nullptr, join_ev = nullptr;
   bool timing = false;
 };
 
@@ -121,8 +98,6 @@ namespace {
 
 void release(moeq_layer* L) {
   if (!L) return;
-  if (L->fork_ev) hipEventDestroy(L->fork_ev);
-  if (L->join_ev) hipEventDestroy(L->join_ev);
   hipFree(L->store);
   hipFree(L->desc);
   hipFree(L->mask);
@@ -329,7 +304,7 @@ moeq_status moeq_layer_create(const moeq_config* cfg, const uint8_t* expert_mask
     wo = align_up(wo + bytes, 256);
     return at;
   };
-  const int max_mtiles = prefill_max_mtiles(T, k, S, n_kept), max_rtiles = prefill_max_rtiles(T, k, S, n_kept);
+  const int max_mtiles = prefill_max_mtiles(T, k, S, n_kept), max_rtiles = prefill_max_rtiles(T, k, S, n_kept, kRdTile / 2);
   const size_t o_idx = ws_take(nk * 4), o_w = ws_take(nk * 4), o_off = ws_take((size_t)(E + 1) * 4),
                o_perm = ws_take(nk * 4), o_act = ws_take((size_t)(E + 1) * 4),
                o_cc = ws_take(chunks * E * 4), o_rank = ws_take(nk * 4),
@@ -483,10 +458,6 @@ moeq_status moeq_layer_create(const moeq_config* cfg, const uint8_t* expert_mask
   L->ws.zeros = (uint32_t*)(w + o_zero);
   if ((he = hipMemset(L->ws.zeros, 0, 256)) != hipSuccess || (he = hipStreamSynchronize(nullptr)) != hipSuccess)
     return bail(he, "hipMemset(zeros)");
-  if ((he = aux_stream(L->device, &L->aux)) != hipSuccess) return bail(he, "hipStreamCreate (auxiliary)");
-  if ((he = hipEventCreateWithFlags(&L->fork_ev, hipEventDisableTiming)) != hipSuccess ||
-      (he = hipEventCreateWithFlags(&L->join_ev, hipEventDisableTiming)) != hipSuccess)
-    return bail(he, "hipEventCreate");
   *out = L;
   return ok();
 }
@@ -552,7 +523,8 @@ moeq_status moeq_forward(moeq_layer* L, const void* x, const float* logits, int3
   a.rowmax = L->ws.rowmax;
   a.max_mtiles = prefill_max_mtiles(n, a.k, a.S, L->n_kept);
   a.tiles_all = L->ws.tiles_all;
-  a.max_rtiles = prefill_max_rtiles(n, a.k, a.S, L->n_kept);
+  a.rd_tile = prefill_rd_tile(n, a.k, a.S, L->n_kept, a.I);
+  a.max_rtiles = prefill_max_rtiles(n, a.k, a.S, L->n_kept, a.rd_tile);
   a.tiles_rd = L->ws.tiles_rd;
   a.x16 = L->ws.x16;
   a.h16 = L->ws.h16;
@@ -585,33 +557,16 @@ moeq_status moeq_forward(moeq_layer* L, const void* x, const float* logits, int3
   const bool self_routed = !prefill && n == 1 && gateup1_routes(rp1);
   if (e == hipSuccess && !self_routed) e = route_and_bucket(L, logits, n, s, prefill || hybrid ? x : nullptr);
   mark(1);
-  // work beside the caller's stream: fork() orders the auxiliary stream after
-  // it, join() brings it back
-  auto fork = [&] {
-    if (e == hipSuccess) e = hipEventRecord(L->fork_ev, s);
-    if (e == hipSuccess) e = hipStreamWaitEvent(L->aux, L->fork_ev, 0);
-  };
-  auto join = [&] {
-    if (e == hipSuccess) e = hipEventRecord(L->join_ev, L->aux);
-    if (e == hipSuccess) e = hipStreamWaitEvent(s, L->join_ev, 0);
-  };
   const bool gemms = prefill || hybrid;
   if (e == hipSuccess && gemms) e = launch_prefill_tiles(a, s);
-  if (gemms) fork();
   if (e == hipSuccess && gemms) e = launch_gateup_prefill(a, s);
-  if (e == hipSuccess && gemms) e = launch_gateup_prefill_small(a, L->aux);
   if (e == hipSuccess && !prefill)
     e = self_routed ? launch_gateup_decode_routing(a, rp1, L->ws, s) : launch_gateup_decode(a, s);
   if (e == hipSuccess && !prefill) e = launch_wide_gateup(a, s);
-  if (gemms) join();
   mark(2);
-  if (e == hipSuccess && gemms) e = launch_h16(a, s);
-  if (gemms) fork();
   if (e == hipSuccess && gemms) e = launch_down_prefill(a, s);
-  if (e == hipSuccess && gemms) e = launch_down_prefill_small(a, L->aux);
   if (e == hipSuccess && !prefill) e = launch_down_decode(a, s);
   if (e == hipSuccess && !prefill) e = launch_wide_down(a, s);
-  if (gemms) join();
   mark(3);
   if (e == hipSuccess && (prefill || !down_combines(a))) e = launch_combine(a, s);
   mark(4);

@@ -89,7 +89,7 @@ struct Workspace {
   uint32_t* rowmax;    // [T*k + T*S] max |h| of each activation row (float bits)
   int32_t* tiles_all;  // [1 + 2*max_mtiles] count, then (slot, first row) of every bucket's
                        // tiles of up to 128 rows, slot order
-  int32_t* tiles_rd;   // [1 + 2*max_rtiles] the same for tiles of up to 64 rows
+  int32_t* tiles_rd;   // [1 + 2*max_rtiles] the same for tiles of up to rd_tile rows, dealt to the XCDs
   uint16_t* x16;       // [T x H]  binary16 x * 2^-xexp (many-token path)
   uint16_t* h16;       // [(T*k + T*S) x I] binary16 h * 2^-(row exponent) (many-token path)
   uint32_t* zeros;     // [64]    zeroed at create, never written again
@@ -135,6 +135,7 @@ struct DecodeArgs {
   int32_t max_mtiles;
   int32_t* tiles_all;
   int32_t max_rtiles;
+  int32_t rd_tile;        // tokens per register-decoded tile (prefill_rd_tile)
   int32_t* tiles_rd;
   const uint16_t* x16;
   uint16_t* h16;
@@ -194,21 +195,15 @@ hipError_t launch_expert_importance(const int32_t* offsets, const int32_t* perm,
                                     hipStream_t s);
 // prefill.hip
 constexpr int kGemmBM = 128;  // tokens per m-tile of the LDS-decoded GEMMs
-#ifndef MOEQ_RD_TILE
-#define MOEQ_RD_TILE 128
-#endif
-constexpr int kRdTile = MOEQ_RD_TILE;  // tokens per tile of the register-decoded GEMMs
+constexpr int kRdTile = 128;  // tokens per tile of the register-decoded GEMMs, at most
 int prefill_max_mtiles(int n, int k, int S, int n_kept);
-int prefill_max_rtiles(int n, int k, int S, int n_kept);
-// the tile list (and cleared h row maxima), then the gate/up GEMMs, h in
-// binary16 and the down GEMMs; the tiles of up to 32 tokens of 2-4-bit
-// tensors (_small) are kernels of their own, which may run beside the others
+int prefill_rd_tile(int n, int k, int S, int n_kept, int I);
+int prefill_max_rtiles(int n, int k, int S, int n_kept, int rd_tile);
+// the tile list (and cleared h row maxima), then the gate/up GEMMs, then
+// h in binary16 and the down GEMMs
 hipError_t launch_prefill_tiles(const DecodeArgs& a, hipStream_t s);
 hipError_t launch_gateup_prefill(const DecodeArgs& a, hipStream_t s);
-hipError_t launch_gateup_prefill_small(const DecodeArgs& a, hipStream_t s);
-hipError_t launch_h16(const DecodeArgs& a, hipStream_t s);
 hipError_t launch_down_prefill(const DecodeArgs& a, hipStream_t s);
-hipError_t launch_down_prefill_small(const DecodeArgs& a, hipStream_t s);
 // the grouped GEMMs' weight decoder: binary16 d * (c - 2^(b-1)) bit patterns
 hipError_t launch_dequant_gemm(const TensorDev& t, uint16_t* out, hipStream_t s);
 

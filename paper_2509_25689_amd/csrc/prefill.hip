@@ -60,7 +60,8 @@ constexpr int kRdDeal = MOEQ_RD_DEAL;  // register-decoded tiles dealt to an XCD
 // tiles first (kRdDeal = 0: slot order).  Also clears the running maxima of
 // the h rows.
 __global__ __launch_bounds__(1024) void prefill_tiles_kernel(DecodeArgs a) {
-  constexpr int kCls = kRdTile / 32;  // remainder classes by 32-row steps
+  constexpr int kCls = kRdTile / 32;  // remainder classes by 32-row steps (at most)
+  const int rdt = a.rd_tile;
   // per-slot counts scanned over the slots: LDS-decoded tiles, full
   // register-decoded tiles, register-decoded tiles, remainders of each class
   constexpr int NF = 3 + kCls;
@@ -94,11 +95,11 @@ __global__ __launch_bounds__(1024) void prefill_tiles_kernel(DecodeArgs a) {
       M = a.offsets[e + 1] - a.offsets[e];
     }
     if (M <= a.gemm_above) M = 0;  // (small buckets of a decode forward: the GEMV kernels)
-    const int rem = M % kRdTile;
+    const int rem = M % rdt;
     cls[h] = (rem + 31) / 32;
     val[h][0] = (M + BM - 1) / BM;
-    val[h][1] = M / kRdTile;
-    val[h][2] = M / kRdTile + (rem ? 1 : 0);
+    val[h][1] = M / rdt;
+    val[h][2] = M / rdt + (rem ? 1 : 0);
 #pragma unroll
     for (int c = 1; c <= kCls; ++c) val[h][2 + c] = cls[h] == c ? 1 : 0;
   }
@@ -190,7 +191,7 @@ __global__ __launch_bounds__(1024) void prefill_tiles_kernel(DecodeArgs a) {
       }
       if (t < kXcds * B) {
         a.tiles_rd[1 + 2 * t] = s;
-        a.tiles_rd[2 + 2 * t] = i * kRdTile;
+        a.tiles_rd[2 + 2 * t] = i * rdt;
       }
     }
   }
@@ -818,6 +819,7 @@ constexpr size_t rd_lds(int nt) { return (size_t)RD_NBUF * nt * RD_TSUB; }
 static_assert(RD_WAVES * RD_WROWS == RD_ROWS, "the waves cover the workgroup's rows");
 static_assert(rd_lds(1) >= (size_t)(RD_WAVES / 2) * RD_RT * 64 * 64,
               "the SwiGLU hand-over must fit the activation buffers");
+static_assert(RD_NTMAX == 4 && rd_lds(2) <= 64 * 1024, "tiles of up to 128 tokens; the small kernel needs no raised limit");
 static_assert(rd_lds(RD_NTMAX) <= 160 * 1024, "the activation buffers fit a compute unit's LDS");
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -966,7 +968,7 @@ __device__ __forceinline__ half8 rd_piece(const RdUnit<B>& u, const RdConsts& k)
 // (each chunk is requested 4 WL - 2 sub-stages before the sub-stage that
 // first uses it, as soon as the ring slot's previous stage has finished with
 // it).
-template <int B, int NT, bool ACT, int AL, int WL>
+template <int B, int NT, bool ACT, int AL, int WL, bool PIPE>
 __device__ __forceinline__ void rd_kloop(const MOEQ_GLOBAL u32x4* const (&rc)[RD_RT],
                                          const MOEQ_GLOBAL u32x2* const (&rs)[RD_RT], int Uk,
                                          const MOEQ_GLOBAL u32x4* const (&arow)[RD_APT], int su, int sm,
@@ -1119,6 +1121,27 @@ __device__ __forceinline__ void rd_kloop(const MOEQ_GLOBAL u32x4* const (&rc)[RD
     RD_PRODUCTS(fa1, fb1);                                                                              \
   } while (0)
 
+  // the same without the software pipeline (its second set of operands is
+  // registers that two token tiles at four waves per SIMD do not have; the
+  // other waves fill the waits instead)
+#define RD_KSTEP1(W, Q, TS)                                                                             \
+  do {                                                                                                  \
+    RD_OPERANDS(W, Q, TS, fa0, fb0);                                                                    \
+    RD_PRODUCTS(fa0, fb0);                                                                              \
+    __builtin_amdgcn_sched_barrier(0);                                                                  \
+  } while (0)
+#define RD_KSTEPS1(W, Q)                                                                                \
+  do {                                                                                                  \
+    RD_KSTEP1(W, Q, 0);                                                                                 \
+    RD_KSTEP1(W, Q, 1);                                                                                 \
+    RD_KSTEP1(W, Q, 2);                                                                                 \
+    RD_KSTEP1(W, Q, 3);                                                                                 \
+    RD_KSTEP1(W, Q, 4);                                                                                 \
+    RD_KSTEP1(W, Q, 5);                                                                                 \
+    RD_KSTEP1(W, Q, 6);                                                                                 \
+    RD_KSTEP1(W, Q, 7);                                                                                 \
+  } while (0)
+
   // sub-stage s = 4 (U + W) + Q in LDS buffer Q, weights in ring slot W:
   // request sub-stage s + AL into the staging set that held s (stored at the
   // end of s - 1), multiply sub-stage s, store sub-stage s + 1 (requested
@@ -1134,7 +1157,10 @@ __device__ __forceinline__ void rd_kloop(const MOEQ_GLOBAL u32x4* const (&rc)[RD
 #define RD_SUBSTAGE(W, Q)                                                                               \
   do {                                                                                                  \
     aload(xs[(4 * (W) + (Q)) % AL], min(4 * (U + (W)) + (Q) + AL, NSUB - 1));                           \
-    RD_KSTEPS(W, Q);                                                                                    \
+    if constexpr (PIPE)                                                                                 \
+      RD_KSTEPS(W, Q);                                                                                  \
+    else                                                                                                \
+      RD_KSTEPS1(W, Q);                                                                                 \
     astore(xs[(4 * (W) + (Q) + 1) % AL], ((Q) + 1) & 3);                                                \
     if constexpr ((Q) == 0)                                                                             \
       rload_first(raw[((W) + WL - 1) % WL], 3, min(U + (W) + WL - 1, NSp));                             \
@@ -1159,6 +1185,8 @@ __device__ __forceinline__ void rd_kloop(const MOEQ_GLOBAL u32x4* const (&rc)[RD
   }
 #undef RD_SUBSTAGE
 #undef RD_KSTEPS
+#undef RD_KSTEPS1
+#undef RD_KSTEP1
 #undef RD_PRODUCTS
 #undef RD_OPERANDS
 }
@@ -1182,7 +1210,7 @@ __device__ __forceinline__ void rd_kloop_any(int bits, bool act, const MOEQ_GLOB
                                              const MOEQ_GLOBAL uint32_t* zero, char* lds, int tid, int lane,
                                              f32x16 (&acc)[RD_RT][NT]) {
   constexpr int AL = MOEQ_RD_AL, WL = MOEQ_RD_WL;
-#define RD_KLOOP(B, ACT) rd_kloop<B, NT, ACT, AL, WL>(rc, rs, Uk, arow, su, sm, zero, lds, tid, lane, acc)
+#define RD_KLOOP(B, ACT) rd_kloop<B, NT, ACT, AL, WL, (WIDE || NT == 1)>(rc, rs, Uk, arow, su, sm, zero, lds, tid, lane, acc)
   if (!act)
     RD_KLOOP(2, false);
   else if (bits == 2)
@@ -1359,13 +1387,14 @@ __device__ void rd_down_tile(const GemmArgs& a, const SlotInfo& sl, int m0, int 
   }
 }
 
-// The tiles of up to 32 tokens of 2-4-bit tensors have a kernel of their own
-// (SMALL): they are bound by the weights they stream, and with 128 registers
-// and 32 KB of LDS two workgroups share a compute unit, each filling the
-// other's waits (512 tokens, 192 experts of about 21 tokens, 3-bit gate/up:
-// 657 us with one workgroup per compute unit for every tile, 548 + 65 us in two
-// kernels one after the other).  Both kernels walk the same list.
-__device__ __forceinline__ bool rd_small(int Mt, int bits) { return Mt <= 32 && bits <= 4; }
+// The tiles of up to 64 tokens of 2-4-bit tensors have a kernel of their own
+// (SMALL): they are bound by the weights they stream and decode, and with 128
+// registers and 64 KB of LDS two workgroups share a compute unit, each filling
+// the other's waits (gate/up of 512 tokens over 192 experts, about 21 tokens
+// each, 3 bits: 657 us with one workgroup per compute unit, 540 with two).
+// Both kernels walk the same list; the one for larger tiles and wider tensors
+// is launched only when there can be some.
+__device__ __forceinline__ bool rd_small(int Mt, int bits) { return Mt <= 64 && bits <= 4; }
 
 // grid: tile_grid(max m-tiles, n-tiles)
 template <bool SMALL>
@@ -1378,12 +1407,15 @@ __global__ __launch_bounds__(RD_THREADS, SMALL ? 4 : 1) void gateup_rd_kernel(De
   const int m0 = a.tiles_rd[2 + 2 * mt];
   const TensorDev tg = a.desc[sl.desc * 3 + 0], tu = a.desc[sl.desc * 3 + 1];
   if (!tg.codes || !tu.codes || !rd_ok(tg) || !rd_ok(tu)) return;
-  const int Mt = min(RD_T, sl.M - m0);
+  const int Mt = min(a.rd_tile, sl.M - m0);
   if (rd_small(Mt, max(tg.bits, tu.bits)) != SMALL) return;
   const GemmArgs g = gemm_args(a);
   const int f0 = nt * (RD_ROWS / 2);
   if constexpr (SMALL) {
-    rd_gateup_tile<1, false>(g, sl, m0, Mt, f0, tg, tu, lds_c);
+    if (Mt <= 32)
+      rd_gateup_tile<1, false>(g, sl, m0, Mt, f0, tg, tu, lds_c);
+    else
+      rd_gateup_tile<2, false>(g, sl, m0, Mt, f0, tg, tu, lds_c);
   } else {
     if (Mt <= 32)
       rd_gateup_tile<1, true>(g, sl, m0, Mt, f0, tg, tu, lds_c);
@@ -1406,12 +1438,15 @@ __global__ __launch_bounds__(RD_THREADS, SMALL ? 4 : 1) void down_rd_kernel(Deco
   const int m0 = a.tiles_rd[2 + 2 * mt];
   const TensorDev td = a.desc[sl.desc * 3 + 2];
   if (!td.codes || !rd_ok(td)) return;
-  const int Mt = min(RD_T, sl.M - m0);
+  const int Mt = min(a.rd_tile, sl.M - m0);
   if (rd_small(Mt, td.bits) != SMALL) return;
   const GemmArgs g = gemm_args(a);
   const int n0 = nt * RD_ROWS;
   if constexpr (SMALL) {
-    rd_down_tile<1, false>(g, sl, m0, Mt, n0, td, lds_c);
+    if (Mt <= 32)
+      rd_down_tile<1, false>(g, sl, m0, Mt, n0, td, lds_c);
+    else
+      rd_down_tile<2, false>(g, sl, m0, Mt, n0, td, lds_c);
   } else {
     if (Mt <= 32)
       rd_down_tile<1, true>(g, sl, m0, Mt, n0, td, lds_c);
@@ -1471,10 +1506,20 @@ int prefill_max_tiles(int n, int k, int S, int n_kept, int rows) {
 }
 
 int prefill_max_mtiles(int n, int k, int S, int n_kept) { return prefill_max_tiles(n, k, S, n_kept, BM); }
+// Tokens per register-decoded tile: 64, every tile of 2-4-bit tensors then in
+// the small kernel, unless the buckets are larger than that on average and the
+// 128-token tiles fill the chip four times over at one workgroup per compute
+// unit (2048 Zipf-routed tokens over 192 experts: 2258 us with 128, 2322 with
+// 64; 777 tokens over 48 experts of 11 x 128 features, 97 per bucket but two
+// rounds: 432 and 409; 900 tokens over 192: 1213 and 1193).
+int prefill_rd_tile(int n, int k, int S, int n_kept, int I) {
+  const long long wgs = (long long)n * (k + S) / kRdTile * (I / 128);
+  return (long long)n * k > 64ll * n_kept && wgs >= 1024 ? kRdTile : kRdTile / 2;
+}
 // capacity of the register-decoded list: 8 runs of the longest run any count
 // of tiles up to the largest needs
-int prefill_max_rtiles(int n, int k, int S, int n_kept) {
-  const int T = prefill_max_tiles(n, k, S, n_kept, kRdTile);
+int prefill_max_rtiles(int n, int k, int S, int n_kept, int rd_tile) {
+  const int T = prefill_max_tiles(n, k, S, n_kept, rd_tile);
   const int g = kRdDeal ? kRdDeal * kXcds : kXcds;
   return (T + g - 1) / g * g;
 }
@@ -1525,8 +1570,14 @@ hipError_t launch_prefill_tiles(const DecodeArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_gateup_prefill(const DecodeArgs& a, hipStream_t s) {
-  hipError_t e = launch_gemm(gateup_rd_kernel<false>, g_attr_gu_rd, RD_THREADS,
-                             tile_grid(a.max_rtiles, (a.I + RD_ROWS / 2 - 1) / (RD_ROWS / 2)), rd_lds(RD_NTMAX), s, a);
+  const int grid = tile_grid(a.max_rtiles, (a.I + RD_ROWS / 2 - 1) / (RD_ROWS / 2));
+  hipError_t e = hipSuccess;
+  if (a.rd_tile > 64 || a.wide_gateup)
+    e = launch_gemm(gateup_rd_kernel<false>, g_attr_gu_rd, RD_THREADS, grid, rd_lds(RD_NTMAX), s, a);
+  if (e == hipSuccess) {
+    gateup_rd_kernel<true><<<grid, RD_THREADS, rd_lds(2), s>>>(a);
+    e = hipGetLastError();
+  }
   if (e == hipSuccess && a.lds_gateup) {
     const size_t lds = (size_t)2 * (BM + 2 * BN) * LDS_STRIDE * sizeof(_Float16);
     e = launch_gemm(gateup_gemm8_kernel, g_attr_gu_w, 512, tile_grid(a.max_mtiles, a.I / BN), lds, s, a);
@@ -1534,31 +1585,23 @@ hipError_t launch_gateup_prefill(const DecodeArgs& a, hipStream_t s) {
   return e;
 }
 
-hipError_t launch_gateup_prefill_small(const DecodeArgs& a, hipStream_t s) {
-  gateup_rd_kernel<true><<<tile_grid(a.max_rtiles, (a.I + RD_ROWS / 2 - 1) / (RD_ROWS / 2)), RD_THREADS, rd_lds(1),
-                           s>>>(a);
-  return hipGetLastError();
-}
-
-hipError_t launch_h16(const DecodeArgs& a, hipStream_t s) {
+hipError_t launch_down_prefill(const DecodeArgs& a, hipStream_t s) {
   const int rows = a.n * (a.k + a.S);
   h16_kernel<<<(rows + 3) / 4, 256, 0, s>>>(a.h, a.rowmax, rows, a.I, a.h16);
-  return hipGetLastError();
-}
-
-hipError_t launch_down_prefill(const DecodeArgs& a, hipStream_t s) {
-  hipError_t e = launch_gemm(down_rd_kernel<false>, g_attr_dn_rd, RD_THREADS,
-                             tile_grid(a.max_rtiles, (a.H + RD_ROWS - 1) / RD_ROWS), rd_lds(RD_NTMAX), s, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int grid = tile_grid(a.max_rtiles, (a.H + RD_ROWS - 1) / RD_ROWS);
+  if (a.rd_tile > 64 || a.wide_down)
+    e = launch_gemm(down_rd_kernel<false>, g_attr_dn_rd, RD_THREADS, grid, rd_lds(RD_NTMAX), s, a);
+  if (e == hipSuccess) {
+    down_rd_kernel<true><<<grid, RD_THREADS, rd_lds(2), s>>>(a);
+    e = hipGetLastError();
+  }
   if (e == hipSuccess && a.lds_down) {
     const size_t lds = (size_t)2 * (BM + BN) * LDS_STRIDE * sizeof(_Float16);
     e = launch_gemm(down_gemm8_kernel, g_attr_dn_w, 512, tile_grid(a.max_mtiles, a.H / BN), lds, s, a);
   }
   return e;
-}
-
-hipError_t launch_down_prefill_small(const DecodeArgs& a, hipStream_t s) {
-  down_rd_kernel<true><<<tile_grid(a.max_rtiles, (a.H + RD_ROWS - 1) / RD_ROWS), RD_THREADS, rd_lds(1), s>>>(a);
-  return hipGetLastError();
 }
 
 }  // namespace moeq
