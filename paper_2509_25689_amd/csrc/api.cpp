@@ -19,7 +19,7 @@
 // decode forwards of at least MOEQ_HYBRID_FROM tokens send the buckets of
 // more than MOEQ_HYBRID_ABOVE rows to the grouped GEMMs
 #ifndef MOEQ_HYBRID_FROM
-#define MOEQ_HYBRID_FROM 24
+#define MOEQ_HYBRID_FROM 16
 #endif
 #ifndef MOEQ_HYBRID_ABOVE
 #define MOEQ_HYBRID_ABOVE 2
@@ -194,12 +194,8 @@ moeq_status check_routing(const moeq_config* c, const uint8_t* mask, int* n_kept
   return ok();
 }
 
-RouterParams router_params(const moeq_layer* L, const float* logits, const void* x = nullptr) {
+RouterParams router_params(const moeq_layer* L, const float* logits) {
   RouterParams rp;
-  rp.x = (const uint16_t*)x;
-  rp.H = L->cfg.hidden;
-  rp.xexp = L->ws.xexp;
-  rp.x16 = L->ws.x16;
   rp.logits = logits;
   rp.mask = L->mask;
   rp.kept_ids = L->kept_ids;
@@ -224,15 +220,67 @@ moeq_status check_device(const moeq_layer* L) {
   return ok();
 }
 
+// The many-token router (a workgroup per 4 tokens) instead of the small one
+// (one workgroup for everything: 12 us at 16 tokens, 26-37 at 48), with the
+// buckets built by the tile-list launch of the grouped GEMMs if one workgroup's
+// LDS holds them.
+bool buckets_with_tiles(const moeq_layer* L, int n) {
+  return n >= MOEQ_HYBRID_FROM && bucket_fits(n, L->cfg.n_experts);
+}
+
 // Route (+ bucket) n tokens into the workspace: the first stage of a forward.
-// With x given, the router also records each token's binary16 prescale.
-hipError_t route_and_bucket(moeq_layer* L, const float* logits, int n, hipStream_t s,
-                            const void* x = nullptr) {
-  const RouterParams rp = router_params(L, logits, x);
-  if (n <= kDecodeMaxTokens) return launch_route_bucket_small(rp, nullptr, n, L->ws, s);
-  hipError_t e = launch_route_tokens(rp, n, L->ws.idx, L->ws.w, s);
-  if (e != hipSuccess) return e;
+// With x (the grouped GEMMs follow) a call that buckets_with_tiles serves
+// leaves the buckets to the tile-list launch; *copied tells whether the
+// prescaled copy of x was made here.
+hipError_t route_and_bucket(moeq_layer* L, const float* logits, int n, hipStream_t s, const void* x = nullptr,
+                            bool* copied = nullptr) {
+  const RouterParams rp = router_params(L, logits);
+  const bool tiles = x && buckets_with_tiles(L, n);
+  if (n <= kDecodeMaxTokens && !tiles) return launch_route_bucket_small(rp, nullptr, n, L->ws, s);
+  if (copied) *copied = x != nullptr;
+  hipError_t e = launch_route_tokens(rp, n, L->ws.idx, L->ws.w, (const uint16_t*)x, L->cfg.hidden, L->ws, s);
+  if (e != hipSuccess || tiles) return e;
   return launch_bucket_chunked(L->ws.idx, n, L->cfg.top_k, L->cfg.n_experts, L->ws, s);
+}
+
+// The kernels' arguments for a forward of n tokens.
+DecodeArgs decode_args(const moeq_layer* L, const void* x, int n, float* y) {
+  DecodeArgs a;
+  a.desc = L->desc;
+  a.x = (const uint16_t*)x;
+  a.active = L->ws.active;
+  a.offsets = L->ws.offsets;
+  a.perm = L->ws.perm;
+  a.w = L->ws.w;
+  a.h = L->ws.h;
+  a.partial = L->ws.partial;
+  a.y = y;
+  a.n = n;
+  a.H = L->cfg.hidden;
+  a.I = L->cfg.inter;
+  a.E = L->cfg.n_experts;
+  a.S = L->cfg.n_shared;
+  a.k = L->cfg.top_k;
+  const long long nk = (long long)n * a.k;
+  a.max_active = (int)(nk < L->n_kept ? nk : L->n_kept);
+  a.xexp = L->ws.xexp;
+  a.rowmax = L->ws.rowmax;
+  a.max_mtiles = prefill_max_mtiles(n, a.k, a.S, L->n_kept);
+  a.tiles_all = L->ws.tiles_all;
+  a.rd_tile = prefill_rd_tile(n, a.k, a.S, L->n_kept, a.I);
+  a.max_rtiles = prefill_max_rtiles(n, a.k, a.S, L->n_kept, a.rd_tile);
+  a.tiles_rd = L->ws.tiles_rd;
+  a.x16 = L->ws.x16;
+  a.h16 = L->ws.h16;
+  a.zeros = L->ws.zeros;
+  a.wide_gateup = L->wide_gateup;
+  a.wide_down = L->wide_down;
+  a.lds_gateup = L->lds_gateup;
+  a.lds_down = L->lds_down;
+  a.idx = L->ws.idx;
+  a.down_bits = L->down_bits;
+  a.gemm_above = 0;
+  return a;
 }
 
 }  // namespace
@@ -501,40 +549,7 @@ moeq_status moeq_forward(moeq_layer* L, const void* x, const float* logits, int3
   moeq_status st = check_device(L);
   if (st != MOEQ_OK) return st;
   hipStream_t s = (hipStream_t)stream;
-  DecodeArgs a;
-  a.desc = L->desc;
-  a.x = (const uint16_t*)x;
-  a.active = L->ws.active;
-  a.offsets = L->ws.offsets;
-  a.perm = L->ws.perm;
-  a.w = L->ws.w;
-  a.h = L->ws.h;
-  a.partial = L->ws.partial;
-  a.y = y;
-  a.n = n;
-  a.H = L->cfg.hidden;
-  a.I = L->cfg.inter;
-  a.E = L->cfg.n_experts;
-  a.S = L->cfg.n_shared;
-  a.k = L->cfg.top_k;
-  const long long nk = (long long)n * a.k;
-  a.max_active = (int)(nk < L->n_kept ? nk : L->n_kept);
-  a.xexp = L->ws.xexp;
-  a.rowmax = L->ws.rowmax;
-  a.max_mtiles = prefill_max_mtiles(n, a.k, a.S, L->n_kept);
-  a.tiles_all = L->ws.tiles_all;
-  a.rd_tile = prefill_rd_tile(n, a.k, a.S, L->n_kept, a.I);
-  a.max_rtiles = prefill_max_rtiles(n, a.k, a.S, L->n_kept, a.rd_tile);
-  a.tiles_rd = L->ws.tiles_rd;
-  a.x16 = L->ws.x16;
-  a.h16 = L->ws.h16;
-  a.zeros = L->ws.zeros;
-  a.wide_gateup = L->wide_gateup;
-  a.wide_down = L->wide_down;
-  a.lds_gateup = L->lds_gateup;
-  a.lds_down = L->lds_down;
-  a.idx = L->ws.idx;
-  a.down_bits = L->down_bits;
+  DecodeArgs a = decode_args(L, x, n, y);
   const bool prefill =
       L->path == MOEQ_PATH_PREFILL || (L->path == MOEQ_PATH_AUTO && n > L->decode_max);
   // decode forwards of several tokens: the buckets of more than
@@ -555,10 +570,15 @@ moeq_status moeq_forward(moeq_layer* L, const void* x, const float* logits, int3
   // one token: the gate/up workgroups route the token themselves
   const RouterParams rp1 = router_params(L, logits);
   const bool self_routed = !prefill && n == 1 && gateup1_routes(rp1);
-  if (e == hipSuccess && !self_routed) e = route_and_bucket(L, logits, n, s, prefill || hybrid ? x : nullptr);
-  mark(1);
   const bool gemms = prefill || hybrid;
-  if (e == hipSuccess && gemms) e = launch_prefill_tiles(a, s);
+  bool copied = false;
+  if (e == hipSuccess && !self_routed) e = route_and_bucket(L, logits, n, s, gemms ? x : nullptr, &copied);
+  if (e == hipSuccess && gemms) {
+    DecodeArgs t = a;
+    if (copied) t.x = nullptr;
+    e = launch_prefill_tiles(t, buckets_with_tiles(L, n) ? &L->ws : nullptr, s);
+  }
+  mark(1);
   if (e == hipSuccess && gemms) e = launch_gateup_prefill(a, s);
   if (e == hipSuccess && !prefill)
     e = self_routed ? launch_gateup_decode_routing(a, rp1, L->ws, s) : launch_gateup_decode(a, s);
@@ -716,8 +736,7 @@ hipError_t importance_run(const moeq_config* cfg, const float* score_bias, const
   rp.topn = cfg->group_topn;
   rp.norm = 0;       // weights = sigmoid scores
   rp.scale = 1.0f;
-  rp.x = nullptr;
-  if (e == hipSuccess) e = launch_route_tokens(rp, n_tokens, ws.idx, ws.w, s);
+  if (e == hipSuccess) e = launch_route_tokens(rp, n_tokens, ws.idx, ws.w, nullptr, 0, ws, s);
   if (e == hipSuccess) e = launch_bucket_chunked(ws.idx, n_tokens, k, E, ws, s);
   if (e == hipSuccess)
     e = launch_expert_importance(ws.offsets, ws.perm, ws.w, E, n_tokens, alpha, keep, importance, mask, counts, s);
@@ -834,10 +853,15 @@ moeq_status moeq_bucket(moeq_layer* L, const int32_t* idx, int32_t n, int32_t* o
     e = hipMemsetAsync(offsets, 0, (size_t)(E + 1) * 4, s);
     return e == hipSuccess ? ok() : hip_fail(e, "bucket");
   }
-  if (n <= kDecodeMaxTokens)
+  if (n <= kDecodeMaxTokens && !buckets_with_tiles(L, n)) {
     e = launch_route_bucket_small(router_params(L, nullptr), idx, n, L->ws, s);
-  else
+  } else if (buckets_with_tiles(L, n)) {
+    DecodeArgs a = decode_args(L, nullptr, n, nullptr);
+    a.idx = idx;
+    e = launch_prefill_tiles(a, &L->ws, s);
+  } else {
     e = launch_bucket_chunked(idx, n, k, E, L->ws, s);
+  }
   if (e != hipSuccess) return hip_fail(e, "bucket launch");
   if ((e = hipMemcpyAsync(offsets, L->ws.offsets, (size_t)(E + 1) * 4, hipMemcpyDeviceToDevice, s)) !=
           hipSuccess ||

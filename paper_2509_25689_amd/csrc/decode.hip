@@ -1050,7 +1050,7 @@ hipError_t launch_gateup_decode(const DecodeArgs& a, hipStream_t s) {
   return launch_lds(gateupn_kernel<TM>, grid, lds, s, a, kGuThreads);
 }
 
-bool gateup1_routes(const RouterParams& rp) { return !rp.kept_ids && !rp.x && rp.E_row <= 256 && rp.k <= kMaxTopK; }
+bool gateup1_routes(const RouterParams& rp) { return !rp.kept_ids && rp.E_row <= 256 && rp.k <= kMaxTopK; }
 
 hipError_t launch_gateup_decode_routing(const DecodeArgs& a, const RouterParams& rp, const Workspace& ws,
                                         hipStream_t s) {

@@ -65,13 +65,6 @@ struct RouterParams {
   int32_t E_row;
   int32_t E, G, TG, k, topn, norm;
   float scale;
-  // optional (many-token path): activations whose per-token binary exponent
-  // prescale for half precision is written to xexp, and the prescaled
-  // binary16 copy x * 2^-xexp to x16
-  const uint16_t* x;      // bf16 [n x H] or null
-  int32_t H;
-  int32_t* xexp;          // [n]
-  uint16_t* x16;          // binary16 [n x H]
 };
 
 // Workspace views (device pointers) for one forward.
@@ -99,8 +92,9 @@ struct Workspace {
 // route.hip
 hipError_t launch_route_bucket_small(const RouterParams& rp, const int32_t* idx_in, int n,
                                      const Workspace& ws, hipStream_t s);
-hipError_t launch_route_tokens(const RouterParams& rp, int n, int32_t* idx, float* w,
-                               hipStream_t s);
+// (with x, bf16 [n x H], also ws.xexp and ws.x16)
+hipError_t launch_route_tokens(const RouterParams& rp, int n, int32_t* idx, float* w, const uint16_t* x, int H,
+                               const Workspace& ws, hipStream_t s);
 hipError_t launch_bucket_chunked(const int32_t* idx, int n, int k, int E, const Workspace& ws,
                                  hipStream_t s);
 // weights.hip
@@ -130,14 +124,14 @@ struct DecodeArgs {
   int32_t n, H, I, E, S, k;
   int32_t max_active;     // routed slots launched: min(n*k, kept experts)
   // many-token path
-  const int32_t* xexp;
+  int32_t* xexp;
   uint32_t* rowmax;
   int32_t max_mtiles;
   int32_t* tiles_all;
   int32_t max_rtiles;
   int32_t rd_tile;        // tokens per register-decoded tile (prefill_rd_tile)
   int32_t* tiles_rd;
-  const uint16_t* x16;
+  uint16_t* x16;
   uint16_t* h16;
   const uint32_t* zeros;  // 256 zero bytes
   const int32_t* idx;     // [n*k] chosen experts, token-major
@@ -199,9 +193,11 @@ constexpr int kRdTile = 128;  // tokens per tile of the register-decoded GEMMs, 
 int prefill_max_mtiles(int n, int k, int S, int n_kept);
 int prefill_rd_tile(int n, int k, int S, int n_kept, int I);
 int prefill_max_rtiles(int n, int k, int S, int n_kept, int rd_tile);
-// the tile list (and cleared h row maxima), then the gate/up GEMMs, then
-// h in binary16 and the down GEMMs
-hipError_t launch_prefill_tiles(const DecodeArgs& a, hipStream_t s);
+// the tile list (and cleared h row maxima) and, with a.x, the binary16 copy of
+// x; then the gate/up GEMMs, then h in binary16 and the down GEMMs.  With ws the
+// launch also buckets a.idx (bucket_fits)
+bool bucket_fits(int n, int E);
+hipError_t launch_prefill_tiles(const DecodeArgs& a, const Workspace* ws, hipStream_t s);
 hipError_t launch_gateup_prefill(const DecodeArgs& a, hipStream_t s);
 hipError_t launch_down_prefill(const DecodeArgs& a, hipStream_t s);
 // the grouped GEMMs' weight decoder: binary16 d * (c - 2^(b-1)) bit patterns

@@ -83,6 +83,44 @@ __device__ __forceinline__ int wave_incl_sum(int v) {
   return v;
 }
 
+// Experts per lane for E experts (the kernels are instantiated per value).
+inline int experts_per_lane(int E) { return E <= 64 ? 1 : E <= 128 ? 2 : E <= 256 ? 4 : E <= 512 ? 8 : 16; }
+
+// Exclusive scan of cnt[0..E) by one wavefront into off[0..E] (off[E] = total),
+// plus the ascending list of experts with cnt > 0 into active[1..], count in
+// active[0].  Lane l owns experts [l*EPL, l*EPL + EPL), EPL*64 >= E.
+template <int EPL>
+__device__ void wave_scan_experts(const int* cnt, int E, int32_t* off_lds, int32_t* off_g,
+                                  int32_t* active_g) {
+  const int lane = threadIdx.x & 63;
+  int c[EPL];
+  int local = 0, nact = 0;
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) {
+    const int e = lane * EPL + i;
+    c[i] = e < E ? cnt[e] : 0;
+    local += c[i];
+    nact += c[i] > 0;
+  }
+  const int incl = wave_incl_sum(local), iact = wave_incl_sum(nact);
+  int run = incl - local, arun = iact - nact;
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) {
+    const int e = lane * EPL + i;
+    if (e < E) {
+      if (off_lds) off_lds[e] = run;
+      off_g[e] = run;
+      if (c[i] > 0) active_g[1 + arun++] = e;
+      run += c[i];
+    }
+  }
+  if (lane == 63) {
+    off_g[E] = incl;
+    if (off_lds) off_lds[E] = incl;
+    active_g[0] = iact;
+  }
+}
+
 // Which of the lane's experts the selection chose: bit i of `bits` for
 // expert lane*EPL + i, chosen as the token's j-th expert with j = order[i].
 template <int EPL>
@@ -99,53 +137,6 @@ template <int EPL>
 __device__ LaneChoice<EPL> route_token_wave(const RouterParams& rp, int t, float* gs_l, int32_t* idx_g,
                                             float* w_g, int32_t* idx_s) {
   const int lane = threadIdx.x & 63;
-  if (rp.x) {
-    // binary exponent prescale for half precision: e puts the row's largest
-    // |x| in [2^14, 2^15) (e >= -100 keeps 2^-e finite for an all-zero row),
-    // and the prescaled binary16 copy of the row (exact unless a value lies
-    // more than 2^28 below the largest, then rounded to nearest even)
-    const MOEQ_GLOBAL u32x4* xr = gptr(reinterpret_cast<const u32x4*>(rp.x + (size_t)t * rp.H));
-    const int C = rp.H / 8;
-    // XB pieces per lane requested together in each pass (indices past the
-    // row read its last piece again: loads that do not depend on a
-    // condition go out before the first is used)
-    constexpr int XB = EPL >= 8 ? 4 : 8;
-    uint32_t mx = 0;
-    for (int c0 = lane; c0 < C; c0 += 64 * XB) {
-      u32x4 v[XB];
-#pragma unroll
-      for (int b = 0; b < XB; ++b) v[b] = xr[min(c0 + 64 * b, C - 1)];
-#pragma unroll
-      for (int b = 0; b < XB; ++b) {
-        const uint32_t q[4] = {v[b].x, v[b].y, v[b].z, v[b].w};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) mx = max(mx, max(q[j] & 0x7FFFu, (q[j] >> 16) & 0x7FFFu));
-      }
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
-    const int e = max((int)((mx >> 7) & 0xFFu) - 127 - 14, -100);
-    if (lane == 0) rp.xexp[t] = e;
-    const float sc = __builtin_amdgcn_ldexpf(1.0f, -e);
-    MOEQ_GLOBAL u32x4* hr = (MOEQ_GLOBAL u32x4*)(rp.x16 + (size_t)t * rp.H);
-    for (int c0 = lane; c0 < C; c0 += 64 * XB) {
-      u32x4 v[XB];
-#pragma unroll
-      for (int b = 0; b < XB; ++b) v[b] = xr[min(c0 + 64 * b, C - 1)];
-#pragma unroll
-      for (int b = 0; b < XB; ++b) {
-        const uint32_t q[4] = {v[b].x, v[b].y, v[b].z, v[b].w};
-        uint32_t o[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const float lo = __uint_as_float(q[j] << 16) * sc, hi = __uint_as_float(q[j] & 0xFFFF0000u) * sc;
-          o[j] = (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)lo) |
-                 ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)hi) << 16);
-        }
-        if (c0 + 64 * b < C) hr[c0 + 64 * b] = u32x4{o[0], o[1], o[2], o[3]};
-      }
-    }
-  }
   const int E = rp.E, G = rp.G, per = rp.E / rp.G;
   const float* lg = rp.logits + (size_t)t * rp.E_row;
   float s[EPL], b[EPL];
@@ -364,6 +355,47 @@ __device__ LaneChoice<EPL> route_token_wave(const RouterParams& rp, int t, float
   }
   wave_sync();  // gs_l is reused by this wave's next token
   return ch;
+}
+
+// Token t's binary exponent e, which puts its largest |x| in [2^14, 2^15) (e >=
+// -100 keeps 2^-e finite for an all-zero row), and its prescaled binary16 copy
+// (exact unless a value lies more than 2^28 below the largest, then rounded
+// to nearest even).  One workgroup of NT threads, 1024 / NT 16-byte pieces per
+// thread (H <= 8192).
+template <int NT>
+__device__ __forceinline__ void prescale_x(const uint16_t* x, int H, int t, int32_t* xexp, uint16_t* x16) {
+  constexpr int NP = 1024 / NT;
+  __shared__ uint32_t wmax[NT / 64];
+  const int tid = threadIdx.x, C = H / 8;
+  const MOEQ_GLOBAL u32x4* xr = gptr(reinterpret_cast<const u32x4*>(x + (size_t)t * H));
+  u32x4 v[NP];
+  uint32_t mx = 0;
+#pragma unroll
+  for (int i = 0; i < NP; ++i) v[i] = xr[min(tid + i * NT, C - 1)];
+#pragma unroll
+  for (int i = 0; i < NP; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) mx = max(mx, max(v[i][j] & 0x7FFFu, (v[i][j] >> 16) & 0x7FFFu));
+  mx = wave_max_u32(mx);
+  if ((tid & 63) == 0) wmax[tid >> 6] = mx;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) mx = max(mx, wmax[w]);
+  const int e = max((int)((mx >> 7) & 0xFFu) - 127 - 14, -100);
+  if (tid == 0) xexp[t] = e;
+  const float sc = __builtin_amdgcn_ldexpf(1.0f, -e);
+  u32x4* out = reinterpret_cast<u32x4*>(x16 + (size_t)t * H);
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    u32x4 o;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float lo = __uint_as_float(v[i][j] << 16) * sc, hi = __uint_as_float(v[i][j] & 0xFFFF0000u) * sc;
+      o[j] = (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)lo) |
+             ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)hi) << 16);
+    }
+    if (tid + i * NT < C) out[tid + i * NT] = o;
+  }
 }
 
 }  // namespace
