@@ -12,21 +12,17 @@
 // experts (no host synchronization: slots beyond the active count exit at
 // once).  Lanes hold neighbouring rows (R of them) at 64 / R neighbouring
 // 128-weight units, so a load of 16-byte chunks takes runs of 16 R bytes
-// (layout.h) and reads the staged activations of only 64 / R units; a lane's
-// waves and lanes of one row meet at the end in a fixed order, so results are
+// (layout.h) and reads the staged activations of only 64 / R units; the lanes
+// and waves that share a row meet at the end in a fixed order, so results are
 // deterministic.  The dot products accumulate in float32; the per-block scale
 // and zero point are applied once per block.
 //
 // gate/up kernel: writes h (float32) for every assignment in bucket order.
-// Arithmetic of the 2-4-bit kernels.  The one-token gate/up kernel and the
-// down kernel stage their activations (x, exactly, and h) in binary16 after a
-// power-of-two prescale per block of 32 (11 significant bits at any
-// magnitude), mask the code pairs out of the packed dwords as binary16
-// subnormals (layout.h) and run the dot products on v_dot2_f32_f16.  The
-// gate/up kernel for buckets of 2-64 tokens stages x in bfloat16 as given and
-// multiplies it with the codes unpacked to bfloat16 (v_dot2_f32_bf16): there,
-// converting four tokens' x per workgroup costs more than the cheaper unpack
-// saves.
+// Arithmetic of the 2-4-bit kernels: the activations (x, exactly, and h) are
+// staged in binary16 after a power-of-two prescale per block of 32 (11
+// significant bits at any magnitude), the code pairs masked out of the packed
+// dwords as binary16 subnormals (layout.h), the dot products run on
+// v_dot2_f32_f16.  The 5/6/8-bit kernels stage bfloat16 and unpack to it.
 // down kernel: the result, times the token's routing weight, is written as
 // one partial row per (token, slot).
 // combine kernel: y_t = sum_j partial(t, j) (j in slot order) + shared.
@@ -333,7 +329,7 @@ __device__ __forceinline__ void down_body(const DecodeArgs& a, const Slot sl, co
 
 // grid = (H / (4 R), S + max_active), 256 threads
 template <int TM, int R>
-__global__ __launch_bounds__(256, 4) void down_kernel(DecodeArgs a) {
+__global__ __launch_bounds__(256, TM <= 4 ? 4 : 2) void down_kernel(DecodeArgs a) {
   extern __shared__ uint32_t smem[];
   const Slot sl = slot_info(a, blockIdx.y);
   if (sl.M < 0 || sl.M > a.gemm_above) return;  // (large buckets: the grouped GEMMs)
@@ -556,8 +552,9 @@ __global__ __launch_bounds__(256) void combine_kernel(DecodeArgs a) {
 constexpr int kGuWaves = 4, kGuThreads = 64 * kGuWaves, kGuHalf = kGuWaves / 2;
 constexpr int kGuRows1 = 16, kGuRowsN = 32;
 
+template <int TM>
 struct GateUpShared {
-  float red[kGuWaves][2][32];
+  float red[kGuWaves][TM][32];
 };
 
 // this lane's share of its row (of the tensor its wave takes); the first
@@ -577,8 +574,8 @@ __device__ __forceinline__ void gateup_dots(const TensorDev& t, int row, int U, 
 template <int TM, int R, typename F>
 __device__ __forceinline__ void gateup_rows(const DecodeArgs& a, const TensorDev& tg, const TensorDev& tu, int f0,
                                             int hrow, int mc, const uint32_t* xl, const float2* xs, int xts, int sts,
-                                            GateUpShared& sh, F stage) {
-  static_assert(128 % R == 0 && R <= 32 && TM <= 2, "whole workgroups, and their sums fit");
+                                            GateUpShared<TM>& sh, F stage) {
+  static_assert(128 % R == 0 && R <= 32, "whole workgroups, and their sums fit");
   const int H = a.H, I = a.I, U = H / kUnit;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const TensorDev& t = wave < kGuHalf ? tg : tu;
@@ -640,7 +637,7 @@ __device__ __forceinline__ bool narrow_gateup(const TensorDev& tg, const TensorD
 // one workgroup's share of the gate/up of a bucket of one token (STAGED: x is
 // in LDS already)
 template <int R, bool STAGED>
-__device__ __forceinline__ void gateup1_slot(const DecodeArgs& a, const Slot& sl, uint32_t* smem, GateUpShared& sh) {
+__device__ __forceinline__ void gateup1_slot(const DecodeArgs& a, const Slot& sl, uint32_t* smem, GateUpShared<1>& sh) {
   const TensorDev tg = a.desc[sl.desc * 3 + 0], tu = a.desc[sl.desc * 3 + 1];
   if (!narrow_gateup(tg, tu)) return;
   uint32_t* xl = smem;
@@ -669,7 +666,7 @@ template <int EPL>
 __global__ __launch_bounds__(kGuThreads, 5) void gateup1_route_kernel(DecodeArgs a, RouterParams rp,
                                                                                 Workspace ws) {
   extern __shared__ uint32_t smem[];
-  __shared__ GateUpShared sh;
+  __shared__ GateUpShared<1> sh;
   __shared__ float gs_l[64];
   __shared__ int32_t chosen[kMaxTopK];
   Slot sl;
@@ -726,15 +723,16 @@ __global__ __launch_bounds__(kGuThreads, 5) void gateup1_route_kernel(DecodeArgs
 // code pairs are unpacked once and multiplied with every staged token.  One
 // launch: two, the larger buckets' on a second stream, cost as much at 16
 // tokens (the streams' events take about 20 us each way) and more below.
+// TM = 2, or 8 for small layers (fits_8_tokens).
 // grid = (I / kGuRowsN, S + max_active), kGuThreads threads
 template <int TM>
 __global__ __launch_bounds__(kGuThreads, TM <= 2 ? 4 : 2) void gateupn_kernel(DecodeArgs a) {
   extern __shared__ uint32_t smem[];
-  __shared__ GateUpShared sh;
+  __shared__ GateUpShared<TM> sh;
   const Slot sl = slot_info(a, blockIdx.y);
   if (sl.M < 1 || sl.M > a.gemm_above) return;
   if (sl.M == 1) {
-    gateup1_slot<kGuRowsN, false>(a, sl, smem, sh);
+    gateup1_slot<kGuRowsN, false>(a, sl, smem, reinterpret_cast<GateUpShared<1>&>(sh));
     return;
   }
   const TensorDev tg = a.desc[sl.desc * 3 + 0], tu = a.desc[sl.desc * 3 + 1];
@@ -1042,12 +1040,20 @@ hipError_t launch_wide_down(const DecodeArgs& a, hipStream_t s) {
   return few ? launch_wide_down_tm<4, 4, 16>(a, s) : launch_wide_down_tm<4, 4, 32>(a, s);
 }
 
+// Layers so small that a pass over a bucket is its latency (loading, staging,
+// two barriers) stage 8 tokens per pass instead of 2 (gate/up) or 4 (down), at
+// most 32 KB of LDS: hidden 512, intermediate 256, 8 tokens 29.4 -> 27.0 us, 15
+// tokens 47.3 -> 42.8, but 3 tokens 21.7 -> 22.3.  With the grouped GEMMs taking
+// the buckets of more than 2 tokens, 2 suffice.
+static bool fits_8_tokens(const DecodeArgs& a, int K) { return a.n > 4 && a.gemm_above > 4 && K / kUnit <= 13; }
+
 hipError_t launch_gateup_decode(const DecodeArgs& a, hipStream_t s) {
-  constexpr int TM = 2;
   const int U = a.H / kUnit;
-  const size_t lds = (size_t)(a.n == 1 ? 1 : TM) * (U * kXStride + U * 8) * 4;
+  const bool small = fits_8_tokens(a, a.H);
+  const size_t lds = (size_t)(a.n == 1 ? 1 : small ? 8 : 2) * (U * kXStride + U * 8) * 4;
   dim3 grid(a.I / kGuRowsN, a.S + a.max_active);
-  return launch_lds(gateupn_kernel<TM>, grid, lds, s, a, kGuThreads);
+  return small ? launch_lds(gateupn_kernel<8>, grid, lds, s, a, kGuThreads)
+               : launch_lds(gateupn_kernel<2>, grid, lds, s, a, kGuThreads);
 }
 
 bool gateup1_routes(const RouterParams& rp) { return !rp.kept_ids && rp.E_row <= 256 && rp.k <= kMaxTopK; }
@@ -1104,6 +1110,8 @@ hipError_t launch_down_decode(const DecodeArgs& a, hipStream_t s) {
   hipError_t e;
   if (a.n == 1)
     e = launch_lds(down_kernel<1, 16>, dim3(a.H / 64, slots), lds1, s, a);
+  else if (fits_8_tokens(a, a.I) && fits_8_tokens(a, a.H))
+    e = launch_lds(down_kernel<8, 16>, dim3(a.H / 64, slots), 8 * lds1, s, a);
   else if (a.H / 128 * slots < 2048)
     e = launch_lds(down_kernel<4, 16>, dim3(a.H / 64, slots), 4 * lds1, s, a);
   else
