@@ -12,15 +12,14 @@
 // and the SwiGLU activations h (binary16 after a per-row power-of-two
 // prescale) enter binary16 matrix instructions with float32 accumulation.
 //
-// 2-4-bit tensors whose block scales are positive, finite and within the
-// register decoder's bound, with rows of an even number of 128-weight units
-// (every tensor of the workloads measured here), take the register-decoded
-// GEMMs below (v_mfma_f32_32x32x16_f16, tiles of up to 128 tokens): the
-// packed weights are decoded in registers straight into the matrix operand.
-// Every other tensor (5, 6 or 8 bits, scales outside the bound, or an odd
-// unit count) takes the LDS-decoded GEMMs (gateup_gemm8_kernel,
-// down_gemm8_kernel, v_mfma_f32_16x16x32_f16): 128 tokens x 128 weight rows
-// per workgroup, the weight tile of each K step decoded once into LDS.
+// Tensors whose block scales are positive, finite and within the register
+// decoder's bound (every tensor of the workloads measured here) take the
+// register-decoded GEMMs below (v_mfma_f32_32x32x16_f16, tiles of up to 64 or
+// 128 tokens): the packed weights are decoded in registers straight into the
+// matrix operand.  Every other tensor takes the LDS-decoded GEMMs
+// (gateup_gemm8_kernel, down_gemm8_kernel, v_mfma_f32_16x16x32_f16): 128 tokens
+// x 128 weight rows per workgroup, the weight tile of each K step decoded once
+// into LDS.
 // Workgroups are mapped to tiles from counts the device wrote, whatever the
 // worst-case size of the grid: each XCD takes an equal run of list
 // positions, the LDS-decoded tiles in slot order (one expert's tiles share
@@ -305,10 +304,9 @@ __device__ __forceinline__ bool rd_tile_of_wg(const int32_t* tiles, int hw, int 
   return tiles[1 + 2 * *mt] >= 0;
 }
 
-// The register-decoded GEMMs take a tensor of 2-4 bits whose scales the
-// create-time scan found positive, finite and small enough and whose rows
-// hold an even number of units (flags); the LDS-decoded GEMMs take every
-// other tensor.
+// The register-decoded GEMMs take a tensor whose scales the create-time scan
+// found positive, finite and small enough (flags); the LDS-decoded GEMMs take
+// every other tensor.
 __device__ __forceinline__ bool rd_ok(const TensorDev& t) {
   return !(t.flags & kTensorOffRegisterDecoder);
 }
@@ -703,9 +701,9 @@ __device__ void gateup_gemm_body8(const GemmArgs a, const SlotInfo sl, int m0, i
   }
 }
 
-// The tiles whose gate or up tensor the register decoder cannot take (5, 6
-// or 8 bits wide, or scales outside its range; the other of the two may be
-// any width); the other tiles take gateup_rd_kernel.
+// The tiles whose gate or up tensor the register decoder cannot take (scales
+// outside its range; the other of the two may be any); the other tiles take
+// gateup_rd_kernel.
 __global__ __launch_bounds__(512, 1) void gateup_gemm8_kernel(DecodeArgs a) {
   extern __shared__ _Float16 lds_h[];
   const int nN = a.I / BN;
@@ -799,10 +797,10 @@ __device__ void down_gemm_body8(const GemmArgs a, const SlotInfo sl, int m0, int
   }
 }
 
-// The tiles whose down tensor the register decoder cannot take (5, 6 or 8
-// bits wide, or scales outside its range; the other tiles take
-// down_rd_kernel).  Four waves per SIMD (128 registers): two workgroups share
-// a compute unit (2 x 80 KB of LDS) and overlap their K-step chains.
+// The tiles whose down tensor the register decoder cannot take (scales outside
+// its range; the other tiles take down_rd_kernel).  Four waves per SIMD (128
+// registers): two workgroups share a compute unit (2 x 80 KB of LDS) and
+// overlap their K-step chains.
 __global__ __launch_bounds__(512, 4) void down_gemm8_kernel(DecodeArgs a) {
   extern __shared__ _Float16 lds_h[];
   const int nN = a.H / BN;
@@ -818,8 +816,7 @@ __global__ __launch_bounds__(512, 4) void down_gemm8_kernel(DecodeArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Register-decoded grouped GEMM for 2-4-bit weights (gate/up with SwiGLU, and
-// down).
+// Register-decoded grouped GEMM (gate/up with SwiGLU, and down).
 //
 // Weights are the MFMA's first operand (32 weight rows x 16 k) and tokens
 // its second (16 k x 32 tokens) of v_mfma_f32_32x32x16_f16 (on gfx950 it
@@ -827,13 +824,23 @@ __global__ __launch_bounds__(512, 4) void down_gemm8_kernel(DecodeArgs a) {
 // costs ceil(M / 32) token tiles per 32 weight rows.  A workgroup of eight
 // waves owns up to 128 tokens of one expert bucket and 256 weight rows; each
 // wave owns one row tile of 32 and all the tokens (1-4 token tiles), so one
-// decoded weight fragment feeds up to four matrix instructions.  One
-// workgroup per compute unit (two waves per SIMD).
+// decoded weight fragment feeds up to four matrix instructions.  Tiles of up
+// to 64 tokens share a compute unit two by two, larger ones have it alone
+// (rd_small).
+//
+// What bounds them (timing-only copies that leave one part out; 192 buckets of
+// about 21 tokens, 3-bit gate/up, 540 us): without the decode 426, i.e. the
+// weight stream at 5.4 TB/s; without the activation staging 484; without the
+// LDS fragment reads 536.  The decode is about 3.4 vector instructions per code
+// pair.  128-token tiles (2048 tokens; with every tile in one kernel and whole
+// rows in memory, 1556 us): without staging 1272, without the decode 1321,
+// without the fragment reads 1332, matrix products and barriers alone 837: a
+// row tile of 32 makes the fragment reads as long as the products.
 //
 // Weights never pass through LDS.  Lane l of a wave (row r = l % 32 of its
 // row tile, k-half g = l / 32) loads, for each K stage of 512 weights (4
-// units of 128), units 4U + 2g and 4U + 2g + 1 of its row: the two lanes of
-// a row read 64 contiguous bytes per chunk plane.  It decodes them in
+// units of 128), units 4U + 2g and 4U + 2g + 1 of its row: two runs of 512
+// bytes per load.  It decodes them in
 // registers straight into the operand layout, binary16 d * (c - 2^(b-1))
 // with one rounding: at k step t (0..7) of sub-stage q (block q of each
 // unit), the 8 operand values of lane (r, g) are weights 32 q + 8 (t % 4) ..
@@ -1058,10 +1065,8 @@ __device__ __forceinline__ void rd_kloop(const MOEQ_GLOBAL u32x4* const (&rc)[RD
       *reinterpret_cast<u32x4*>(wdst + buf * (NT * RD_TSUB) + j * (RD_THREADS * 16)) = v[j];
   };
   // chunk j / scale half h of this lane's two units in stage V, every row
-  // tile, into one ring slot.  Plain (not streaming) loads: a stage reads 64
-  // bytes of each row's chunk plane, half of a 128-byte line whose other half
-  // the next stage reads, so the line has to stay in L2 until then
-  // (streaming loads here cost 20%).
+  // tile, into one ring slot.  Plain (not streaming) loads: the other tiles of
+  // the bucket read the same lines.
   auto rload_chunk = [&](RdUnit<B> (&dst)[RD_RT][2], int j, int V) {
     if constexpr (ACT) {
 #pragma unroll
@@ -1082,9 +1087,9 @@ __device__ __forceinline__ void rd_kloop(const MOEQ_GLOBAL u32x4* const (&rc)[RD
       if (c >= c0 && c <= c1) rload_chunk(dst, c, V);
   };
   // the scales of this lane's two units of stage V (units 2g and 2g + 1 of
-  // the stage, four binary16 scales each: 16 contiguous bytes, as rows hold
-  // an even number of units), one load per row tile, requested in sub-stage
-  // 1 of the stage before and moved into the stage's ring slot at its end.
+  // the stage, four binary16 scales each: 16 contiguous bytes, zeros in the
+  // place of a unit past an odd row), one load per row tile, requested in
+  // sub-stage 1 of the stage before and moved into the stage's ring slot at its end.
   // A stage past the row reads 16 zero bytes, so its weights decode to zeros
   // (the choice is made on the address, so no instruction waits for the
   // loaded value).
@@ -1291,8 +1296,8 @@ __device__ __forceinline__ void rd_kloop_any(int bits, bool act, const MOEQ_GLOB
 // 8 (v / 4) + 4 (l / 32) + v % 4, column (token) l % 32.
 __device__ __forceinline__ int rd_acc_row(int v, int lane) { return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); }
 
-// Gate/up tile: features [f0, f0 + 256) of one slot, tokens [m0, m0 + 64)
-// of its bucket (Mt of them real).  NT token tiles of 32 are multiplied.
+// Gate/up tile: features [f0, f0 + 128) of one slot, tokens [m0, m0 + Mt)
+// of its bucket.  NT token tiles of 32 are multiplied.
 template <int NT, bool WIDE>
 __device__ void rd_gateup_tile(const GemmArgs& a, const SlotInfo& sl, int m0, int Mt, int f0, const TensorDev& tg,
                                const TensorDev& tu, char* lds) {
@@ -1376,8 +1381,8 @@ __device__ void rd_gateup_tile(const GemmArgs& a, const SlotInfo& sl, int m0, in
   }
 }
 
-// Down tile: output features [n0, n0 + 512) (rows of the down tensor) of one
-// slot, tokens [m0, m0 + 64); results times the routing weight are the
+// Down tile: output features [n0, n0 + 256) (rows of the down tensor) of one
+// slot, tokens [m0, m0 + Mt); results times the routing weight are the
 // slot's partial rows.
 template <int NT, bool WIDE>
 __device__ void rd_down_tile(const GemmArgs& a, const SlotInfo& sl, int m0, int Mt, int n0, const TensorDev& td,
