@@ -17,9 +17,13 @@
 #include "internal.h"
 
 // decode forwards of at least MOEQ_HYBRID_FROM tokens send the buckets of
-// more than MOEQ_HYBRID_ABOVE rows to the grouped GEMMs
+// more than MOEQ_HYBRID_ABOVE rows to the grouped GEMMs.  From 16 tokens,
+// skewed batches would gain (20 Zipf-routed tokens 317 us, by GEMVs 519), evenly
+// routed ones lose (16 tokens N(0,1) 399, 393), and y loses precision: the GEMMs
+// round the weights and scale h by rows instead of blocks of 32 (16 tokens,
+// relative error against float64 3.2e-4 instead of 2.2e-4)
 #ifndef MOEQ_HYBRID_FROM
-#define MOEQ_HYBRID_FROM 16
+#define MOEQ_HYBRID_FROM 24
 #endif
 #ifndef MOEQ_HYBRID_ABOVE
 #define MOEQ_HYBRID_ABOVE 2
@@ -225,7 +229,7 @@ moeq_status check_device(const moeq_layer* L) {
 // buckets built by the tile-list launch of the grouped GEMMs if one workgroup's
 // LDS holds them.
 bool buckets_with_tiles(const moeq_layer* L, int n) {
-  return n >= MOEQ_HYBRID_FROM && bucket_fits(n, L->cfg.n_experts);
+  return n >= 16 && bucket_fits(n, L->cfg.n_experts);
 }
 
 // Route (+ bucket) n tokens into the workspace: the first stage of a forward.

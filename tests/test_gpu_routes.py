@@ -1,8 +1,10 @@
 """The branches that sizes and widths choose between, at their edges, against
 the CPU oracle:
 
-* the decode path around 16 tokens, where buckets of more than 2 tokens begin
+* the decode path around 24 tokens, where buckets of more than 2 tokens begin
   to take the grouped GEMMs and the many-token router replaces the small one;
+* the prefill path around 16 tokens, where the tile lists' launch begins to
+  build the buckets;
 * the buckets built by one workgroup with the tile lists, at the edges of its
   64-token chunks and of the LDS it may use;
 * the grouped GEMMs at the edges of their 32-token tiles, for every width in the
@@ -53,13 +55,14 @@ def _layer(moeq, shape, plan, key, max_tokens):
 
 
 @pytest.mark.parametrize("plan", ["all4", "p234_602020", "wide_all"])
-def test_decode_around_16_tokens(gpu_lib, plan):
-    data, L = _layer(gpu_lib, synth.TINY, plan, f"routes-16-{plan}", 17)
-    for n in (15, 16, 17):
+def test_few_tokens_around_switches(gpu_lib, plan):
+    data, L = _layer(gpu_lib, synth.TINY, plan, f"routes-16-{plan}", 25)
+    for n in (15, 16, 17, 23, 24, 25):
         logits = synth.normal_logits(n, data.shape.n_experts, "routes-16", n)
         idx = _check(gpu_lib, data, L, n, "routes-16", logits, gpu_lib.MOEQ_PATH_DECODE)
         sizes = np.bincount(idx.ravel())
         assert (sizes[sizes > 0] <= 2).any() and (sizes > 2).any()
+        _check(gpu_lib, data, L, n, "routes-16", logits, gpu_lib.MOEQ_PATH_PREFILL)
     L.close()
 
 
