@@ -42,11 +42,11 @@ MFMA_F16_PEAK_TFLOPS = 2500.0   # dense fp16 / bf16 matrix peak of one MI355X
 # sha256: any change to them reports traffic as null until the counters are
 # retaken.
 GATEUP_TRAFFIC = {
-    "bytes": 127422233,
+    "bytes": 127100115,
     "sources": {
-        "paper_2509_25689_amd/csrc/decode.hip": "115a87a545c2200d351c0a348f881c93749bd8e2a0a9df9136ea075383b65585",
-        "paper_2509_25689_amd/csrc/layout.h": "ec9f6185567429769228f45977ef62d3009e3530746c8104eb4a54119a1468b5",
-        "paper_2509_25689_amd/csrc/route_wave.h": "eb3854b178047d6ade2936070a4e74a0b27d75ca6945b4e3099ddd0a53941b6d",
+        "paper_2509_25689_amd/csrc/decode.hip": "1f49015d776a54128972eef2d8ee919cf503d0ad36d3779b7a3dbc9f28767e4a",
+        "paper_2509_25689_amd/csrc/layout.h": "2f1dc7876c82d861b96751e8e82ae7721817d9769ccd27b178ff6994351f8b75",
+        "paper_2509_25689_amd/csrc/route_wave.h": "a248bab68313b27d9daa07c8cf1e8d95cab6c36e6356757025f76c17cb2c279b",
     },
 }
 
