@@ -226,10 +226,10 @@ moeq_status check_device(const moeq_layer* L) {
 
 // The many-token router (a workgroup per 4 tokens) instead of the small one
 // (one workgroup for everything: 12 us at 16 tokens, 26-37 at 48), with the
-// buckets built by the tile-list launch of the grouped GEMMs if one workgroup's
-// LDS holds them.
+// buckets built by the tile-list launch of the grouped GEMMs if one workgroup
+// serves (bucket_fits).
 bool buckets_with_tiles(const moeq_layer* L, int n) {
-  return n >= 16 && bucket_fits(n, L->cfg.n_experts);
+  return n >= 16 && bucket_fits(n, L->cfg.top_k, L->cfg.n_experts);
 }
 
 // Route (+ bucket) n tokens into the workspace: the first stage of a forward.

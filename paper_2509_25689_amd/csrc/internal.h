@@ -196,7 +196,7 @@ int prefill_max_rtiles(int n, int k, int S, int n_kept, int rd_tile);
 // the tile list (and cleared h row maxima) and, with a.x, the binary16 copy of
 // x; then the gate/up GEMMs, then h in binary16 and the down GEMMs.  With ws the
 // launch also buckets a.idx (bucket_fits)
-bool bucket_fits(int n, int E);
+bool bucket_fits(int n, int k, int E);
 hipError_t launch_prefill_tiles(const DecodeArgs& a, const Workspace* ws, hipStream_t s);
 hipError_t launch_gateup_prefill(const DecodeArgs& a, hipStream_t s);
 hipError_t launch_down_prefill(const DecodeArgs& a, hipStream_t s);

@@ -206,7 +206,7 @@ template <int EPL>
 __device__ __forceinline__ void bucket_all(const DecodeArgs& a, const Workspace& ws, unsigned long long* lds) {
   const int tid = threadIdx.x, E = a.E, k = a.k, nk = a.n * a.k, C = (a.n + kChunk - 1) / kChunk;
   unsigned long long* mask = lds;
-  uint16_t* pre = reinterpret_cast<uint16_t*>(mask + (size_t)C * E);
+  uint16_t* pre = reinterpret_cast<uint16_t*>(mask + (size_t)C * E);  // (n <= 65535: bucket_fits)
   int32_t* total = reinterpret_cast<int32_t*>(lds + (size_t)C * E + ((size_t)C * E + 3) / 4);
   int32_t* off = total + E;
   for (int i = tid; i < C * E; i += 1024) mask[i] = 0ull;
@@ -1630,8 +1630,18 @@ static size_t bucket_lds_bytes(int n, int E) {
   const size_t ce = (size_t)((n + kChunk - 1) / kChunk) * E;
   return ce * 8 + (ce + 3) / 4 * 8 + (2 * (size_t)E + 1) * 4;
 }
-// (beside the 21 KB of the tile lists: 2560 tokens over 256 experts)
-bool bucket_fits(int n, int E) { return bucket_lds_bytes(n, E) <= 104 * 1024; }
+// Three bounds.  LDS: 104 KB beside the 21 KB of the tile lists (2560 tokens
+// over 256 experts).  The counts: an expert's running count over the chunks has
+// 16 bits, and it may take every token.  Time: one workgroup walks the n k
+// assignments twice, while the chunked kernels pay three launches and a serial
+// scan over the n / 64 chunks, so the line moves with k (us of a forward of
+// hidden = intermediate = 128, chunked -> one workgroup: k = 2, 8 experts, 16384
+// tokens 160 -> 122; k = 6, 16 experts, 10000 156 -> 153, 30000 444 -> 452; k = 8, 8
+// experts, 2048 67.0 -> 67.4, 4096 94 -> 101; k = 16, 32 experts, 800 60 -> 58, 1600
+// 75 -> 79; k = 32, 64 experts, 400 62 -> 61, 800 75 -> 83).
+bool bucket_fits(int n, int k, int E) {
+  return n <= 0xFFFF && (long long)n * (k - 5) <= 8192 && bucket_lds_bytes(n, E) <= 104 * 1024;
+}
 
 namespace {
 template <int EPL>

@@ -6,7 +6,8 @@ the CPU oracle:
 * the prefill path around 16 tokens, where the tile lists' launch begins to
   build the buckets;
 * the buckets built by one workgroup with the tile lists, at the edges of its
-  64-token chunks and of the LDS it may use;
+  64-token chunks, of the LDS it may use, of its 16-bit counts and of the sizes
+  it is the faster at, and a forward above 65535 tokens;
 * the grouped GEMMs at the edges of their 32-token tiles, for every width in the
   register decoder, rows of an odd number of 128-weight units, and lists of
   64- and 128-token tiles;
@@ -67,9 +68,12 @@ def test_few_tokens_around_switches(gpu_lib, plan):
 
 
 @pytest.mark.parametrize("E,k,sizes", [(16, 2, (15, 16, 63, 64, 65, 128, 129)), (256, 8, (16, 64, 65, 2559, 2561)),
-                                       (1024, 4, (17, 576, 577))])
+                                       (1024, 4, (17, 576, 577)), (8, 2, (65535, 65536)),
+                                       (8, 8, (2730, 2731, 70001)), (1, 1, (65535, 65537)),
+                                       (64, 32, (303, 304))])
 def test_bucket_one_workgroup(gpu_lib, E, k, sizes):
-    shape = synth.LayerShape(hidden=128, inter=128, n_experts=E, n_kept=E, n_shared=0, n_group=1, topk_group=1, top_k=k)
+    shape = synth.LayerShape(hidden=128, inter=128, n_experts=E, n_kept=E, n_shared=0, n_group=1, topk_group=1, top_k=k,
+                             group_topn=min(2, E))
     one = layers.quantized_layer(shape, "all2", "routes-bucket")
     t = one.tensor("r", 0, 0), one.tensor("r", 0, 1), one.tensor("r", 0, 2)
     L = gpu_lib.Layer(shape, np.ones(E, np.uint8), {e: t for e in range(E)}, [], max_tokens=max(sizes))
@@ -81,6 +85,24 @@ def test_bucket_one_workgroup(gpu_lib, E, k, sizes):
         torch.cuda.synchronize()
         roff, rperm, _ = obucket.bucket(idx, E)
         assert np.array_equal(off.cpu().numpy(), roff) and np.array_equal(perm.cpu().numpy(), rperm), n
+    L.close()
+
+
+def test_forward_above_16_bit_counts(gpu_lib):
+    """70001 tokens that all take all 8 experts: every expert's count is past
+    65535.  The oracle checks tokens spread over the batch and its ends."""
+    shape = synth.LayerShape(hidden=128, inter=128, n_experts=8, n_kept=8, n_shared=1, n_group=1, topk_group=1, top_k=8)
+    n = 70001
+    data, L = _layer(gpu_lib, shape, "p234_602020", "routes-70001", n)
+    x_bits = synth.activations(n, shape.hidden, "routes-70001")
+    logits = synth.normal_logits(n, 8, "routes-70001")
+    y = L.forward(_dev(x_bits.view(np.int16), torch.bfloat16), _dev(logits))
+    torch.cuda.synchronize()
+    rows = np.unique(np.concatenate([np.arange(0, n, 997), np.arange(65530, 65545), np.arange(n - 4, n)]))
+    idx, w = router.route(logits[rows], data.mask, n_group=1, topk_group=1, top_k=8, group_topn=shape.group_topn,
+                          norm_topk=shape.norm_topk, routed_scale=shape.routed_scale)
+    err = moe.token_errors(y.cpu().numpy()[rows], layers.oracle_forward(data, x_bits[rows], idx, w))
+    assert err.max() <= TOL, err.max()
     L.close()
 
 
