@@ -240,6 +240,7 @@ __device__ __forceinline__ void unit_dots(const uint32_t* w, u32x2 sc, const uin
     uint32_t p[16];
     block_pairs_sub<B>(w + q * B, p);
     const float ds = block_scale_sub(sc, q);
+    if constexpr (TM == 1) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int m = 0; m < TM; ++m)
       if (TM == 1 || m < mc) acc[m] = block_dot_sub<B>(p, xu + m * xts + 16 * q, ds, su4[m * sts + q], acc[m]);
@@ -249,6 +250,14 @@ __device__ __forceinline__ void unit_dots(const uint32_t* w, u32x2 sc, const uin
 // This lane's share of a row against the staged tokens: units u0, u0 + step,
 // ... < U, the next one in flight while one is reduced; `first` holds unit
 // min(u0, U - 1).
+// One token: no branch in the loop.  A lane past the row computes on its last
+// unit and drops the result, and an odd unit comes after the loop; scheduling
+// barriers keep the next unit's requests before this one's products.  With a
+// branch around the products the compiler no longer knows which loads are
+// outstanding and waited for a unit's chunks before it requested the next
+// (one token of the benchmark's layer, 7 slots 36.9 -> 35.9 us, 9 slots 44.1
+// -> 42.8).  Several tokens keep the branches: without them the products of
+// both units are scheduled together and spill.
 template <int B, int TM>
 __device__ __forceinline__ void row_dots(const RowPtr& r, int U, int u0, int step, const uint32_t* xl,
                                          const float2* xs, int xts, int sts, int mc, const UnitBuf<B>& first,
@@ -258,17 +267,38 @@ __device__ __forceinline__ void row_dots(const RowPtr& r, int U, int u0, int ste
 #pragma unroll
   for (int m = 0; m < TM; ++m) acc[m] = 0.0f;
   const int n = (U + step - 1) / step;  // the same for every lane
+  // (requests past the row repeat its last unit)
+  auto load = [&](UnitBuf<B>& b, int i) { load_unit_buf<B>(b, r, min(u0 + step * min(i, n - 1), U - 1)); };
+  if constexpr (TM == 1) {
+    auto dots = [&](const UnitBuf<B>& b, int i) {
+      const int u = u0 + step * i, uc = min(u, U - 1);
+      float v[1] = {acc[0]};
+      unit_dots<B, 1>(b.w, b.s, xl + uc * kXStride, xs + uc * 4, xts, sts, mc, v);
+      acc[0] = u < U ? v[0] : acc[0];
+    };
 #pragma unroll 1
-  for (int i0 = 0; i0 < n; i0 += 2) {
-    asm volatile("" ::: "memory");
+    for (int i = 0; i + 2 <= n; i += 2) {
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int i = i0 + b;
-      if (i < n) {
-        // the next unit (clamped to the row's last) goes out before this one is reduced
-        load_unit_buf<B>(buf[1 - b], r, min(u0 + step * min(i + 1, n - 1), U - 1));
-        const int u = u0 + step * i;
-        if (u < U) unit_dots<B, TM>(buf[b].w, buf[b].s, xl + u * kXStride, xs + u * 4, xts, sts, mc, acc);
+      for (int b = 0; b < 2; ++b) {
+        load(buf[1 - b], i + b + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        dots(buf[b], i + b);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    if (n & 1) dots(buf[0], n - 1);
+  } else {
+#pragma unroll 1
+    for (int i0 = 0; i0 < n; i0 += 2) {
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        const int i = i0 + b;
+        if (i < n) {
+          load(buf[1 - b], i + 1);
+          const int u = u0 + step * i;
+          if (u < U) unit_dots<B, TM>(buf[b].w, buf[b].s, xl + u * kXStride, xs + u * 4, xts, sts, mc, acc);
+        }
       }
     }
   }
@@ -634,16 +664,17 @@ __device__ __forceinline__ bool narrow_gateup(const TensorDev& tg, const TensorD
   return tg.codes && tu.codes && tg.bits <= 4 && tu.bits <= 4;
 }
 
-// one workgroup's share of the gate/up of a bucket of one token (STAGED: x is
-// in LDS already)
-template <int R, bool STAGED>
-__device__ __forceinline__ void gateup1_slot(const DecodeArgs& a, const Slot& sl, uint32_t* smem, GateUpShared<1>& sh) {
+// one workgroup's share of the gate/up of a bucket of one token (staged: x is
+// in LDS already; one instance for both, uniform over the workgroup)
+template <int R>
+__device__ __forceinline__ void gateup1_slot(const DecodeArgs& a, const Slot& sl, uint32_t* smem, GateUpShared<1>& sh,
+                                             bool staged) {
   const TensorDev tg = a.desc[sl.desc * 3 + 0], tu = a.desc[sl.desc * 3 + 1];
   if (!narrow_gateup(tg, tu)) return;
   uint32_t* xl = smem;
   float2* xs = reinterpret_cast<float2*>(smem + a.H / kUnit * kXStride);
   gateup_rows<1, R>(a, tg, tu, blockIdx.x * R, sl.base, 1, xl, xs, 0, 0, sh, [&] {
-    if constexpr (!STAGED) {
+    if (!staged) {
       // (one token: token 0, without reading the bucket permutation, which the
       // routing workgroup of gateup1_route_kernel may still be writing)
       stage_x_token(a, sl.shared >= 0 || a.n == 1 ? 0 : a.perm[sl.base] / a.k, xl, xs);
@@ -669,6 +700,7 @@ __global__ __launch_bounds__(kGuThreads, 5) void gateup1_route_kernel(DecodeArgs
   __shared__ GateUpShared<1> sh;
   __shared__ float gs_l[64];
   __shared__ int32_t chosen[kMaxTopK];
+  rp.kept_ids = nullptr;  // (gateup1_routes)
   Slot sl;
   if ((int)blockIdx.y < a.S) {
     sl = slot_info(a, blockIdx.y);
@@ -708,14 +740,12 @@ __global__ __launch_bounds__(kGuThreads, 5) void gateup1_route_kernel(DecodeArgs
     }
     __syncthreads();
     const int i = blockIdx.y - a.S;
-    sl.desc = chosen[i];
+    sl.desc = __builtin_amdgcn_readfirstlane(chosen[i]);
     sl.base = i;
     sl.M = 1;
     sl.shared = -1;
-    gateup1_slot<kGuRows1, true>(a, sl, smem, sh);
-    return;
   }
-  gateup1_slot<kGuRows1, false>(a, sl, smem, sh);
+  gateup1_slot<kGuRows1>(a, sl, smem, sh, (int)blockIdx.y >= a.S);
 }
 
 // ---------------------------------------------------------------------------
@@ -732,7 +762,7 @@ __global__ __launch_bounds__(kGuThreads, TM <= 2 ? 4 : 2) void gateupn_kernel(De
   const Slot sl = slot_info(a, blockIdx.y);
   if (sl.M < 1 || sl.M > a.gemm_above) return;
   if (sl.M == 1) {
-    gateup1_slot<kGuRowsN, false>(a, sl, smem, reinterpret_cast<GateUpShared<1>&>(sh));
+    gateup1_slot<kGuRowsN>(a, sl, smem, reinterpret_cast<GateUpShared<1>&>(sh), false);
     return;
   }
   const TensorDev tg = a.desc[sl.desc * 3 + 0], tu = a.desc[sl.desc * 3 + 1];
