@@ -750,6 +750,17 @@ __global__ __launch_bounds__(kGuThreads, 5) void gateup1_route_kernel(DecodeArgs
   gateup1_slot<kGuRows1>(a, sl, smem, sh, (int)blockIdx.y >= a.S);
 }
 
+// A forward of one token whose routing is a launch of its own (regrouped
+// experts, or more than 256): the same 16 rows per workgroup (32 in
+// gateupn_kernel: 56.7 instead of 53.9 us per step of the benchmark's layer).
+// grid = (I / kGuRows1, S + max_active), kGuThreads threads
+__global__ __launch_bounds__(kGuThreads, 5) void gateup1_kernel(DecodeArgs a) {
+  extern __shared__ uint32_t smem[];
+  __shared__ GateUpShared<1> sh;
+  const Slot sl = slot_info(a, blockIdx.y);
+  if (sl.M == 1) gateup1_slot<kGuRows1>(a, sl, smem, sh, false);
+}
+
 // ---------------------------------------------------------------------------
 // The buckets of 1 .. gemm_above tokens, TM tokens staged per pass: each unit's
 // code pairs are unpacked once and multiplied with every staged token.  One
@@ -1081,8 +1092,11 @@ static bool fits_8_tokens(const DecodeArgs& a, int K) { return a.n > 4 && a.gemm
 
 hipError_t launch_gateup_decode(const DecodeArgs& a, hipStream_t s) {
   const int U = a.H / kUnit;
+  const size_t token_lds = (size_t)(U * kXStride + U * 8) * 4;
+  if (a.n == 1)
+    return launch_lds(gateup1_kernel, dim3(a.I / kGuRows1, a.S + a.max_active), token_lds, s, a, kGuThreads);
   const bool small = fits_8_tokens(a, a.H);
-  const size_t lds = (size_t)(a.n == 1 ? 1 : small ? 8 : 2) * (U * kXStride + U * 8) * 4;
+  const size_t lds = (small ? 8 : 2) * token_lds;
   dim3 grid(a.I / kGuRowsN, a.S + a.max_active);
   return small ? launch_lds(gateupn_kernel<8>, grid, lds, s, a, kGuThreads)
                : launch_lds(gateupn_kernel<2>, grid, lds, s, a, kGuThreads);

@@ -11,6 +11,8 @@ the CPU oracle:
 * the grouped GEMMs at the edges of their 32-token tiles, for every width in the
   register decoder, rows of an odd number of 128-weight units, and lists of
   64- and 128-token tiles;
+* one token whose routing is a launch of its own (regrouped or more than 256
+  experts), which the gate/up takes in 16 rows per workgroup;
 * one and two tokens with a 5/6/8-bit shared down tensor, with one shared expert
   (the down kernel ends the forward) and two (a combine follows).
 
@@ -44,7 +46,8 @@ def _check(moeq, data, L, n, key, logits, path):
     y = L.forward(_dev(x_bits.view(np.int16), torch.bfloat16), _dev(logits))
     torch.cuda.synchronize()
     idx, w = router.route(logits, data.mask, n_group=s.n_group, topk_group=s.topk_group, top_k=s.top_k,
-                          group_topn=s.group_topn, norm_topk=s.norm_topk, routed_scale=s.routed_scale)
+                          group_topn=s.group_topn, norm_topk=s.norm_topk, routed_scale=s.routed_scale,
+                          regroup=bool(s.regroup))
     err = moe.token_errors(y.cpu().numpy(), layers.oracle_forward(data, x_bits, idx, w))
     assert err.max() <= TOL, (n, err.max(), int(err.argmax()))
     return idx
@@ -140,4 +143,18 @@ def test_decode_wide_shared_down(gpu_lib, n_shared, bits):
     for n in (1, 2):
         logits = synth.normal_logits(n, shape.n_experts, "routes-sh", n)
         _check(gpu_lib, data, L, n, "routes-sh", logits, gpu_lib.MOEQ_PATH_AUTO)
+    L.close()
+
+
+@pytest.mark.parametrize("plan", ["p234_602020", "wide_all"])
+@pytest.mark.parametrize("shape", [
+    synth.LayerShape(hidden=384, inter=640, n_experts=16, n_kept=12, n_shared=1, n_group=4, topk_group=2, top_k=3,
+                     regroup=1),
+    synth.LayerShape(hidden=128, inter=384, n_experts=320, n_kept=240, n_shared=2, n_group=8, topk_group=4, top_k=6)],
+    ids=["regroup", "320_experts"])
+def test_one_token_routed_apart(gpu_lib, shape, plan):
+    data, L = _layer(gpu_lib, shape, plan, f"routes-apart-{shape.n_experts}", 2)
+    for n in (1, 2):
+        logits = synth.normal_logits(n, shape.n_experts, "routes-apart", n)
+        _check(gpu_lib, data, L, n, "routes-apart", logits, gpu_lib.MOEQ_PATH_DECODE)
     L.close()
