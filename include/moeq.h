@@ -215,15 +215,17 @@ const char* moeq_last_error(void);
 moeq_status moeq_set_path(moeq_layer* layer, int32_t path);
 
 /* Diagnostic: the router stage of the forward alone (Section 3.2 grouped
- * top-k over the experts kept by Section 3.1).  Runs the same device code
- * the forward would run for this n_tokens.
+ * top-k over the experts kept by Section 3.1).  Runs the routing kernel that
+ * the forward would run for this n_tokens on the path set (one token that the
+ * gate/up kernel routes itself: the same routing function in its own launch).
  *   logits  DEVICE float32 [n_tokens x n_experts]
  *   idx     DEVICE int32 [n_tokens x top_k]: chosen experts, best first
  *   w       DEVICE float32 [n_tokens x top_k]: their combine weights */
 moeq_status moeq_route(moeq_layer* layer, const float* logits, int32_t n_tokens,
                        int32_t* idx, float* w, void* stream);
 
-/* Diagnostic: the bucketing stage alone, on given expert ids.
+/* Diagnostic: the bucketing stage alone, on given expert ids, by the kernels
+ * that the forward would run for this n_tokens on the path set.
  *   idx      DEVICE int32 [n_tokens x top_k]; every id a kept expert, ids of
  *            one token distinct (as the router produces)
  *   offsets  DEVICE int32 [n_experts + 1]: exclusive prefix sum of counts

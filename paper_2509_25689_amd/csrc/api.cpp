@@ -232,14 +232,24 @@ bool buckets_with_tiles(const moeq_layer* L, int n) {
   return n >= 16 && bucket_fits(n, L->cfg.top_k, L->cfg.n_experts);
 }
 
+bool takes_prefill(const moeq_layer* L, int n) {
+  return L->path == MOEQ_PATH_PREFILL || (L->path == MOEQ_PATH_AUTO && n > L->decode_max);
+}
+// decode forwards of several tokens: the buckets of more than
+// MOEQ_HYBRID_ABOVE rows (the large buckets of a skewed routing) take the
+// grouped GEMMs, which read an expert's weights once for all its tokens
+bool takes_hybrid(const moeq_layer* L, int n) { return !takes_prefill(L, n) && n >= MOEQ_HYBRID_FROM; }
+// a forward of n tokens runs the grouped GEMMs
+bool takes_gemms(const moeq_layer* L, int n) { return takes_prefill(L, n) || takes_hybrid(L, n); }
+
 // Route (+ bucket) n tokens into the workspace: the first stage of a forward.
-// With x (the grouped GEMMs follow) a call that buckets_with_tiles serves
-// leaves the buckets to the tile-list launch; *copied tells whether the
-// prescaled copy of x was made here.
+// Where the grouped GEMMs follow, a call that buckets_with_tiles serves leaves
+// the buckets to the tile-list launch; *copied tells whether the prescaled copy
+// of x (not made without x) was made here.
 hipError_t route_and_bucket(moeq_layer* L, const float* logits, int n, hipStream_t s, const void* x = nullptr,
                             bool* copied = nullptr) {
   const RouterParams rp = router_params(L, logits);
-  const bool tiles = x && buckets_with_tiles(L, n);
+  const bool tiles = takes_gemms(L, n) && buckets_with_tiles(L, n);
   if (n <= kDecodeMaxTokens && !tiles) return launch_route_bucket_small(rp, nullptr, n, L->ws, s);
   if (copied) *copied = x != nullptr;
   hipError_t e = launch_route_tokens(rp, n, L->ws.idx, L->ws.w, (const uint16_t*)x, L->cfg.hidden, L->ws, s);
@@ -554,12 +564,7 @@ moeq_status moeq_forward(moeq_layer* L, const void* x, const float* logits, int3
   if (st != MOEQ_OK) return st;
   hipStream_t s = (hipStream_t)stream;
   DecodeArgs a = decode_args(L, x, n, y);
-  const bool prefill =
-      L->path == MOEQ_PATH_PREFILL || (L->path == MOEQ_PATH_AUTO && n > L->decode_max);
-  // decode forwards of several tokens: the buckets of more than
-  // MOEQ_HYBRID_ABOVE rows (the large buckets of a skewed routing) take the
-  // grouped GEMMs, which read an expert's weights once for all its tokens
-  const bool hybrid = !prefill && n >= MOEQ_HYBRID_FROM;
+  const bool prefill = takes_prefill(L, n), hybrid = takes_hybrid(L, n);
   a.gemm_above = prefill ? 0 : hybrid ? MOEQ_HYBRID_ABOVE : kDecodeMaxTokens;
   hipError_t e = hipSuccess;
   auto mark = [&](int i) {
@@ -857,12 +862,12 @@ moeq_status moeq_bucket(moeq_layer* L, const int32_t* idx, int32_t n, int32_t* o
     e = hipMemsetAsync(offsets, 0, (size_t)(E + 1) * 4, s);
     return e == hipSuccess ? ok() : hip_fail(e, "bucket");
   }
-  if (n <= kDecodeMaxTokens && !buckets_with_tiles(L, n)) {
-    e = launch_route_bucket_small(router_params(L, nullptr), idx, n, L->ws, s);
-  } else if (buckets_with_tiles(L, n)) {
+  if (takes_gemms(L, n) && buckets_with_tiles(L, n)) {
     DecodeArgs a = decode_args(L, nullptr, n, nullptr);
     a.idx = idx;
     e = launch_prefill_tiles(a, &L->ws, s);
+  } else if (n <= kDecodeMaxTokens) {
+    e = launch_route_bucket_small(router_params(L, nullptr), idx, n, L->ws, s);
   } else {
     e = launch_bucket_chunked(idx, n, k, E, L->ws, s);
   }

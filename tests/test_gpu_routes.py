@@ -80,6 +80,7 @@ def test_bucket_one_workgroup(gpu_lib, E, k, sizes):
     one = layers.quantized_layer(shape, "all2", "routes-bucket")
     t = one.tensor("r", 0, 0), one.tensor("r", 0, 1), one.tensor("r", 0, 2)
     L = gpu_lib.Layer(shape, np.ones(E, np.uint8), {e: t for e in range(E)}, [], max_tokens=max(sizes))
+    L.set_path(gpu_lib.MOEQ_PATH_PREFILL)
     r = np.random.default_rng(E)
     for n in sizes:
         # skewed: low ids often, some experts never
