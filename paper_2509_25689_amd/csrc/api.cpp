@@ -33,8 +33,6 @@ using namespace moeq;
 
 namespace {
 thread_local std::string g_last_error;
-
-constexpr int kMaxDevices = 64;
 }  // namespace
 
 moeq_status moeq::vset_error(moeq_status st, const char* fmt, va_list ap) {

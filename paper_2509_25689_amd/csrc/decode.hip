@@ -1040,14 +1040,17 @@ __global__ __launch_bounds__(64 * NW) void wide_down_kernel(DecodeArgs a) {
   }
 }
 
-// launches a kernel whose dynamic LDS may exceed the 64 KiB default
-template <typename K>
-hipError_t launch_lds(K kernel, dim3 grid, size_t lds, hipStream_t s, const DecodeArgs& a, int threads = 256) {
+// launches a kernel whose dynamic LDS may exceed the 64 KiB default: the
+// largest is the wide down kernel's, 4 tokens of intermediate 8192
+constexpr size_t kMostLds = 4 * (2 * 64 * kXStride + 64 * 4) * 4;
+template <auto Kernel>
+hipError_t launch_lds(dim3 grid, size_t lds, hipStream_t s, const DecodeArgs& a, int threads = 256) {
   if (lds > 65536) {
-    const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    static std::atomic<uint64_t> done{0};
+    const hipError_t e = raise_lds_limit((const void*)Kernel, done, kMostLds);
     if (e != hipSuccess) return e;
   }
-  kernel<<<grid, threads, lds, s>>>(a);
+  Kernel<<<grid, threads, lds, s>>>(a);
   return hipGetLastError();
 }
 
@@ -1056,7 +1059,7 @@ hipError_t launch_wide_gateup_tm(const DecodeArgs& a, hipStream_t s) {
   const int U = a.H / kUnit;
   const size_t lds = (size_t)TM * (U * kXStride + U * 4) * 4;
   dim3 grid(a.I / R, a.wide_gateup == 1 ? a.S : a.S + a.max_active);
-  return launch_lds(wide_gateup_kernel<TM, NW, R>, grid, lds, s, a, 64 * NW);
+  return launch_lds<wide_gateup_kernel<TM, NW, R>>(grid, lds, s, a, 64 * NW);
 }
 
 template <int TM, int NW, int R>
@@ -1064,7 +1067,7 @@ hipError_t launch_wide_down_tm(const DecodeArgs& a, hipStream_t s) {
   const int U = a.I / kUnit;
   const size_t lds = (size_t)TM * (2 * U * kXStride + U * 4) * 4;
   dim3 grid(a.H / R, a.wide_down == 1 ? a.S : a.S + a.max_active);
-  return launch_lds(wide_down_kernel<TM, NW, R>, grid, lds, s, a, 64 * NW);
+  return launch_lds<wide_down_kernel<TM, NW, R>>(grid, lds, s, a, 64 * NW);
 }
 
 }  // namespace
@@ -1094,12 +1097,12 @@ hipError_t launch_gateup_decode(const DecodeArgs& a, hipStream_t s) {
   const int U = a.H / kUnit;
   const size_t token_lds = (size_t)(U * kXStride + U * 8) * 4;
   if (a.n == 1)
-    return launch_lds(gateup1_kernel, dim3(a.I / kGuRows1, a.S + a.max_active), token_lds, s, a, kGuThreads);
+    return launch_lds<gateup1_kernel>(dim3(a.I / kGuRows1, a.S + a.max_active), token_lds, s, a, kGuThreads);
   const bool small = fits_8_tokens(a, a.H);
   const size_t lds = (small ? 8 : 2) * token_lds;
   dim3 grid(a.I / kGuRowsN, a.S + a.max_active);
-  return small ? launch_lds(gateupn_kernel<8>, grid, lds, s, a, kGuThreads)
-               : launch_lds(gateupn_kernel<2>, grid, lds, s, a, kGuThreads);
+  return small ? launch_lds<gateupn_kernel<8>>(grid, lds, s, a, kGuThreads)
+               : launch_lds<gateupn_kernel<2>>(grid, lds, s, a, kGuThreads);
 }
 
 bool gateup1_routes(const RouterParams& rp) { return !rp.kept_ids && rp.E_row <= 256 && rp.k <= kMaxTopK; }
@@ -1155,13 +1158,13 @@ hipError_t launch_down_decode(const DecodeArgs& a, hipStream_t s) {
   const int slots = a.S + a.max_active;
   hipError_t e;
   if (a.n == 1)
-    e = launch_lds(down_kernel<1, 16>, dim3(a.H / 64, slots), lds1, s, a);
+    e = launch_lds<down_kernel<1, 16>>(dim3(a.H / 64, slots), lds1, s, a);
   else if (fits_8_tokens(a, a.I) && fits_8_tokens(a, a.H))
-    e = launch_lds(down_kernel<8, 16>, dim3(a.H / 64, slots), 8 * lds1, s, a);
+    e = launch_lds<down_kernel<8, 16>>(dim3(a.H / 64, slots), 8 * lds1, s, a);
   else if (a.H / 128 * slots < 2048)
-    e = launch_lds(down_kernel<4, 16>, dim3(a.H / 64, slots), 4 * lds1, s, a);
+    e = launch_lds<down_kernel<4, 16>>(dim3(a.H / 64, slots), 4 * lds1, s, a);
   else
-    e = launch_lds(down_kernel<4, 32>, dim3(a.H / 128, slots), 4 * lds1, s, a);
+    e = launch_lds<down_kernel<4, 32>>(dim3(a.H / 128, slots), 4 * lds1, s, a);
   return e;
 }
 

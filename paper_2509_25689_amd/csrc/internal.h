@@ -6,6 +6,8 @@
 #include <stdarg.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "moeq.h"
 
 namespace moeq {
@@ -23,6 +25,7 @@ constexpr int kMaxShared = 4;
 constexpr int kChunk = 64;          // tokens per bucketing chunk (one bit per token in a 64-bit mask)
 constexpr int kDecodeMaxTokens = 64;
 constexpr int kDefaultDecodeMax = 64;
+constexpr int kMaxDevices = 64;
 
 // One stored tensor in the device layout.
 //   codes:  tiles of 64 rows (rows are a multiple of 128), each U = K/128 units
@@ -87,6 +90,22 @@ struct Workspace {
   uint16_t* h16;       // [(T*k + T*S) x I] binary16 h * 2^-(row exponent) (many-token path)
   uint32_t* zeros;     // [64]    zeroed at create, never written again
 };
+
+// Raises a kernel's dynamic LDS limit to the most it is ever launched with,
+// once per device and kernel (`done`): set per call to the call's own need, a
+// thread could lower it between another's setting and launch.
+inline hipError_t raise_lds_limit(const void* kernel, std::atomic<uint64_t>& done, size_t most) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = dev < kMaxDevices ? 1ull << dev : 0ull;
+  if (!bit || !(done.load(std::memory_order_acquire) & bit)) {
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
+    if (e != hipSuccess) return e;
+    done.fetch_or(bit, std::memory_order_release);
+  }
+  return hipSuccess;
+}
 
 // ---- launchers (return hipSuccess or the launch error) ----
 // route.hip

@@ -25,8 +25,6 @@
 // positions, the LDS-decoded tiles in slot order (one expert's tiles share
 // its L2), the register-decoded ones sorted by work and dealt to the XCDs
 // in turn (equal work per XCD).
-#include <atomic>
-
 #include "internal.h"
 #include "layout.h"
 #include "route_wave.h"
@@ -1588,21 +1586,12 @@ int prefill_max_rtiles(int n, int k, int S, int n_kept, int rd_tile) {
 
 namespace {
 
-// Raises a GEMM kernel's dynamic LDS limit (once per device and kernel), then
-// launches it.
-constexpr int kMaxDevices = 64;
+// Launches a GEMM kernel, whose LDS is the same in every call.
 template <typename K>
 hipError_t launch_gemm(K kernel, std::atomic<uint64_t>& done, int block, int grid, size_t lds, hipStream_t s,
                        const DecodeArgs& a) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
+  const hipError_t e = raise_lds_limit((const void*)kernel, done, lds);
   if (e != hipSuccess) return e;
-  const uint64_t bit = dev < kMaxDevices ? 1ull << dev : 0ull;
-  if (!bit || !(done.load(std::memory_order_acquire) & bit)) {
-    e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    done.fetch_or(bit, std::memory_order_release);
-  }
   kernel<<<grid, block, lds, s>>>(a);
   return hipGetLastError();
 }
@@ -1626,6 +1615,7 @@ hipError_t launch_dequant_gemm(const TensorDev& t, uint16_t* out, hipStream_t s)
   return hipGetLastError();
 }
 
+constexpr size_t kBucketLds = 104 * 1024;
 static size_t bucket_lds_bytes(int n, int E) {
   const size_t ce = (size_t)((n + kChunk - 1) / kChunk) * E;
   return ce * 8 + (ce + 3) / 4 * 8 + (2 * (size_t)E + 1) * 4;
@@ -1640,15 +1630,15 @@ static size_t bucket_lds_bytes(int n, int E) {
 // experts, 2048 67.0 -> 67.4, 4096 94 -> 101; k = 16, 32 experts, 800 60 -> 58, 1600
 // 75 -> 79; k = 32, 64 experts, 400 62 -> 61, 800 75 -> 83).
 bool bucket_fits(int n, int k, int E) {
-  return n <= 0xFFFF && (long long)n * (k - 5) <= 8192 && bucket_lds_bytes(n, E) <= 104 * 1024;
+  return n <= 0xFFFF && (long long)n * (k - 5) <= 8192 && bucket_lds_bytes(n, E) <= kBucketLds;
 }
 
 namespace {
 template <int EPL>
 hipError_t launch_tiles(const DecodeArgs& a, const Workspace& ws, size_t lds, hipStream_t s) {
-  if (lds > 40 * 1024) {
-    const hipError_t e = hipFuncSetAttribute((const void*)prefill_tiles_kernel<EPL>,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if constexpr (EPL > 0) {
+    static std::atomic<uint64_t> done{0};
+    const hipError_t e = raise_lds_limit((const void*)prefill_tiles_kernel<EPL>, done, kBucketLds);
     if (e != hipSuccess) return e;
   }
   prefill_tiles_kernel<EPL><<<a.x ? 1 + a.n : 1, 1024, lds, s>>>(a, ws);
