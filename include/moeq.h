@@ -273,8 +273,10 @@ moeq_status moeq_dequant_as(moeq_layer* layer, int32_t expert, int32_t proj, int
 moeq_status moeq_quantize(const float* w, int32_t rows, int32_t K, int32_t bits,
                           void* codes, uint16_t* scales, void* stream);
 
-/* Sizes: weight bytes as stored (codes plus scales of every kept expert and
- * shared expert) and workspace bytes.  Either pointer may be NULL. */
+/* Sizes: weight bytes in the canonical packing (codes plus scales of every kept
+ * expert and shared expert; on the device a tensor starts on 256 bytes, and the
+ * scales of a row of an odd number of 128-weight units are padded by one unit)
+ * and workspace bytes.  Either pointer may be NULL. */
 moeq_status moeq_layer_bytes(const moeq_layer* layer, uint64_t* weight_bytes,
                              uint64_t* workspace_bytes);
 

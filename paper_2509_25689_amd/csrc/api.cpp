@@ -76,7 +76,7 @@ struct moeq_layer {
   int path = MOEQ_PATH_AUTO;
   int decode_max = kDefaultDecodeMax;
   int n_kept = 0;
-  uint64_t weight_bytes = 0;   // codes + scales as stored
+  uint64_t weight_bytes = 0;   // codes + scales in the canonical packing
   uint64_t ws_bytes = 0;
   std::vector<TensorDev> desc_host;  // [(E + S) * 3]
   void* store = nullptr;

@@ -116,6 +116,9 @@ def test_gemm_tile_edges_odd_units(gpu_lib, plan):
     experts, so their buckets (and the shared expert's) hold n tokens."""
     shape = synth.LayerShape(hidden=384, inter=640, n_experts=4, n_kept=4, n_shared=1, n_group=1, topk_group=1, top_k=2)
     data, L = _layer(gpu_lib, shape, plan, f"routes-odd-{plan}", 129)
+    # the reported weight bytes are the canonical packing's, whatever the layout pads
+    canonical = sum(t["codes"].nbytes + t["scales"].nbytes for tr in [*data.routed().values(), *data.shared()] for t in tr)
+    assert L.bytes()[0] == canonical
     for n in (1, 31, 32, 33, 64, 65, 96, 97, 128, 129):
         logits = synth.normal_logits(n, 4, "routes-odd", n)
         logits[:, [1, 2]] += 20.0
