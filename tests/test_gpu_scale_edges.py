@@ -2,21 +2,24 @@
 
 That decoder forms binary16(d * (c - z)) with one fused multiply-add from
 d * 2^(14 + b), so it takes a tensor only if every scale is a positive finite
-binary16 no larger than the largest d for which that product stays finite; a
-scan at layer creation sends every other 2-4-bit tensor to the LDS-decoded
-GEMMs, whose decoder has no such bound.  Both must produce the format's
+binary16 no larger than the largest d for which that product stays finite (0.0156
+at 8 bits); a scan at layer creation sends every other tensor, of any width, to
+the LDS-decoded GEMMs, whose decoder has no such bound.  Both must produce the
+format's
 binary16 weights bit for bit (the oracle's dequantize_half: Section 3.3's
 weight = d * (c - 2^(b-1)), rounded once) and a prefill forward within the
 output tolerance of the fp64 oracle.
 
-Edits on the tiny layer (one per tensor, the rest of the tensor unchanged):
+Edits on the tiny layer, at 2-4 bits mixed, at 5, 6 and 8 bits and at every width
+mixed (one per tensor, the rest of the tensor unchanged):
 * shared gate: every scale times 64 (far above the bound at any width);
 * a routed down tensor: one block scale zero;
 * a routed up tensor: one block scale negated;
 * a routed gate tensor: one block scale the smallest positive subnormal
   (still on the register decoder);
 * another routed down tensor: one block scale exactly at the bound (still on
-  the register decoder; d * 2^(14 + b) is the largest finite binary16)."""
+  the register decoder; d * 2^(14 + b) is the largest finite binary16);
+* a third routed down tensor: one block scale the next binary16 above it."""
 import numpy as np
 import pytest
 import torch
@@ -61,9 +64,9 @@ def _set_block(value):
     return f
 
 
-@pytest.fixture(scope="module")
-def edited(gpu_lib):
-    base = layers.quantized_layer(synth.TINY, "p234_602020", "scale-edges")
+@pytest.fixture(scope="module", params=["p234_602020", "all5", "all6", "all8", "wide_all"])
+def edited(gpu_lib, request):
+    base = layers.quantized_layer(synth.TINY, request.param, "scale-edges")
     kept = [int(e) for e in np.nonzero(base.mask)[0]]
     edits = {
         ("s", 0, 0): _times64,
@@ -71,6 +74,7 @@ def edited(gpu_lib):
         ("r", kept[1], 1): _set_block(lambda v, b: int(v) | 0x8000),
         ("r", kept[2], 0): _set_block(lambda v, b: 1),
         ("r", kept[3], 2): _set_block(lambda v, b: rd_scale_limit(b)),
+        ("r", kept[4], 2): _set_block(lambda v, b: rd_scale_limit(b) + 1),
     }
     data = EditedLayer(base, edits)
     L = gpu_lib.Layer(data.shape, data.mask, data.routed(), data.shared(), max_tokens=256)
@@ -100,7 +104,7 @@ def test_scale_edges_reach_both_decoders(edited):
         bad = ((s & 0x8000) != 0) | ((s & 0x7FFF) == 0) | ((s & 0x7FFF) > rd_scale_limit(t["bits"]))
         lim_over += bool(bad.any())
         lim_under += bool(not bad.any())
-    assert lim_over == 3 and lim_under == 2
+    assert lim_over == 4 and lim_under == 2
 
 
 @pytest.mark.parametrize("path", [1, 2])
