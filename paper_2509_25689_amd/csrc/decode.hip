@@ -766,10 +766,11 @@ __global__ __launch_bounds__(kGuThreads, 5) void gateup1_kernel(DecodeArgs a) {
 // code pairs are unpacked once and multiplied with every staged token.  One
 // launch: two, the larger buckets' on a second stream, cost as much at 16
 // tokens (the streams' events take about 20 us each way) and more below.
-// TM = 2, or 8 for small layers (fits_8_tokens).
+// TM = 2, or 8 for small layers (fits_8_tokens); W workgroups per compute unit
+// at least.
 // grid = (I / kGuRowsN, S + max_active), kGuThreads threads
-template <int TM>
-__global__ __launch_bounds__(kGuThreads, TM <= 2 ? 4 : 2) void gateupn_kernel(DecodeArgs a) {
+template <int TM, int W>
+__global__ __launch_bounds__(kGuThreads, W) void gateupn_kernel(DecodeArgs a) {
   extern __shared__ uint32_t smem[];
   __shared__ GateUpShared<TM> sh;
   const Slot sl = slot_info(a, blockIdx.y);
@@ -1086,12 +1087,26 @@ hipError_t launch_wide_down(const DecodeArgs& a, hipStream_t s) {
   return few ? launch_wide_down_tm<4, 4, 16>(a, s) : launch_wide_down_tm<4, 4, 32>(a, s);
 }
 
+// A gate/up launch of more than 8 workgroups per compute unit.
+static bool many_gateup_groups(const DecodeArgs& a) {
+  return (long long)(a.I / kGuRowsN) * (a.S + a.max_active) > 2048;
+}
+
 // Layers so small that a pass over a bucket is its latency (loading, staging,
 // two barriers) stage 8 tokens per pass instead of 2 (gate/up) or 4 (down), at
-// most 32 KB of LDS: hidden 512, intermediate 256, 8 tokens 29.4 -> 27.0 us, 15
-// tokens 47.3 -> 42.8, but 3 tokens 21.7 -> 22.3.  With the grouped GEMMs taking
-// the buckets of more than 2 tokens, 2 suffice.
-static bool fits_8_tokens(const DecodeArgs& a, int K) { return a.n > 4 && a.gemm_above > 4 && K / kUnit <= 13; }
+// most 13 units of 128 weights (32 KB of LDS).  With the grouped GEMMs taking
+// the buckets of more than 2 tokens, 2 suffice.  Above 13 units per down row and
+// in a long launch the buckets of one token decide, which the larger kernel
+// serves no faster: 8 tokens then only for buckets of 2 and more on average.
+// us per step, 2 / 4 tokens per pass -> 8 (4 bits; units per gate/up, down row;
+// kept experts, top-k): 4, 2 (48, 6): 8 tokens 31.0 -> 29.0, 23: 69.5 -> 62.2; 8, 8:
+// 43.3 -> 40.4, 98.0 -> 86.2; 13, 13: 62.9 -> 61.6, 145 -> 126; 13, 13 (192, 8): 74.3 ->
+// 76.9, 192 -> 167; 13, 32 (12, 2): 74.3 -> 71.0; 13, 32 (48, 6): 108 -> 111 (not
+// taken), 16 tokens 183 -> 176.
+static bool fits_8_tokens(const DecodeArgs& a, int K) {
+  return a.n > 4 && a.gemm_above > 4 && K / kUnit <= 13 &&
+         (a.I / kUnit <= 13 || !many_gateup_groups(a) || (long long)a.n * a.k >= 2ll * a.max_active);
+}
 
 hipError_t launch_gateup_decode(const DecodeArgs& a, hipStream_t s) {
   const int U = a.H / kUnit;
@@ -1101,8 +1116,13 @@ hipError_t launch_gateup_decode(const DecodeArgs& a, hipStream_t s) {
   const bool small = fits_8_tokens(a, a.H);
   const size_t lds = (small ? 8 : 2) * token_lds;
   dim3 grid(a.I / kGuRowsN, a.S + a.max_active);
-  return small ? launch_lds<gateupn_kernel<8>>(grid, lds, s, a, kGuThreads)
-               : launch_lds<gateupn_kernel<2>>(grid, lds, s, a, kGuThreads);
+  if (!small) return launch_lds<gateupn_kernel<2, 4>>(grid, lds, s, a, kGuThreads);
+  // four workgroups per compute unit cost a few spilled registers (9, 9 units,
+  // 12 kept, 8 tokens 41.0 -> 41.5 us; 8, 8 units, 192 kept, 23 tokens 101 -> 104) and
+  // pay where many buckets of one token wait on their weights (4, 13 units, 192
+  // kept, 8 tokens 56.7 -> 53.3; 13, 13: 74.9 -> 73.3)
+  return a.I / kUnit > 8 && many_gateup_groups(a) ? launch_lds<gateupn_kernel<8, 4>>(grid, lds, s, a, kGuThreads)
+                                                  : launch_lds<gateupn_kernel<8, 2>>(grid, lds, s, a, kGuThreads);
 }
 
 bool gateup1_routes(const RouterParams& rp) { return !rp.kept_ids && rp.E_row <= 256 && rp.k <= kMaxTopK; }

@@ -11,6 +11,8 @@ the CPU oracle:
 * the grouped GEMMs at the edges of their 32-token tiles, for every width in the
   register decoder, rows of an odd number of 128-weight units, and lists of
   64- and 128-token tiles;
+* the matrix-vector kernels at odd numbers of 128-weight units per row, with 8
+  tokens staged per pass (up to 13 units) and with fewer;
 * one token whose routing is a launch of its own (regrouped or more than 256
   experts), which the gate/up takes in 16 rows per workgroup;
 * one and two tokens with a 5/6/8-bit shared down tensor, with one shared expert
@@ -161,4 +163,31 @@ def test_one_token_routed_apart(gpu_lib, shape, plan):
     for n in (1, 2):
         logits = synth.normal_logits(n, shape.n_experts, "routes-apart", n)
         _check(gpu_lib, data, L, n, "routes-apart", logits, gpu_lib.MOEQ_PATH_DECODE)
+    L.close()
+
+
+@pytest.mark.parametrize("plan", ["p234_602020", "wide_all"])
+@pytest.mark.parametrize("hu,iu", [(3, 5), (5, 11), (11, 3), (13, 9), (14, 13), (9, 14)])
+def test_decode_odd_units(gpu_lib, hu, iu, plan):
+    """hu / iu units of 128 weights per gate/up / down row."""
+    shape = synth.LayerShape(hidden=128 * hu, inter=128 * iu, n_experts=8, n_kept=6, n_shared=1, n_group=2,
+                             topk_group=1, top_k=2)
+    data, L = _layer(gpu_lib, shape, plan, f"routes-units-{hu}-{iu}-{plan}", 12)
+    for n in (1, 2, 4, 5, 6, 12):
+        logits = synth.normal_logits(n, 8, "routes-units", n)
+        _check(gpu_lib, data, L, n, "routes-units", logits, gpu_lib.MOEQ_PATH_DECODE)
+    L.close()
+
+
+@pytest.mark.parametrize("iu", [13, 14])
+def test_decode_many_buckets(gpu_lib, iu):
+    """More than 2048 gate/up workgroups: 12 tokens over 40 experts make buckets
+    of one token on average, 21 tokens of two and more."""
+    shape = synth.LayerShape(hidden=128, inter=128 * iu, n_experts=48, n_kept=40, n_shared=1, n_group=1, topk_group=1,
+                             top_k=4)
+    data, L = _layer(gpu_lib, shape, "p234_602020", f"routes-many-{iu}", 21)
+    for n in (12, 21):
+        logits = synth.normal_logits(n, 48, "routes-many", n)
+        idx = _check(gpu_lib, data, L, n, "routes-many", logits, gpu_lib.MOEQ_PATH_DECODE)
+        assert (np.bincount(idx.ravel()) == 1).any() and iu * 4 * 41 > 2048
     L.close()
