@@ -878,17 +878,40 @@ __device__ __noinline__ WideAcc<TM> wide_row_dot(const TensorDev t, int row, int
   const RowPtr rp = row_ptr(t, B, U, row);
   UnitBuf<B> buf[2];
   load_unit_buf<B>(buf[0], rp, min(j, U - 1));
+  auto load = [&](UnitBuf<B>& b, int i) { load_unit_buf<B>(b, rp, min(j + step * min(i, UPL - 1), U - 1)); };
+  if constexpr (TM == 1) {
+    // (no branch in the loop, as in row_dots: one token of the benchmark's layer
+    // with an 8-bit shared expert 62.3 -> 60.3 us, every width mixed 81.5 -> 78.7)
+    auto dots = [&](const UnitBuf<B>& b, int i) {
+      const int u = j + step * i, uc = min(u, U - 1);
+      float v[1] = {r.v[0]};
+      wide_unit_dot<B, NX, 1>(b, xl + uc * kXStride, xts, lo, xs + uc * 4, sts, 1, v);
+      r.v[0] = u < U ? v[0] : r.v[0];
+    };
 #pragma unroll 1
-  for (int i0 = 0; i0 < UPL; i0 += 2) {
-    asm volatile("" ::: "memory");
+    for (int i = 0; i + 2 <= UPL; i += 2) {
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int i = i0 + b;
-      if (i < UPL) {
-        // the next unit (clamped to the last valid one) goes out before this one is reduced
-        load_unit_buf<B>(buf[1 - b], rp, min(j + step * min(i + 1, UPL - 1), U - 1));
-        const int u = j + step * i;
-        if (u < U) wide_unit_dot<B, NX, TM>(buf[b], xl + u * kXStride, xts, lo, xs + u * 4, sts, mc, r.v);
+      for (int b = 0; b < 2; ++b) {
+        load(buf[1 - b], i + b + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        dots(buf[b], i + b);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    if (UPL & 1) dots(buf[0], UPL - 1);
+  } else {
+#pragma unroll 1
+    for (int i0 = 0; i0 < UPL; i0 += 2) {
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        const int i = i0 + b;
+        if (i < UPL) {
+          // the next unit (clamped to the last valid one) goes out before this one is reduced
+          load(buf[1 - b], i + 1);
+          const int u = j + step * i;
+          if (u < U) wide_unit_dot<B, NX, TM>(buf[b], xl + u * kXStride, xts, lo, xs + u * 4, sts, mc, r.v);
+        }
       }
     }
   }
@@ -1087,7 +1110,12 @@ hipError_t launch_wide_down_tm(const DecodeArgs& a, hipStream_t s) {
 hipError_t launch_wide_gateup(const DecodeArgs& a, hipStream_t s) {
   if (!a.wide_gateup) return hipSuccess;
   const bool few = a.wide_gateup == 1;  // shared experts only
-  if (a.n == 1) return few ? launch_wide_gateup_tm<1, 4, 8>(a, s) : launch_wide_gateup_tm<1, 4, 32>(a, s);
+  // shared experts only: 8 rows per workgroup unless 16 still make one per compute
+  // unit (us per step, 6 bits, 8 -> 16 rows: one shared expert of the benchmark's
+  // layer 57.2 -> 58.9, two 68.6 -> 66.6, four 91.4 -> 84.1)
+  if (a.n == 1 && few)
+    return a.S * (a.I / 16) >= 256 ? launch_wide_gateup_tm<1, 4, 16>(a, s) : launch_wide_gateup_tm<1, 4, 8>(a, s);
+  if (a.n == 1) return launch_wide_gateup_tm<1, 4, 32>(a, s);
   return few ? launch_wide_gateup_tm<4, 8, 16>(a, s) : launch_wide_gateup_tm<4, 4, 32>(a, s);
 }
 
