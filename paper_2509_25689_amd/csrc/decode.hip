@@ -589,9 +589,12 @@ __global__ __launch_bounds__(256) void combine_kernel(DecodeArgs a) {
 // each wave R rows at 64 / R units per step, the units of a row dealt to the
 // two waves of its tensor.  The partial sums meet in LDS in wave order.
 // One token: R = 16, so that the nine slots of the benchmark's layer make 1152
-// workgroups, all resident at once (R = 32: 27.4 instead of 26.4 us; eight
-// waves of 32 rows: 29.6).  More tokens: R = 32, which halves the staging of
-// x per weight (16 tokens: 297 -> 270 us beside the one-token buckets).
+// workgroups, all resident at once (R = 32: 56.7 instead of 53.9 us per step,
+// regrouped).  More tokens: R = 32, which halves the staging of x per weight (16
+// tokens: 297 -> 270 us beside the one-token buckets).  Workgroups in launch order:
+// renumbered so that the four of a 64-row tile share an XCD, or so that an XCD
+// sees every quarter of its tiles, a step of one token takes 0.5 to 0.8 us more;
+// with three units in flight instead of two 1.5 us more at 7 slots.
 constexpr int kGuWaves = 4, kGuThreads = 64 * kGuWaves, kGuHalf = kGuWaves / 2;
 constexpr int kGuRows1 = 16, kGuRowsN = 32;
 
@@ -1186,7 +1189,7 @@ size_t down1_lds(const DecodeArgs& a) {
   return NS * units * (kXStride * 4 + 4 * sizeof(float2));
 }
 
-// three slots in flight per lane (two: the same; four: 19.5 instead of 18.3 us)
+// three slots in flight per lane (two: the same; four: 1.2 us slower)
 template <int BD>
 hipError_t launch_down1_b(const DecodeArgs& a, hipStream_t s) {
   down1_kernel<BD, 3><<<a.H / 32, 512, down1_lds(a), s>>>(a);

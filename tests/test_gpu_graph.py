@@ -82,7 +82,7 @@ def test_graph_replay_tiny(gpu_lib, tiny_layer, n, path):
 @pytest.mark.parametrize("n", [1, 16, 48])
 def test_graph_replay_v3(gpu_lib, v3_layer, n):
     """The V3 decode layer on the automatic path: the benchmark's batch-1
-    forward, 16 tokens, and 48 tokens (8-wave gate/up workgroups)."""
+    forward, 16 tokens (GEMVs) and 48 tokens (GEMVs and grouped GEMMs)."""
     data, L = v3_layer
     _check_replays(gpu_lib, L, data.shape, n, gpu_lib.MOEQ_PATH_AUTO, f"graph-v3-{n}")
 

@@ -166,8 +166,9 @@ def test_one_token_routed_apart(gpu_lib, shape, plan):
     L.close()
 
 
-@pytest.mark.parametrize("plan", ["p234_602020", "wide_all"])
-@pytest.mark.parametrize("hu,iu", [(3, 5), (5, 11), (11, 3), (13, 9), (14, 13), (9, 14)])
+@pytest.mark.parametrize("hu,iu,plan", [(3, 5, "p234_602020"), (3, 5, "wide_all"), (5, 11, "wide_all"),
+                                        (11, 3, "p234_602020"), (11, 3, "wide_all"), (13, 9, "p234_602020"),
+                                        (14, 13, "p234_602020"), (9, 14, "p234_602020")])
 def test_decode_odd_units(gpu_lib, hu, iu, plan):
     """hu / iu units of 128 weights per gate/up / down row."""
     shape = synth.LayerShape(hidden=128 * hu, inter=128 * iu, n_experts=8, n_kept=6, n_shared=1, n_group=2,
